@@ -179,9 +179,10 @@ at_status at_create(const at_problem* prob, const at_delay* delay, void* ws_dev,
 
 /* Set u^0 (the initial condition of Sec. 5.1 eq. IC or any field; bulk
  * precision, device, [nz][ny][nx] x fastest, copied) and reset the step
- * counter to 0. Every ring slot is filled with the edge strips of u^0 (no
- * level exists before t = 0; the start-up clamp of the delays keeps their
- * weights at zero). AT_EINVAL for a null pointer. */
+ * counter to 0. The ring slot of level 0 takes the edge strips of u^0 (no
+ * level exists before t = 0: the start-up clamp of the delays keeps their
+ * weights at zero, so no other slot counts before it is published).
+ * AT_EINVAL for a null pointer. */
 at_status at_set_state(at_ctx* ctx, const void* u0_dev);
 
 /* Advance nsteps time steps (queued on the context's stream, asynchronous):
@@ -358,8 +359,8 @@ at_status at_ens_workspace_size(int32_t count, const at_ens_member* members, int
 at_status at_ens_create(int32_t count, const at_ens_member* members, int32_t precision, void* ws_dev,
                         size_t ws_bytes, void* hip_stream, at_ens** out);
 
-/* Set u^0 of every member (packed, device, bulk precision), fill every ring
- * slot with its edge strips and reset the step counter to 0. */
+/* Set u^0 of every member (packed, device, bulk precision), publish its edge
+ * strips as level 0 and reset the step counter to 0. */
 at_status at_ens_set_state(at_ens* ens, const void* u0_dev);
 
 /* Advance every member nsteps steps in ONE persistent launch: a workgroup

@@ -429,7 +429,7 @@ at_status at_set_state(at_ctx* c, const void* u0_dev) {
   if (!c || !u0_dev) return fail(c, AT_EINVAL, "null argument");
   HIP_TRY(c, launch_field_copy(c->sp, c->g.f64, u0_dev, c->sp.ubuf[0], true, c->stream));
   HIP_TRY(c, launch_set_counter(c->sp.counter, 0, c->stream));
-  if (c->delay.mode != AT_SYNC) HIP_TRY(c, launch_publish_all(c->sp, c->g.f64, c->g.sd, c->stream));
+  if (c->delay.mode != AT_SYNC) HIP_TRY(c, launch_publish_level0(c->sp, c->g.f64, c->g.sd, c->stream));
   c->n = 0;
   c->state_set = true;
   return AT_OK;

@@ -298,22 +298,18 @@ __global__ __launch_bounds__(MAXT) void ens_steps_kernel(EnsParams p) {
   if (threadIdx.x == 0) advance_counter(p.counter, n0 + p.nsteps - 1);
 }
 
-// Every ring slot of every member holds the edge strips of u^0.
+// The edge strips of u^0 into the ring slot of level 0 of every member (the
+// other slots are published before they are read with a nonzero weight).
 template <typename Real>
-__global__ __launch_bounds__(256) void ens_publish_all_kernel(EnsParams p) {
+__global__ __launch_bounds__(256) void ens_publish_level0_kernel(EnsParams p) {
   const EnsMember& M = p.mem[blockIdx.x];
   if (M.mode == AT_SYNC) return;
-  const Real* u = static_cast<const Real*>(p.u[0]);
-  Real* ring = static_cast<Real*>(p.ring);
-  const int s = M.s;
-  const int64_t per_slot = static_cast<int64_t>(M.npe) * 2 * s;
-  for (int64_t j = threadIdx.x; j < per_slot * M.nslots; j += blockDim.x) {
-    const int64_t e = j % per_slot;
-    const int pe = static_cast<int>(e / (2 * s));
-    const int face = static_cast<int>((e / s) % 2);
-    const int d = static_cast<int>(e % s);
-    const int64_t src = static_cast<int64_t>(pe) * M.b + (face ? M.b - s + d : d);
-    ring[M.ring_off + j] = u[M.off + src];
+  const Real* u = static_cast<const Real*>(p.u[0]) + M.off;
+  Real* ring = static_cast<Real*>(p.ring) + M.ring_off;
+  const int s = M.s, b = M.b, faces = M.npe * 2;
+  for (int j = threadIdx.x; j < faces; j += blockDim.x) {
+    const Real* src = u + static_cast<int64_t>(j >> 1) * b + ((j & 1) ? b - s : 0);
+    for (int d = 0; d < s; ++d) ring[static_cast<int64_t>(j) * s + d] = src[d];
   }
 }
 
@@ -499,11 +495,11 @@ hipError_t launch_ens_steps(const EnsParams& p, bool f64, int nbins, int threads
   return hipGetLastError();
 }
 
-hipError_t launch_ens_publish_all(const EnsParams& p, bool f64, int count, hipStream_t st) {
+hipError_t launch_ens_publish_level0(const EnsParams& p, bool f64, int count, hipStream_t st) {
   if (f64)
-    hipLaunchKernelGGL(ens_publish_all_kernel<double>, dim3(count), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(ens_publish_level0_kernel<double>, dim3(count), dim3(256), 0, st, p);
   else
-    hipLaunchKernelGGL(ens_publish_all_kernel<float>, dim3(count), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(ens_publish_level0_kernel<float>, dim3(count), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 

@@ -58,7 +58,7 @@ struct EnsStatsParams {
 
 hipError_t launch_ens_stats(const EnsStatsParams& p, hipStream_t st);
 hipError_t launch_ens_steps(const EnsParams& p, bool f64, int nbins, int threads, hipStream_t st);
-hipError_t launch_ens_publish_all(const EnsParams& p, bool f64, int count, hipStream_t st);
+hipError_t launch_ens_publish_level0(const EnsParams& p, bool f64, int count, hipStream_t st);
 hipError_t launch_ens_norms(const EnsNormParams& p, bool f64, int count, hipStream_t st);
 
 }  // namespace atfd

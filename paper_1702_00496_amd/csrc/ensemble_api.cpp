@@ -298,7 +298,7 @@ at_status at_ens_set_state(at_ens* e, const void* u0_dev) {
   // the sweep reads f^{n-1} at every step and weights it by an exact zero at
   // n = 0 (and for Euler members): it must hold finite values from the start
   if (e->ep.f) ENS_TRY(e, hipMemsetAsync(e->ep.f, 0, e->field_bytes, e->stream));
-  if (e->ring_elems) ENS_TRY(e, launch_ens_publish_all(e->ep, e->f64, e->count, e->stream));
+  if (e->ring_elems) ENS_TRY(e, launch_ens_publish_level0(e->ep, e->f64, e->count, e->stream));
   e->n = 0;
   e->state_set = true;
   return AT_OK;
