@@ -365,14 +365,16 @@ at_status at_ens_set_state(at_ens* ens, const void* u0_dev);
 
 /* Advance every member nsteps steps in ONE persistent launch: a workgroup
  * loops over the steps of its members with a workgroup barrier between
- * steps. The launch is captured into a HIP graph the first time a given
+ * steps (a member that fits stays on its compute unit for all of them). The launch is captured into a HIP graph the first time a given
  * nsteps is run and the graph is replayed afterwards (the start step is read
  * from a device counter). */
 at_status at_ens_run(at_ens* ens, int64_t nsteps);
 
 /* Schedule: workgroups per compute unit (1, 2 or 4) and threads per
  * workgroup (256, 512 or 1024); 0 keeps the current value. Results are
- * bit-identical for every choice. */
+ * bit-identical for every choice. The default is one workgroup of 1024
+ * threads, or more and smaller ones where there are more members than
+ * compute units and all are short. */
 at_status at_ens_set_tuning(at_ens* ens, int32_t groups_per_cu, int32_t threads);
 
 /* The workgroup schedule of the persistent launch (host arrays): `*nbins`
@@ -381,7 +383,8 @@ at_status at_ens_set_tuning(at_ens* ens, int32_t groups_per_cu, int32_t threads)
  * per member; either may be NULL to query *nbins first). A workgroup holds
  * the descriptors of at most AT_ENS_BATCH members at a time: a larger bin
  * runs every step for its first AT_ENS_BATCH members, then for the next
- * ones (members are independent problems). */
+ * ones, and a member kept on the compute unit runs all its steps before the
+ * next (members are independent problems). */
 enum { AT_ENS_BATCH = 24 };
 at_status at_ens_get_schedule(const at_ens* ens, int32_t* nbins, int32_t* bin_start, int32_t* order);
 

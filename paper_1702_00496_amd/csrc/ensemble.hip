@@ -3,7 +3,9 @@
 // see them with random delays (Sec. 2; Sec. 5.1 simulation of delays). A
 // member never spans two workgroups, so one persistent launch can run all
 // steps: each workgroup loops over the steps of its members with a workgroup
-// barrier between steps (all members' data stay in L2 / Infinity Cache).
+// barrier between steps. A member that fits is kept on the compute unit
+// (line.hpp: registers and LDS, no memory traffic between steps); the others
+// are streamed through L2 / Infinity Cache.
 //
 // Per point and step: the standard central difference on level n for taps
 // inside the PE (Sec. 2 eq. general_deriv), the AT combination in double of
@@ -14,6 +16,8 @@
 // are published to the ring slot of level n + 1.
 
 #include "ensemble.hpp"
+
+#include <type_traits>
 
 namespace atfd {
 namespace {
@@ -72,7 +76,7 @@ __device__ inline void ens_member_halos(const EnsMember& M, const Real* __restri
       for (int m = 0; m < kMaxT; ++m) {
         const double w = m < M.T ? M.wt[k][m] : 0.0;
 #pragma unroll
-        for (int d = 0; d < S; ++d) acc[d] += w != 0.0 ? w * static_cast<double>(raw[m][d]) : 0.0;
+        for (int d = 0; d < S; ++d) acc[d] = add_level(acc[d], w, raw[m][d]);
       }
 #pragma unroll
       for (int d = 0; d < S; ++d) v[d] = static_cast<Real>(acc[d]);
@@ -169,14 +173,14 @@ __device__ inline void ens_chunk_finish(const EnsMember& M, const EnsChunk<Real,
     Real a = Real(0);
 #pragma unroll
     for (int o = 1; o <= S; ++o) {
-      a += ens_tap<Real>(M, S - o) * (k.w[S + e - o] - u0);
-      a += ens_tap<Real>(M, S + o) * (k.w[S + e + o] - u0);
+      a = fmadd(ens_tap<Real>(M, S - o), k.w[S + e - o] - u0, a);
+      a = fmadd(ens_tap<Real>(M, S + o), k.w[S + e + o] - u0, a);
     }
     acc[e] = a;
     if constexpr (AB2)
-      r[e] = u0 + dt * (b1 * a + b2 * k.fo[e]);
+      r[e] = ab2_update(u0, dt, b1, a, b2, k.fo[e]);
     else
-      r[e] = u0 + dt * (b1 * a);
+      r[e] = euler_update(u0, dt, a);
   }
   ens_store<Real, V>(un + k.g0, r);
   if constexpr (AB2) ens_store<Real, V>(f + k.g0, acc);
@@ -240,9 +244,9 @@ __device__ inline void ens_member_sweep_s(const EnsMember& M, const Real* u, Rea
 // Members whose descriptors a workgroup holds in LDS at a time.
 constexpr int kEnsLdsMembers = AT_ENS_BATCH;
 
-// All steps of `count` members whose descriptors are in LDS.
+// All steps of the `count` streamed members mem[idx[0..count-1]].
 template <typename Real, int UX>
-__device__ inline void ens_run(const EnsParams& p, int64_t n0, const EnsMember* mem, int count) {
+__device__ __forceinline__ void ens_stream(const EnsParams& p, int64_t n0, const EnsMember* mem, const int* idx, int count) {
   Real* f = static_cast<Real*>(p.f);
   Real* ring = static_cast<Real*>(p.ring);
   Real* hb = static_cast<Real*>(p.hbuf);
@@ -251,7 +255,7 @@ __device__ inline void ens_run(const EnsParams& p, int64_t n0, const EnsMember* 
     const Real* u = static_cast<const Real*>(p.u[n & 1]);
     Real* un = static_cast<Real*>(p.u[(n + 1) & 1]);
     for (int i = 0; i < count; ++i) {
-      const EnsMember& M = mem[i];
+      const EnsMember& M = mem[idx[i]];
       switch (M.s) {
         case 1: ens_member_halos<Real, 1>(M, u, ring, hb, n); break;
         case 2: ens_member_halos<Real, 2>(M, u, ring, hb, n); break;
@@ -261,7 +265,7 @@ __device__ inline void ens_run(const EnsParams& p, int64_t n0, const EnsMember* 
     // halo values complete before the sweep reads them
     __syncthreads();
     for (int i = 0; i < count; ++i) {
-      const EnsMember& M = mem[i];
+      const EnsMember& M = mem[idx[i]];
       switch (M.s) {
         case 1: ens_member_sweep_s<Real, 1, UX>(M, u, un, f, ring, hb, n); break;
         case 2: ens_member_sweep_s<Real, 2, UX>(M, u, un, f, ring, hb, n); break;
@@ -274,18 +278,88 @@ __device__ inline void ens_run(const EnsParams& p, int64_t n0, const EnsMember* 
   }
 }
 
-// One workgroup per bin of members. Members are independent problems, so a
-// bin larger than the LDS descriptor cache runs all steps for one batch of
-// members, then for the next.
-template <typename Real, int MAXT, int UX>
-__global__ __launch_bounds__(MAXT) void ens_steps_kernel(EnsParams p) {
-  __shared__ EnsMember s_mem[kEnsLdsMembers];
+// All steps of one member kept on the compute unit. A function of its own (not
+// inlined) per form, so that each is allocated registers by itself: inlined
+// side by side the forms' invariants were hoisted together and spilled inside
+// the step loops (512-member ensemble: 16.0 us a step inlined, 14.8 this way).
+// Pointers into LDS are passed as LDS offsets: the callee then addresses LDS
+// directly. SMALL only keeps the 64-register forms apart from the others.
+using LdsByte = __attribute__((address_space(3))) unsigned char;
+__device__ inline uint32_t lds_offset(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((LdsByte*)p));
+}
+__device__ inline unsigned char* lds_pointer(uint32_t off) {
+  return (unsigned char*)reinterpret_cast<LdsByte*>(off);
+}
+
+template <typename Real, int S, int PT, int KIND, bool GR, bool FG, bool SMALL>
+__device__ __attribute__((noinline)) void ens_line_fn(uint32_t member, LinePlan pl, const Real* u_in, Real* u_out, Real* f,
+                                                      Real* ring, int64_t n0, int64_t nsteps, uint32_t smem) {
+  // (arguments arrive in vector registers)
+  LineBufs<Real> B{uniform(u_in), uniform(u_out), uniform(f), nullptr, nullptr, uniform(ring), nullptr, nullptr, nullptr, nullptr};
+  const EnsMember& M = *reinterpret_cast<const EnsMember*>(lds_pointer(uniform(static_cast<int>(member))));
+  line_run<Real, S, PT, S + 1, KIND, AT_ADVDIFF, GR, FG, false>(M, pl, B, uniform(n0), uniform(nsteps),
+                                                  lds_pointer(uniform(static_cast<int>(smem))));
+}
+
+template <typename Real, bool SMALL>
+__device__ __forceinline__ void ens_line(const EnsParams& p, int64_t n0, const EnsMember& M, const LinePlan& pl,
+                                         unsigned char* smem) {
+  const Real* u_in = static_cast<const Real*>(p.u[n0 & 1]) + M.off;
+  Real* u_out = static_cast<Real*>(p.u[(n0 + p.nsteps) & 1]) + M.off;
+  Real* f = static_cast<Real*>(p.f) + M.off;   // read and written by AB2 members only
+  Real* ring = static_cast<Real*>(p.ring) + M.ring_off;
+  const uint32_t mo = lds_offset(&M), so = lds_offset(smem);
+  const int s = uniform(M.s), pt = uniform(pl.pt);
+  const bool ab2 = uniform(M.integrator) == AT_AB2, glob = uniform(pl.glob) != 0;
+  const int64_t ns = p.nsteps;
+  auto by_s = [&](auto PTc, auto GRc) __attribute__((always_inline)) {
+    constexpr int PT = decltype(PTc)::value;
+    constexpr bool GR = decltype(GRc)::value;
+    constexpr bool kFg = PT == (sizeof(Real) == 4 ? 64 : 32);   // AB2 keeps f in device memory (line_plan)
+    if (ab2) {
+      if (s == 1) ens_line_fn<Real, 1, PT, AT_AB2, GR, kFg, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
+      else if (s == 2) ens_line_fn<Real, 2, PT, AT_AB2, GR, kFg, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
+      else ens_line_fn<Real, 3, PT, AT_AB2, GR, kFg, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
+    } else {
+      if (s == 1) ens_line_fn<Real, 1, PT, AT_EULER, GR, false, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
+      else if (s == 2) ens_line_fn<Real, 2, PT, AT_EULER, GR, false, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
+      else ens_line_fn<Real, 3, PT, AT_EULER, GR, false, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
+    }
+  };
+  auto by_pt = [&](auto PTc) __attribute__((always_inline)) {
+    if (glob) by_s(PTc, std::true_type{});
+    else by_s(PTc, std::false_type{});
+  };
+  if (pt == 4) by_s(std::integral_constant<int, 4>{}, std::false_type{});
+  if constexpr (!SMALL || sizeof(Real) == 4)
+    if (pt == 8) by_s(std::integral_constant<int, 8>{}, std::false_type{});
+  if constexpr (!SMALL) {
+    if (pt == 16) by_pt(std::integral_constant<int, 16>{});
+    if (pt == 32) by_pt(std::integral_constant<int, 32>{});
+    if constexpr (sizeof(Real) == 4)
+      if (pt == 64) by_pt(std::integral_constant<int, 64>{});
+  }
+}
+
+// One workgroup per bin of members. Members are independent problems: a
+// member that fits its compute unit (line_plan) runs all its steps there, one
+// member after the other; the others of a batch of descriptors are streamed
+// through the caches together, step by step. 512 members, 7.5 million points,
+// FP32: 31 us a step with every member streamed (bound by the largest, whose
+// loads one CU issues), 7.6 kept (bound by the largest again: 65536 points,
+// fourth order, L = 8, whose history and ring alone stay in memory); 321
+// members of 1024 points, second order, FP64: 4.7 -> 0.77 us.
+template <typename Real, int MAXT, int UX, bool SMALL>
+__device__ __forceinline__ void ens_bin(const EnsParams& p, EnsMember* s_mem, unsigned char* smem) {
+  constexpr int kHeld = SMALL ? 1 : kEnsLdsMembers;
+  __shared__ int s_idx[kHeld];
   constexpr int kWords = sizeof(EnsMember) / sizeof(uint32_t);
   static_assert(sizeof(EnsMember) % sizeof(uint32_t) == 0, "descriptors are copied as words");
   const int m0 = p.bin_start[blockIdx.x], m1 = p.bin_start[blockIdx.x + 1];
   const int64_t n0 = p.counter[0];
-  for (int b0 = m0; b0 < m1; b0 += kEnsLdsMembers) {
-    const int count = min(kEnsLdsMembers, m1 - b0);
+  for (int b0 = m0; b0 < m1; b0 += kHeld) {
+    const int count = min(kHeld, m1 - b0);
     __syncthreads();   // the previous batch is done with the descriptors
     uint32_t* dst = reinterpret_cast<uint32_t*>(s_mem);
     for (int i = threadIdx.x; i < count * kWords; i += blockDim.x) {
@@ -293,9 +367,40 @@ __global__ __launch_bounds__(MAXT) void ens_steps_kernel(EnsParams p) {
       dst[i] = reinterpret_cast<const uint32_t*>(p.mem + p.order[b0 + j])[i - j * kWords];
     }
     __syncthreads();
-    ens_run<Real, UX>(p, n0, s_mem, count);
+    int streamed = 0;   // uniform: every thread sees the same plans
+    for (int j = 0; j < count; ++j) {
+      const LinePlan pl = line_plan(s_mem[j], sizeof(Real), blockDim.x, p.lds, SMALL ? ens_small_pt(sizeof(Real) == 8) : kEnsMaxPt, p.share);
+      if (uniform(pl.pt) != 0) {
+        ens_line<Real, SMALL>(p, n0, s_mem[j], pl, smem);
+      } else {
+        if (threadIdx.x == 0) s_idx[streamed] = j;
+        ++streamed;
+      }
+    }
+    if constexpr (!SMALL) {
+      if (uniform(streamed) > 0) {
+        __syncthreads();
+        ens_stream<Real, UX>(p, n0, s_mem, s_idx, uniform(streamed));
+      }
+    }
   }
   if (threadIdx.x == 0) advance_counter(p.counter, n0 + p.nsteps - 1);
+}
+
+template <typename Real, int MAXT, int UX>
+__global__ __launch_bounds__(MAXT) void ens_steps_kernel(EnsParams p) {
+  extern __shared__ __align__(16) unsigned char ens_smem[];
+  __shared__ EnsMember s_mem[kEnsLdsMembers];
+  ens_bin<Real, MAXT, UX, false>(p, s_mem, ens_smem);
+}
+
+// Every member kept on its compute unit with few points per thread: 64
+// registers, so that a CU holds 2048 threads of such workgroups.
+template <typename Real>
+__global__ __launch_bounds__(kEnsMaxThreads, 8) void ens_small_kernel(EnsParams p) {
+  extern __shared__ __align__(16) unsigned char ens_smem[];
+  __shared__ EnsMember s_mem[1];
+  ens_bin<Real, kEnsMaxThreads, 1, true>(p, s_mem, ens_smem);
 }
 
 // The edge strips of u^0 into the ring slot of level 0 of every member (the
@@ -477,20 +582,34 @@ hipError_t launch_ens_stats(const EnsStatsParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_ens_steps(const EnsParams& p, bool f64, int nbins, int threads, hipStream_t st) {
+int64_t ens_static_lds(bool small) {
+  // descriptors and the streamed members' indices, rounded up
+  return ((small ? 1 : kEnsLdsMembers) * static_cast<int64_t>(sizeof(EnsMember) + sizeof(int)) + 255) / 256 * 256;
+}
+
+hipError_t launch_ens_steps(const EnsParams& p, bool f64, bool small, int nbins, int threads, hipStream_t st) {
   if (threads < 64 || threads > kEnsMaxThreads || threads % 64) return hipErrorInvalidValue;
+  if (p.lds < 0 || p.lds + ens_static_lds(small) > static_cast<int64_t>(kLdsLimit)) return hipErrorInvalidValue;
+  const size_t lds = static_cast<size_t>(p.lds);
+  if (small) {
+    if (f64)
+      hipLaunchKernelGGL((ens_small_kernel<double>), dim3(nbins), dim3(threads), lds, st, p);
+    else
+      hipLaunchKernelGGL((ens_small_kernel<float>), dim3(nbins), dim3(threads), lds, st, p);
+    return hipGetLastError();
+  }
   // workgroups of up to 512 threads have twice the registers: twice the
-  // chunks in flight
+  // chunks in flight of a streamed member
   if (f64) {
     if (threads > 512)
-      hipLaunchKernelGGL((ens_steps_kernel<double, 1024, 1>), dim3(nbins), dim3(threads), 0, st, p);
+      hipLaunchKernelGGL((ens_steps_kernel<double, 1024, 1>), dim3(nbins), dim3(threads), lds, st, p);
     else
-      hipLaunchKernelGGL((ens_steps_kernel<double, 512, 2>), dim3(nbins), dim3(threads), 0, st, p);
+      hipLaunchKernelGGL((ens_steps_kernel<double, 512, 2>), dim3(nbins), dim3(threads), lds, st, p);
   } else {
     if (threads > 512)
-      hipLaunchKernelGGL((ens_steps_kernel<float, 1024, 1>), dim3(nbins), dim3(threads), 0, st, p);
+      hipLaunchKernelGGL((ens_steps_kernel<float, 1024, 1>), dim3(nbins), dim3(threads), lds, st, p);
     else
-      hipLaunchKernelGGL((ens_steps_kernel<float, 512, 2>), dim3(nbins), dim3(threads), 0, st, p);
+      hipLaunchKernelGGL((ens_steps_kernel<float, 512, 2>), dim3(nbins), dim3(threads), lds, st, p);
   }
   return hipGetLastError();
 }

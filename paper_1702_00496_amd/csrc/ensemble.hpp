@@ -2,25 +2,16 @@
 // host front end ensemble_api.cpp.
 #pragma once
 
-#include "atfd_internal.hpp"
+#include "line.hpp"
 
 namespace atfd {
 
 // One member of the ensemble: a periodic 1-D advection-diffusion problem.
-struct EnsMember {
+struct EnsMember : Line {
   int64_t off;                     // first point in the packed fields
   int64_t ring_off;                // first value of its ring in the packed ring
   int64_t hoff;                    // first value of its halo values in the packed halo buffer
-  int64_t n;                       // points
-  int b, npe, s, T, L, nslots;     // PE edge, PEs, half-width, levels, max delay, ring slots
-  int integrator, mode;            // AT_EULER | AT_AB2; AT_DELAY_RNG | AT_DELAY_ZERO | AT_SYNC
-  int vec;                         // 4-point vector sweep (b % 4 == 0 and off % 4 == 0)
-  uint64_t key;                    // generator key
-  uint64_t thr[kMaxL];             // delay bin thresholds
-  double wt[kMaxL][kMaxT];         // level weights c_m(k) for every delay k < L
-  double dt;
-  double kad[2 * kMaxS + 1];       // alpha c2/dx^2 - c c1/dx per tap o = -s..s
-  float kadf[2 * kMaxS + 1];
+  int64_t vec;                     // 4-point vector sweep (b % 4 == 0 and off % 4 == 0)
   double length, c, alpha;         // for the exact solution
 };
 
@@ -34,6 +25,8 @@ struct EnsParams {
   void* hbuf;                      // packed halo values of the current step [member][pe][side][s]
   int64_t* counter;                // [0] = step n, [1] = finished workgroups
   int64_t nsteps;                  // steps of this launch
+  int64_t lds;                     // dynamic LDS bytes of a workgroup
+  int share;                       // workgroups per compute unit the schedule asks for
 };
 
 struct EnsNormParams {
@@ -57,7 +50,13 @@ struct EnsStatsParams {
 };
 
 hipError_t launch_ens_stats(const EnsStatsParams& p, hipStream_t st);
-hipError_t launch_ens_steps(const EnsParams& p, bool f64, int nbins, int threads, hipStream_t st);
+// `small`: every member is kept on its compute unit with at most ens_small_pt
+// points per thread (the lighter kernel, two 1024-thread workgroups per CU).
+inline __host__ __device__ constexpr int ens_small_pt(bool f64) { return f64 ? 4 : 8; }
+constexpr int kEnsMaxPt = 64;
+hipError_t launch_ens_steps(const EnsParams& p, bool f64, bool small, int nbins, int threads, hipStream_t st);
+// Static LDS of a workgroup of the steps kernel.
+int64_t ens_static_lds(bool small);
 hipError_t launch_ens_publish_level0(const EnsParams& p, bool f64, int count, hipStream_t st);
 hipError_t launch_ens_norms(const EnsNormParams& p, bool f64, int count, hipStream_t st);
 

@@ -44,6 +44,8 @@ namespace {
 
 constexpr int kPhaseMax = 1 << 16;   // doubles of per-member phases staged for at_ens_norms
 // autotune candidates: workgroups per CU x threads per workgroup
+// points whose arithmetic takes as long as the fixed chain of a step
+constexpr double kEnsChainPoints = 4000.0;
 constexpr int kEnsTuneGroups[3] = {1, 2, 4};
 constexpr int kEnsTuneThreads[3] = {256, 512, 1024};
 
@@ -158,6 +160,57 @@ at_status plan(at_ens* e, int32_t count, const at_ens_member* m, int32_t precisi
   return AT_OK;
 }
 
+// Dynamic LDS of a workgroup of the steps kernel, and whether the lighter
+// kernel takes the launch: where several workgroups share a CU and every
+// member is kept on it with at most ens_small_pt points per thread. (One
+// workgroup per CU gains nothing from fewer registers, and longer chunks take
+// fewer instructions a step: 8192 points, fourth order, FP32: 1.88 us a step in the
+// lighter kernel, 1.27 in the other.)
+// groups_per_cu workgroups share a CU's LDS.
+void launch_shape(const at_ens* e, bool* small, int64_t* lds) {
+  const int w = e->f64 ? 8 : 4;
+  auto need = [&](bool sm, int64_t budget, int64_t* most) -> bool {
+    bool all = true;
+    *most = 0;
+    for (const EnsMember& m : e->mem) {
+      const LinePlan pl = line_plan(m, w, e->threads, budget, sm ? ens_small_pt(e->f64) : kEnsMaxPt, e->groups_per_cu);
+      if (!pl.pt) {
+        all = false;
+        continue;
+      }
+      const int64_t b = line_lds_base(m.s, pl.c * m.npe, m.integrator, w) +
+                        (pl.glob ? 0 : line_lds_ring(m.s, m.npe, m.nslots, m.integrator, w));
+      *most = std::max(*most, b);
+    }
+    return all;
+  };
+  auto budget = [&](bool sm) {
+    return static_cast<int64_t>(kLdsLimit) / e->groups_per_cu - ens_static_lds(sm);
+  };
+  *small = e->groups_per_cu > 1 && need(true, budget(true), lds);
+  if (!*small) need(false, budget(false), lds);
+}
+
+// The schedule before any tuning: one 1024-thread workgroup per CU, or, where
+// every member runs in the lighter kernel with fewer threads, the fewest
+// threads that do and workgroups enough that (up to four per CU) each member
+// has its own: short members are bound by the chain of a step, which
+// workgroups on one CU overlap (1281 members of 1024 points, FP64: 3.7 us a
+// step with (1, 1024), 1.48 with (4, 256); 321 members 1.4 and 0.87).
+void default_schedule(at_ens* e) {
+  for (int threads : kEnsTuneThreads) {
+    if (e->count <= e->cus) break;
+    e->threads = threads;
+    e->groups_per_cu = e->count > 2 * e->cus ? 4 : 2;
+    bool small = false;
+    int64_t lds = 0;
+    launch_shape(e, &small, &lds);
+    if (small) return;
+  }
+  e->groups_per_cu = 1;
+  e->threads = 1024;
+}
+
 // Longest-first balance: members sorted by work, each to the least loaded
 // workgroup; workgroups ordered by load so the heaviest start first.
 void schedule(at_ens* e) {
@@ -166,8 +219,12 @@ void schedule(at_ens* e) {
   std::vector<int> idx(count);
   for (int i = 0; i < count; ++i) idx[i] = i;
   auto work = [&](int i) {
+    // a step of a member kept on its CU is a fixed chain plus its points'
+    // arithmetic; a streamed member's points cost several times as much
     const EnsMember& d = e->mem[i];
-    return static_cast<double>(d.n) * (d.integrator == AT_AB2 ? 1.5 : 1.0);
+    const LinePlan pl = line_plan(d, e->f64 ? 8 : 4, e->threads, static_cast<int64_t>(kLdsLimit) / e->groups_per_cu -
+                                  ens_static_lds(false), kEnsMaxPt, e->groups_per_cu);
+    return kEnsChainPoints + static_cast<double>(d.n) * (d.integrator == AT_AB2 ? 1.5 : 1.0) * (pl.pt ? 1.0 : 4.0);
   };
   std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return work(a) > work(b); });
   std::vector<double> load(nb, 0.0);
@@ -264,6 +321,7 @@ at_status at_ens_create(int32_t count, const at_ens_member* members, int32_t pre
   if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess &&
       prop.multiProcessorCount > 0)
     e->cus = prop.multiProcessorCount;
+  default_schedule(e);
   schedule(e);
   EnsParams& p = e->ep;
   p.mem = reinterpret_cast<const EnsMember*>(e->ws + e->off_mem);
@@ -313,8 +371,11 @@ at_status at_ens_run(at_ens* e, int64_t nsteps) {
     if (!e->cap_stream) ENS_TRY(e, hipStreamCreateWithFlags(&e->cap_stream, hipStreamNonBlocking));
     EnsParams p = e->ep;
     p.nsteps = nsteps;
+    bool small = false;
+    launch_shape(e, &small, &p.lds);
+    p.share = e->groups_per_cu;
     ENS_TRY(e, hipStreamBeginCapture(e->cap_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t le = launch_ens_steps(p, e->f64, e->nbins, e->threads, e->cap_stream);
+    hipError_t le = launch_ens_steps(p, e->f64, small, e->nbins, e->threads, e->cap_stream);
     hipGraph_t gr = nullptr;
     hipError_t ce = hipStreamEndCapture(e->cap_stream, &gr);
     if (le != hipSuccess || ce != hipSuccess) {
@@ -342,12 +403,9 @@ at_status at_ens_set_tuning(at_ens* e, int32_t groups_per_cu, int32_t threads) {
   if (g == e->groups_per_cu && t == e->threads) return AT_OK;
   drop_graph(e);
   e->threads = t;
-  if (g != e->groups_per_cu) {
-    e->groups_per_cu = g;
-    schedule(e);
-    return upload_schedule(e);
-  }
-  return AT_OK;
+  e->groups_per_cu = g;
+  schedule(e);
+  return upload_schedule(e);
 }
 
 at_status at_ens_state_size(const at_ens* e, size_t* bytes) {
