@@ -197,7 +197,8 @@ at_status at_step(at_ctx* ctx, int64_t nsteps);
 
 /* Capture chunks of `chunk` steps into a HIP graph and replay it inside
  * at_step (0 disables). All per-step quantities are read from a device
- * counter, so one graph serves every chunk. */
+ * counter, so one graph serves every chunk. (1-D problems that one compute
+ * unit holds run all steps of a call in one launch and need no graph.) */
 at_status at_set_graph(at_ctx* ctx, int32_t chunk);
 
 /* Tuning of the sweep schedule of the 3-D kernel for 32 x 32 PE cross-

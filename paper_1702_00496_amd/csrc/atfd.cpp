@@ -16,6 +16,7 @@
 #include "adjoint.hpp"
 #include "delays.hpp"
 #include "host_common.hpp"
+#include "line.hpp"
 
 using namespace atfd;
 
@@ -77,6 +78,10 @@ struct at_ctx {
   hipStream_t cap_stream = nullptr;
   // the adjoint's recomputation stream (default priority)
   hipStream_t aux_stream = nullptr;
+  // 1-D problems that one compute unit holds: all steps of a call in one
+  // launch (line.hpp); line.plan.pt = 0 where the context is stepped launch by
+  // launch
+  LineSteps line;
 };
 
 namespace {
@@ -321,6 +326,51 @@ void fill_params(at_ctx* c) {
   p.depth = default_variant(p, g.f64);
 }
 
+// The one-workgroup form of a small 1-D context. Taken for the time-expanded
+// schemes and the synchronous arm where kLineMaxPt points per thread and the
+// LDS of one compute unit hold the problem (up to 8192 points): a step there
+// takes less than the launch of a per-step sweep at every such size.
+void fill_line(at_ctx* c) {
+  LineSteps& q = c->line;
+  std::memset(&q, 0, sizeof(q));
+  const StepParams& p = c->sp;
+  const Geometry& g = c->g;
+  if (g.ndim != 1 || g.scheme != AT_SCHEME_TIME) return;
+  Line& M = q.line;
+  M.n = g.n[0];
+  M.b = g.b[0];
+  M.npe = g.npe;
+  M.s = g.s;
+  M.mode = c->delay.mode;
+  M.T = M.mode == AT_SYNC ? 1 : g.T;
+  M.L = p.L;
+  M.nslots = p.nslots;
+  M.integrator = c->prob.integrator;
+  M.key = p.key;
+  for (int k = 0; k < kMaxL; ++k) M.thr[k] = p.thr[k];
+  for (int k = 0; k < M.L; ++k) level_weights(k, M.T, M.wt[k]);
+  M.dt = p.dt;
+  for (int o = 0; o <= 2 * kMaxS; ++o) {
+    M.kad[o] = p.kad[0][o];
+    M.kadf[o] = p.kadf[0][o];
+    q.lap[o] = p.d2a[0][o];
+    q.lapf[o] = p.d2af[0][o];
+    q.grd[o] = p.c1[0][o];
+    q.grdf[o] = p.c1f[0][o];
+  }
+  q.equation = c->prob.equation;
+  for (int i = 0; i < 2; ++i) {
+    q.ubuf[i] = p.ubuf[i];
+    q.fbuf[i] = p.fbuf[i];
+  }
+  q.ustar = p.ustar;
+  q.ring = p.ring;
+  q.sring = p.sring;
+  q.host = p.host_delays;
+  q.counter = p.counter;
+  q.plan = line_plan(M, g.f64 ? 8 : 4, kMaxSweepThreads, static_cast<int64_t>(kLdsLimit), kLineMaxPt, 1);
+}
+
 // Queue the kernels of one time step on `st`, with the context's parameters
 // or with `p` (the same problem, other solution buffers).
 at_status enqueue_step_p(at_ctx* c, StepParams p, hipStream_t st) {
@@ -399,6 +449,7 @@ at_status at_create(const at_problem* prob, const at_delay* delay, void* ws_dev,
     at_delay tmp = *delay;
     c->delay = tmp;
     fill_params(c);          // uses delay.weights for the thresholds
+    fill_line(c);
     c->delay.weights = nullptr;
     c->delay.host_delays = nullptr;
   }
@@ -447,6 +498,15 @@ at_status at_step(at_ctx* c, int64_t nsteps) {
   if (!c->state_set) return fail(c, AT_ESTATE, "at_step before at_set_state");
   if (c->delay.mode == AT_DELAY_HOST && c->n + nsteps > c->delay.host_nsteps)
     return fail(c, AT_EINVAL, "host delay table covers %lld steps", (long long)c->delay.host_nsteps);
+  if (c->line.plan.pt > 0) {
+    if (nsteps > 0) {
+      LineSteps q = c->line;
+      q.nsteps = nsteps;
+      HIP_TRY(c, launch_line_steps(q, c->g.f64, c->stream));
+    }
+    c->n += nsteps;
+    return AT_OK;
+  }
   int64_t done = 0;
   if (c->graph_chunk > 0 && nsteps >= c->graph_chunk) {
     if (!c->graph_exec) {
