@@ -301,18 +301,18 @@ const char* at_last_error(const at_ctx* ctx);
  *
  * at_adjoint runs the N forward steps from the state set at step 0, saving a
  * checkpoint every `every` steps, then sweeps backwards: each segment is
- * recomputed from its checkpoint, its levels kept, and the transposed steps
- * are applied from lambda^N = seed (dJ/du^N, bulk precision, device) down to
- * lambda^0 = dJ/du^0, which is written to grad_u0_dev. Contributions to older
- * levels through the AT halos go to an adjoint ring of the forward ring's
- * shape (the delayed levels' transpose); RK2 keeps a second one for the
- * predictor's levels. Burgers linearises around the recomputed forward
- * levels of the segment. *grad_alpha receives
+ * recomputed from its checkpoint, its levels kept (the last one is kept as it
+ * runs), and the transposed steps are applied from lambda^N = seed (dJ/du^N,
+ * bulk precision, device) down to lambda^0 = dJ/du^0, which is written to
+ * grad_u0_dev. Contributions to older levels through the AT halos go to an
+ * adjoint ring of the forward ring's shape (the delayed levels' transpose);
+ * RK2 keeps a second one for the predictor's levels. Burgers linearises around
+ * the recomputed forward levels of the segment. *grad_alpha receives
  * dJ/dalpha = sum_n <dJ/df^n, d f^n / d alpha>, accumulated in double in a
  * fixed order. The context is left at step N with the forward field.
  * Scratch (device, 256-B aligned) of at_adjoint_scratch_size bytes holds the
- * checkpoints, the levels of one segment (two when a segment's levels and
- * ring copies take at most 4 GB: segment s-1 is then recomputed on a second
+ * checkpoints, the levels of one segment and a ring that keeps all of them (two
+ * sets when one takes at most 4 GB: segment s-1 is then recomputed on a second
  * stream of the library, at default priority, while segment s is reversed),
  * three adjoint fields and the adjoint ring. Synchronises the stream.
  * AT_ESTATE unless the context is at step 0.

@@ -17,8 +17,10 @@
 // where A^l gathers, at the edge strips that neighbours read, K_{i,a,o} c_m(k)
 // mu_i of every later step with n - k - m = l: an adjoint ring of the forward
 // ring's shape, filled in gather form (one thread per strip value: the strip
-// kernel in 3-D, the stage kernel's own strip phase in 1-D / 2-D) and drained
-// when the sweep reaches level l. The alpha-gradient adds
+// kernel, or the PE-tiled stage kernel's own strip phase in 1-D / 2-D) and
+// drained when the sweep reaches level l. 3-D problems take the stage kernel of
+// adjoint3d.hpp, which keeps the sums over mu themselves and combines them when
+// level l is reached; the kernels here serve the shapes it does not take. The alpha-gradient adds
 // <mu, dF/dalpha> = <mu, AT Laplacian of c>.
 //
 // Euler/AB2 (Sec. 4.1 eqs. time_disc, time_ab2): one stage per step, mu =
@@ -264,27 +266,9 @@ __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const
   }
 }
 
-// Value of level l (ring slot `slot`) at global point (x, y, z), which lies in
-// PE `src` at PE coordinates ls: from the stored levels of the segment, or,
-// for a level before the segment, from the ring as it was at the segment's
-// start (the point is then an edge value of that ring, read through producer
-// face pf).
-template <typename Real>
-__device__ inline double level_value(const AdjParams& q, int64_t l, int slot, int x, int y, int z, int src,
-                                     int pf, const int* ls) {
-  const StepParams& p = q.sp;
-  // both candidates are loaded (from in-range addresses) and one is selected
-  const bool stored = l >= q.seg_start;
-  const Real* U = static_cast<const Real*>(q.levels) + (stored ? l - q.seg_start : 0) * q.npts;
-  const double a = static_cast<double>(U[gindex(p, x, y, z)]);
-  const Real* R0 = static_cast<const Real*>(q.ring0);
-  const double b = static_cast<double>(R0[ring_at_pt(p, slot, src, pf, ls, p.s)]);
-  return stored ? a : b;
-}
-
 // The forward halo values of step n, for the alpha-derivative: for every
 // consumer PE, face f and element e of the producer strip it reads, the AT
-// combination of the stored levels (the synchronous scheme: level n).
+// combination of the segment's ring (the synchronous scheme: level n).
 // hbuf[pe * pe_block + (per-PE offset of face f) + e].
 template <typename Real, int S>
 __device__ inline Real halo_value(const AdjParams& q, const StripPt& sp, const double (*wt)[kMaxT]) {
@@ -302,13 +286,14 @@ __device__ inline Real halo_value(const AdjParams& q, const StripPt& sp, const d
   if (p.mode == AT_SYNC)   // level n, always stored
     return static_cast<const Real*>(q.levels)[(q.n - q.seg_start) * q.npts + gindex(p, gx, gy, gz)];
   // all kMaxT levels are loaded unconditionally (a level m >= T repeats
-  // level T - 1 and is dropped below), so the loads overlap
-  const int rn = static_cast<int>(q.n % p.nslots);
+  // level T - 1 and is dropped below, like a level of weight zero), so the
+  // loads overlap
+  const Real* R = static_cast<const Real*>(q.fring);
+  const int rn = static_cast<int>(q.n % q.fslots);
   double lv[kMaxT];
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m)
-    lv[m] = level_value<Real>(q, q.n - k - min(m, T - 1), slot_back(rn, k + min(m, T - 1), p.nslots), gx, gy,
-                              gz, src, pf, ls);
+    lv[m] = static_cast<double>(R[ring_at_pt(p, slot_back(rn, k + min(m, T - 1), q.fslots), src, pf, ls, S)]);
   double v = 0.0;
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m)
@@ -430,21 +415,15 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
   }
 }
 
-// PE-tiled form of adj_lambda_kernel (same formula, same per-point order of
-// the sums): one workgroup per PE, every global value loaded once.
-//  - 1-D / 2-D: the PE's plane in LDS: the stage values c with the frame of
-//    forward halo values the stencil reads across the PE's faces, and the two
-//    mu fields y0, y1 with a zero frame (taps of consumer points outside the
-//    PE reach this point through the adjoint ring instead). The workgroup
-//    first does its PE's strip work (the halo values straight into the frame,
-//    the gather-form scatter into its own adjoint-ring entries, the level-n
-//    drains into LDS), so no strip kernel runs before it.
-//  - 3-D: each thread owns one (x, y) column of the PE and streams it in z
-//    with register queues of 2S+1 planes of c, y0 and y1 (the z halo values
-//    of c from hbuf, zeros for y0 and y1 beyond the PE), the x/y neighbours
-//    from a double-buffered LDS plane laid out like the 2-D one. The loads of
-//    the plane S+1 ahead are in flight while a plane is computed.
-// The alpha-gradient part of the workgroup goes to partial[PE].
+// PE-tiled form of adj_lambda_kernel for 1-D / 2-D (same formula, same
+// per-point order of the sums): one workgroup per PE, every global value
+// loaded once. The PE's plane in LDS: the stage values c with the frame of
+// forward halo values the stencil reads across the PE's faces, and the two mu
+// fields y0, y1 with a zero frame (taps of consumer points outside the PE
+// reach this point through the adjoint ring instead). The workgroup first does
+// its PE's strip work (the halo values straight into the frame, the
+// gather-form scatter into its own adjoint-ring entries, the level-n drains
+// into LDS), so no strip kernel runs before it. 3-D: adjoint3d.hpp.
 constexpr int kAdjPeThreads = 1024;
 
 template <typename Real, int DIM, int S>
@@ -452,81 +431,46 @@ __global__ __launch_bounds__(kAdjPeThreads) void adj_lambda_pe_kernel(AdjParams 
   const StepParams& p = q.sp;
   extern __shared__ __align__(16) unsigned char adj_smem[];
   const int pe = blockIdx.x;
-  const int qx = pe % p.px, qy = (pe / p.px) % p.py, qz = pe / (p.px * p.py);
-  const int bx = p.bx, by = DIM >= 2 ? p.by : 1, bz = DIM == 3 ? p.bz : 1;
-  const int x0 = qx * p.bx, y0 = qy * p.by, z0 = qz * p.bz;
+  const int qx = pe % p.px, qy = pe / p.px;
+  const int bx = p.bx, by = DIM >= 2 ? p.by : 1;
+  const int x0 = qx * p.bx, y0 = qy * p.by;
   const int W = bx + 2 * S, H = DIM >= 2 ? by + 2 * S : 1;   // LDS plane: rows of W, x = 0 at column S
   const int plane = W * H;
-  const int nbuf = DIM == 3 ? 2 : 1;
-  Real* Cl = reinterpret_cast<Real*>(adj_smem);            // [nbuf][plane]
-  Real* Y0l = Cl + nbuf * plane;
-  Real* Y1l = Y0l + nbuf * plane;
+  Real* Cl = reinterpret_cast<Real*>(adj_smem);            // [plane]
+  Real* Y0l = Cl + plane;
+  Real* Y1l = Y0l + plane;
   Real* __restrict__ out = static_cast<Real*>(q.out);
   const Real* __restrict__ X0 = static_cast<const Real*>(q.x0);
   const Real* __restrict__ X1 = static_cast<const Real*>(q.b1 != 0.0 ? q.x1 : q.x0);
   const Real* __restrict__ Yg0 = static_cast<const Real*>(q.y0);
   const Real* __restrict__ Yg1 = static_cast<const Real*>(q.m1 != 0.0 ? q.y1 : q.y0);
   const Real* __restrict__ C = static_cast<const Real*>(q.levels) + (q.n - q.seg_start) * q.npts;
-  // (not restrict: in 1-D / 2-D this kernel writes both through the strip
-  // work's own pointers first)
-  const Real* hpe = static_cast<const Real*>(q.hbuf) + static_cast<int64_t>(pe) * p.pe_block;
-  Real* aring = static_cast<Real*>(q.aring);
-  const int slot_n = static_cast<int>(q.n % q.anslots);
   const int tid = threadIdx.x, nt = blockDim.x;
   const double m0 = q.m0, m1 = q.m1;
-  // taps in LDS (read with uniform addresses where a point needs them)
-  __shared__ double s_c1[3][2 * S + 1], s_c2a[3][2 * S + 1], s_kad[3][2 * S + 1], s_c2[3][2 * S + 1];
-  if (tid < 3 * (2 * S + 1)) {
-    const int a = tid / (2 * S + 1), o = tid % (2 * S + 1);
-    s_c1[a][o] = p.c1[a][o];
-    s_c2[a][o] = p.c2[a][o];
-    s_c2a[a][o] = p.alpha * p.c2[a][o];
-    s_kad[a][o] = p.kad[a][o];
-  }
   const bool burg = q.burgers != 0;
-  // tap K_{i,a,o} at a point with stage value ci (as tap_k)
-  auto tapk = [&](int a, int o, double ci) -> double {
-    return burg ? s_c2a[a][o + S] - ci * s_c1[a][o + S] : s_kad[a][o + S];
-  };
-  // forward halo value across face f (a = f >> 1) for the PE coordinates l
-  // whose axis-a coordinate ta lies outside the PE
-  auto halo_c = [&](int f, int* l, int ta) -> Real {
-    const int a = f >> 1, b = a == 0 ? bx : a == 1 ? by : bz;
-    set3(l, a, (f & 1) ? ta - b : ta + b);
-    const int64_t pfo = f == 0 ? q.pfo[0] : f == 1 ? q.pfo[1] : f == 2 ? q.pfo[2] : f == 3 ? q.pfo[3]
-                      : f == 4 ? q.pfo[4] : q.pfo[5];
-    return hpe[pfo + strip_elem(p, f ^ 1, l, S)];
-  };
-  // zero frames of y0, y1; the x/y halo frame of c is written per plane
-  for (int i = tid; i < nbuf * plane; i += nt) {
+  // zero frames of y0, y1
+  for (int i = tid; i < plane; i += nt) {
     Y0l[i] = Real(0);
     Y1l[i] = Real(0);
   }
-  // 1-D / 2-D: the level weights c_m(k) of every k < L for the strip work
+  // the level weights c_m(k) of every k < L for the strip work
   __shared__ double s_wt[kMaxL][kMaxT];
-  if (DIM <= 2 && tid < kMaxL * kMaxT) s_wt[tid / kMaxT][tid % kMaxT] = q.wt[tid / kMaxT][tid % kMaxT];
+  if (tid < kMaxL * kMaxT) s_wt[tid / kMaxT][tid % kMaxT] = q.wt[tid / kMaxT][tid % kMaxT];
   __syncthreads();   // the zeros land before any own value is written over them
   // the per-point adjoint (x, y, z PE coordinates; global index g); cget(a, o)
   // / yget(a, o) give c and (y0, y1) at offset o along axis a
   double da = 0.0;
   // dr: the adjoint-ring entries of the strips the point lies in, one per
-  // axis (dr[a], where din[a]), loaded (and cleared) by the caller; nullptr:
-  // loaded and cleared here
+  // axis (dr[a], where din[a]), loaded and cleared by the caller
   auto point = [&](int x, int y, int z, int64_t g, double cj, double y0j, double y1j, double x0j, double x1j,
                    auto cget, auto yget, const Real* dr, const bool* din) {
     const double mu = m0 * y0j + m1 * y1j;
     double acc = q.b0 * x0j + q.b1 * x1j;
     double lap = 0.0, grad = 0.0, sumk = 0.0;
     const int l[3] = {x, y, z};
-    // the taps of axis a: from the kernel arguments where a is a compile-time
-    // constant (scalar registers), else from LDS (uniform addresses)
-    auto axis = [&](int a, auto args) {
-      constexpr bool kArgs = decltype(args)::value;
-      const int b = a == 0 ? bx : a == 1 ? by : bz;
-      auto c1t = [&](int o) -> double { return kArgs ? p.c1[a][o + S] : s_c1[a][o + S]; };
-      auto c2t = [&](int o) -> double { return kArgs ? p.c2[a][o + S] : s_c2[a][o + S]; };
+    auto axis = [&](int a) {
+      const int b = a == 0 ? bx : by;
       auto tk = [&](int o, double ci) -> double {
-        if (!kArgs) return tapk(a, o, ci);
         return burg ? p.alpha * p.c2[a][o + S] - ci * p.c1[a][o + S] : p.kad[a][o + S];
       };
 #pragma unroll
@@ -542,43 +486,22 @@ __global__ __launch_bounds__(kAdjPeThreads) void adj_lambda_pe_kernel(AdjParams 
         acc += (ia >= 0 && ia < b) ? tk(o, ci) * mi : 0.0;
         // forward stencil of the stage field at j
         const double v = cget(a, o) - cj;
-        lap += c2t(o) * v;
-        grad += c1t(o) * v;
+        lap += p.c2[a][o + S] * v;
+        grad += p.c1[a][o + S] * v;
       }
     };
-    if constexpr (DIM <= 2) {
 #pragma unroll
-      for (int a = 0; a < DIM; ++a) axis(a, std::true_type{});
-    } else {
-      // one axis at a time (not unrolled over axes: bounds the values in flight)
-#pragma unroll 1
-      for (int a = 0; a < DIM; ++a) axis(a, std::false_type{});
-    }
+    for (int a = 0; a < DIM; ++a) axis(a);
     // drain the adjoint-ring entries of the strips j lies in
-    if (dr) {
 #pragma unroll
-      for (int a = 0; a < DIM; ++a)
-        if (din[a]) acc += static_cast<double>(dr[a]);
-    } else {
-#pragma unroll
-      for (int a = 0; a < DIM; ++a) {
-        const int b = a == 0 ? bx : a == 1 ? by : bz;
-#pragma unroll
-        for (int side = 0; side < 2; ++side) {
-          if (side ? l[a] >= b - S : l[a] < S) {
-            Real* src = aring + ring_at_pt(p, slot_n, pe, 2 * a + side, l, S);
-            acc += static_cast<double>(*src);
-            *src = Real(0);
-          }
-        }
-      }
-    }
+    for (int a = 0; a < DIM; ++a)
+      if (din[a]) acc += static_cast<double>(dr[a]);
     acc += (-sumk - (burg ? grad : 0.0)) * mu;
     out[g] = static_cast<Real>(acc);
     da += mu * lap;
   };
 
-  if constexpr (DIM <= 2) {
+  {
     // A thread's first kPre points: their base terms are loaded with the plane
     constexpr int kPre = sizeof(Real) == 4 ? 4 : 3;
     Real pre_x0[kPre], pre_x1[kPre];
@@ -625,7 +548,7 @@ __global__ __launch_bounds__(kAdjPeThreads) void adj_lambda_pe_kernel(AdjParams 
     // PE's strip value into its older adjoint-ring levels, and the drained
     // level-n entry (this step's contribution included) into Dl, clearing
     // the ring entry. The two halves run in different waves side by side.
-    Real* Dl = Y1l + nbuf * plane;                        // [pe_block]
+    Real* Dl = Y1l + plane;                        // [pe_block]
     {
       const int blk = static_cast<int>(p.pe_block);
       for (int r = tid; r < 2 * blk; r += nt) {
@@ -701,110 +624,6 @@ __global__ __launch_bounds__(kAdjPeThreads) void adj_lambda_pe_kernel(AdjParams 
       const int64_t g = gindex(p, x0 + x, y0 + y, 0);
       plane_point(i, X0[g], X1[g]);
     }
-  } else {
-    // one column per thread (the host launches bx * by threads)
-    const int x = tid % bx, y = tid / bx;
-    const int at = (y + S) * W + x + S;
-    const int64_t col = gindex(p, x0 + x, y0 + y, z0);
-    const int64_t zs = static_cast<int64_t>(p.nx) * p.ny;
-    // values of plane zz (from -S to bz + S - 1): own planes from memory,
-    // beyond the PE's z faces c from the halo buffer and y0 = y1 = 0
-    auto fetch = [&](int zz, Real& cv, Real& a0, Real& a1) {
-      if (zz >= 0 && zz < bz) {
-        const int64_t g = col + zz * zs;
-        cv = C[g];
-        a0 = Yg0[g];
-        a1 = Yg1[g];
-      } else {
-        int l[3] = {x, y, 0};
-        cv = halo_c(zz < 0 ? 4 : 5, l, zz);
-        a0 = a1 = Real(0);
-      }
-    };
-    Real cq[2 * S + 1], yq0[2 * S + 1], yq1[2 * S + 1];
-#pragma unroll
-    for (int i = 0; i < 2 * S; ++i) fetch(i - S, cq[i], yq0[i], yq1[i]);
-    Real pc, p0, p1;   // plane S ahead, prefetched
-    fetch(S, pc, p0, p1);
-    // x and y frame of c: thread h < nf owns one frame element of every plane
-    // (its LDS position, and its halo-buffer address of plane 0 plus a
-    // per-plane stride: x strips [z][y][d], y strips [z][d][x]); the value of
-    // the next plane is loaded while a plane is computed
-    const int nf = 2 * S * (by + bx);
-    const bool has_f = tid < nf;
-    int f_at = 0;
-    int64_t f_addr = 0, f_stride = 0;
-    if (has_f) {
-      int l[3] = {0, 0, 0};
-      int f, ta;
-      if (tid < 2 * S * by) {
-        const int side = tid >= S * by ? 1 : 0, r = side ? tid - S * by : tid, yy = r / S, d = r - yy * S;
-        ta = side ? bx + d : d - S;
-        l[1] = yy;
-        f = side;
-        f_at = (yy + S) * W + ta + S;
-        f_stride = static_cast<int64_t>(by) * S;
-      } else {
-        const int hy = tid - 2 * S * by, side = hy >= S * bx ? 1 : 0, r = side ? hy - S * bx : hy;
-        const int d = r / bx, xx = r - d * bx;
-        ta = side ? by + d : d - S;
-        l[0] = xx;
-        f = 2 + side;
-        f_at = (ta + S) * W + xx + S;
-        f_stride = static_cast<int64_t>(S) * bx;
-      }
-      const int a = f >> 1, b = a == 0 ? bx : by;
-      set3(l, a, (f & 1) ? ta - b : ta + b);
-      const int64_t pfo = f == 0 ? q.pfo[0] : f == 1 ? q.pfo[1] : f == 2 ? q.pfo[2] : q.pfo[3];
-      f_addr = pfo + strip_elem(p, f ^ 1, l, S);
-    }
-    Real fv = has_f ? hpe[f_addr] : Real(0);
-    // base terms of the point, one plane ahead
-    Real xv0 = X0[col], xv1 = X1[col];
-    for (int z = 0; z < bz; ++z) {
-      const Real xc0 = xv0, xc1 = xv1;
-      if (z + 1 < bz) {
-        xv0 = X0[col + (z + 1) * zs];
-        xv1 = X1[col + (z + 1) * zs];
-      }
-      cq[2 * S] = pc;
-      yq0[2 * S] = p0;
-      yq1[2 * S] = p1;
-      if (z + S + 1 < bz + S) fetch(z + S + 1, pc, p0, p1);
-      Real* Cp = Cl + (z & 1) * plane;
-      Real* P0 = Y0l + (z & 1) * plane;
-      Real* P1 = Y1l + (z & 1) * plane;
-      Cp[at] = cq[S];
-      P0[at] = yq0[S];
-      P1[at] = yq1[S];
-      if (has_f) {
-        Cp[f_at] = fv;
-        if (z + 1 < bz) fv = hpe[f_addr + (z + 1) * f_stride];
-      }
-      __syncthreads();
-      auto cget = [&](int a, int o) -> double {
-        return static_cast<double>(a == 2 ? cq[S + o] : Cp[at + (a == 0 ? o : o * W)]);
-      };
-      auto yget = [&](int a, int o, double& v0, double& v1) {
-        if (a == 2) {
-          v0 = static_cast<double>(yq0[S + o]);
-          v1 = static_cast<double>(yq1[S + o]);
-        } else {
-          const int k = at + (a == 0 ? o : o * W);
-          v0 = static_cast<double>(P0[k]);
-          v1 = static_cast<double>(P1[k]);
-        }
-      };
-      point(x, y, z, col + z * zs, static_cast<double>(cq[S]), static_cast<double>(yq0[S]),
-            static_cast<double>(yq1[S]), static_cast<double>(xc0), static_cast<double>(xc1), cget, yget,
-            static_cast<const Real*>(nullptr), static_cast<const bool*>(nullptr));
-#pragma unroll
-      for (int i = 0; i < 2 * S; ++i) {
-        cq[i] = cq[i + 1];
-        yq0[i] = yq0[i + 1];
-        yq1[i] = yq1[i + 1];
-      }
-    }
   }
   // fixed-order block reduction of the alpha-gradient part
   for (int off = 32; off > 0; off >>= 1) da += __shfl_down(da, off, 64);
@@ -822,9 +641,8 @@ template <typename Real>
 size_t adj_pe_lds(const StepParams& p) {
   const int S = p.s;
   const size_t W = p.bx + 2 * S, H = p.ndim >= 2 ? p.by + 2 * S : 1;
-  // 1-D / 2-D: plus the drained adjoint-ring entries of the PE's strips
-  return (p.ndim == 3 ? 2 : 1) * 3 * W * H * sizeof(Real) +
-         (p.ndim <= 2 ? static_cast<size_t>(p.pe_block) * sizeof(Real) : 0);
+  // the three fields and the drained adjoint-ring entries of the PE's strips
+  return 3 * W * H * sizeof(Real) + static_cast<size_t>(p.pe_block) * sizeof(Real);
 }
 
 template <typename Real>
@@ -832,9 +650,7 @@ hipError_t launch_lambda_pe(const AdjParams& q, hipStream_t st) {
   const StepParams& p = q.sp;
   const size_t lds = adj_pe_lds<Real>(p);
   const int pts = p.bx * (p.ndim >= 2 ? p.by : 1);
-  const int threads = p.ndim == 3 ? (pts + 63) / 64 * 64 : std::min(kAdjPeThreads, (pts + 63) / 64 * 64);
-  // 3-D: every frame element of a plane has its own thread
-  if (p.ndim == 3 && 2 * p.s * (p.bx + p.by) > threads) return hipErrorInvalidValue;
+  const int threads = std::min(kAdjPeThreads, (pts + 63) / 64 * 64);
   const int key = p.ndim * 10 + p.s;
   switch (key) {
 #define ATFD_ADJ_PE_CASE(D, S)                                                                          \
@@ -843,7 +659,6 @@ hipError_t launch_lambda_pe(const AdjParams& q, hipStream_t st) {
     break;
     ATFD_ADJ_PE_CASE(1, 1) ATFD_ADJ_PE_CASE(1, 2) ATFD_ADJ_PE_CASE(1, 3)
     ATFD_ADJ_PE_CASE(2, 1) ATFD_ADJ_PE_CASE(2, 2) ATFD_ADJ_PE_CASE(2, 3)
-    ATFD_ADJ_PE_CASE(3, 1) ATFD_ADJ_PE_CASE(3, 2) ATFD_ADJ_PE_CASE(3, 3)
 #undef ATFD_ADJ_PE_CASE
     default: return hipErrorInvalidValue;
   }
@@ -897,37 +712,71 @@ int adj_blocks(int64_t npts) {
 
 bool adj_pe_applies(const StepParams& p, bool f64) {
   const size_t lds = f64 ? adj_pe_lds<double>(p) : adj_pe_lds<float>(p);
-  if (lds > 64 * 1024) return false;
-  // 3-D: one thread per column, whole waves; the FP64 register queues of
-  // s >= 2 would spill
-  if (p.ndim == 3 && f64 && p.s >= 2) return false;
-  return p.ndim <= 2 || (p.bx * p.by <= kAdjPeThreads && (p.bx * p.by) % 64 == 0 &&
-                         2 * p.s * (p.bx + p.by) <= p.bx * p.by);
+  return p.ndim <= 2 && lds <= 64 * 1024;
 }
 
 hipError_t launch_adj_step(const AdjParams& q, bool f64, hipStream_t st) {
+  if (adj3d_applies(q.sp, f64)) return f64 ? launch_adj3d_f64(q, st) : launch_adj3d_f32(q, st);
+  if (q.sp.pe_major) return hipErrorInvalidValue;   // the kernels below take [z][y][x] fields
+  // the 1-D / 2-D PE-tiled stage kernel does its PE's strip work itself
+  if (adj_pe_applies(q.sp, f64)) return f64 ? launch_lambda_pe<double>(q, st) : launch_lambda_pe<float>(q, st);
   const int64_t strips = static_cast<int64_t>(q.sp.npe) * q.sp.pe_block;
   const int64_t sb = (strips + kAdjThreads - 1) / kAdjThreads;
   const int sblocks = static_cast<int>(sb < kAdjBlocks ? (sb > 0 ? sb : 1) : kAdjBlocks);
-  const int lblocks = adj_blocks(q.npts);
-  const bool pe = adj_pe_applies(q.sp, f64);
-  // the 1-D / 2-D PE-tiled stage kernel does its PE's strip work itself
-  const bool strip_kernel = !(pe && q.sp.ndim <= 2);
-  if (f64) {
-    if (strip_kernel) {
-      hipError_t e = launch_strip<double>(q, sblocks, st);
-      if (e != hipSuccess) return e;
+  const hipError_t e = f64 ? launch_strip<double>(q, sblocks, st) : launch_strip<float>(q, sblocks, st);
+  if (e != hipSuccess) return e;
+  return f64 ? launch_lambda<double>(q, adj_blocks(q.npts), st) : launch_lambda<float>(q, adj_blocks(q.npts), st);
+}
+
+// Levels lo .. of one ring into another of a different slot count (grid y:
+// level); a plain copy of slots, or of chunks where the slots are innermost.
+template <typename Word>
+__global__ __launch_bounds__(256) void ring_levels_kernel(StepParams p, const Word* __restrict__ src, int ns,
+                                                          Word* __restrict__ dst, int nd, int64_t lo, uint32_t words,
+                                                          int wsize) {   // wsize: values per word
+  const int64_t l = lo + blockIdx.y;
+  const int ss = static_cast<int>(l % ns), sd = static_cast<int>(l % nd);
+  for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < words; w += gridDim.x * blockDim.x) {
+    if (!p.pe_major) {
+      dst[static_cast<size_t>(sd) * words + w] = src[static_cast<size_t>(ss) * words + w];
+      continue;
     }
-    hipError_t e = pe ? launch_lambda_pe<double>(q, st) : launch_lambda<double>(q, lblocks, st);
-    if (e != hipSuccess) return e;
-  } else {
-    if (strip_kernel) {
-      hipError_t e = launch_strip<float>(q, sblocks, st);
-      if (e != hipSuccess) return e;
-    }
-    hipError_t e = pe ? launch_lambda_pe<float>(q, st) : launch_lambda<float>(q, lblocks, st);
-    if (e != hipSuccess) return e;
+    // [face][plane][pe][slot][chunk]: the chunk the word lies in
+    int f = 0;
+#pragma unroll
+    for (int i = 1; i < 6; ++i) f += w >= static_cast<uint32_t>(p.face_off[i] / wsize) ? 1 : 0;
+    const uint32_t fo = static_cast<uint32_t>((f == 0 ? p.face_off[0] : f == 1 ? p.face_off[1] : f == 2 ? p.face_off[2]
+                        : f == 3 ? p.face_off[3] : f == 4 ? p.face_off[4] : p.face_off[5]) / wsize);
+    const uint32_t chunk = static_cast<uint32_t>((f < 4 ? p.face_chunk[0] : p.face_chunk[4]) / wsize);
+    const uint32_t blk = (w - fo) / chunk, r = (w - fo) - blk * chunk;
+    const size_t so = static_cast<size_t>(ns) * fo + (static_cast<size_t>(blk) * ns + ss) * chunk + r;
+    const size_t de = static_cast<size_t>(nd) * fo + (static_cast<size_t>(blk) * nd + sd) * chunk + r;
+    dst[de] = src[so];
   }
+}
+
+hipError_t launch_ring_levels(const StepParams& p, bool f64, const void* src, int ns, void* dst, int nd, int64_t lo,
+                              int64_t count, hipStream_t st) {
+  if (count <= 0) return hipSuccess;
+  if (ns < 1 || nd < 1 || count > 65535) return hipErrorInvalidValue;
+  const int w = f64 ? 8 : 4;
+  const int64_t elems = static_cast<int64_t>(p.npe) * p.pe_block, bytes = elems * w;
+  // 16-byte words where a slot (PE-major: every chunk) is a whole number of them
+  const bool vec = p.pe_major ? (p.face_chunk[0] * w) % 16 == 0 && (p.face_chunk[4] * w) % 16 == 0 : bytes % 16 == 0;
+  const int wb = vec ? 16 : w;
+  const int64_t words = bytes / wb;
+  if (words >= (int64_t(1) << 32)) return hipErrorInvalidValue;
+  const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((words + 255) / 256, 1024));
+  const dim3 grid(blocks, static_cast<unsigned>(count));
+  if (vec)
+    hipLaunchKernelGGL((ring_levels_kernel<uint4>), grid, dim3(256), 0, st, p, static_cast<const uint4*>(src), ns,
+                       static_cast<uint4*>(dst), nd, lo, static_cast<uint32_t>(words), 16 / w);
+  else if (f64)
+    hipLaunchKernelGGL((ring_levels_kernel<uint64_t>), grid, dim3(256), 0, st, p, static_cast<const uint64_t*>(src), ns,
+                       static_cast<uint64_t*>(dst), nd, lo, static_cast<uint32_t>(words), 1);
+  else
+    hipLaunchKernelGGL((ring_levels_kernel<uint32_t>), grid, dim3(256), 0, st, p, static_cast<const uint32_t*>(src), ns,
+                       static_cast<uint32_t*>(dst), nd, lo, static_cast<uint32_t>(words), 1);
   return hipGetLastError();
 }
 

@@ -24,14 +24,40 @@ struct AdjParams {
   void* out;                       // the stage's adjoint field
   const void* levels;              // stored levels of the stage field from seg_start, npts apart
   int64_t seg_start;
-  const void* ring0;               // that field's ring at step seg_start
+  const void* fring;               // that field's ring of the segment: fslots slots, level l in l mod fslots
+  int fslots;
+  int64_t nsteps;                  // steps of the whole run
   void* hbuf;                      // forward halo values of this stage [pe][face strips]
   int64_t pfo[6];                  // offset of face f's strip inside one PE's pe_block values
-  void* aring;                     // adjoint ring of the stage field, anslots slots
+  void* aring;                     // adjoint ring of the stage field, anslots slots (3-D kernel: the g ring)
   int anslots;
   double* partial;                 // [adj_partials] alpha-gradient partial sums
   double wt[kMaxL][kMaxT];         // level weights c_m(k) of every delay k < L (host-computed)
 };
+
+// The 3-D stage kernel (adjoint3d.hpp): PEs whose plane takes at most 1024
+// threads of two points each, and whose x / y frame one item each.
+inline int adj3d_threads(const StepParams& p) {
+  const int64_t vec = static_cast<int64_t>((p.bx + 1) / 2) * p.by, items = 2 * static_cast<int64_t>(p.s) * (p.bx + p.by);
+  int64_t t = vec > items ? vec : items;
+  if (t < 160) t = 160;   // the face set-up's threads
+  return static_cast<int>((t + 63) / 64 * 64);
+}
+inline size_t adj3d_lds(const StepParams& p, int w, bool m1) {
+  const size_t S = p.s, W = (p.bx + 4 + S + 2) & ~size_t(1), H = p.by + 2 * S, nh = 2 * S * (p.bx + p.by);
+  return 2 * nh * sizeof(double) + 2 * W * H * (m1 ? sizeof(double) : w) + 2 * W * H * w + S * p.bx * p.by * w;
+}
+inline bool adj3d_applies(const StepParams& p, bool f64) {
+  // (with the wider planes of a second mu term; 8 KB for the static part)
+  return p.ndim == 3 && adj3d_threads(p) <= 1024 && adj3d_lds(p, f64 ? 8 : 4, true) <= kLdsLimit - 8 * 1024;
+}
+hipError_t launch_adj3d_f32(const AdjParams& q, hipStream_t st);
+hipError_t launch_adj3d_f64(const AdjParams& q, hipStream_t st);
+
+// Copy levels lo .. lo + count - 1 between two rings of p's layout: level l
+// from slot l mod ns of src to slot l mod nd of dst.
+hipError_t launch_ring_levels(const StepParams& p, bool f64, const void* src, int ns, void* dst, int nd, int64_t lo,
+                              int64_t count, hipStream_t st);
 
 int adj_blocks(int64_t npts);
 // alpha-gradient partial sums the stage kernels write (>= kAdjBlocks; one per

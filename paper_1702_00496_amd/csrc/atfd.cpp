@@ -819,63 +819,80 @@ const char* at_last_error(const at_ctx* c) {
 
 namespace {
 
-// Scratch layout of at_adjoint: nck + 1 checkpoints; the levels of one
-// segment (contiguous fields: u^seg .. u^{seg+every}, and for RK2 the
-// predictors u*^seg .. u*^{seg+every-1}) with the forward rings at the
-// segment start, twice when the two sets fit kOverlapBytes (then segment s-1
-// is recomputed on a second stream while segment s is reversed); the adjoint
-// fields (lambda x3, sigma); the forward halo buffer; the adjoint ring (two
-// for RK2); alpha partial sums.
+// Scratch layout of at_adjoint. Every segment but the last has a checkpoint
+// (the field, the integrator history and the ring levels a later step can
+// read). A level set holds one segment: its levels (contiguous fields:
+// u^seg .. u^{seg+every}, and for RK2 the predictors u*^seg ..
+// u*^{seg+every-1}) and the segment's rings, which have a slot for every level
+// of the segment besides the L + T - 1 before it, so that the reversal reads
+// the delayed levels from them; two sets when they fit kOverlapBytes (then
+// segment s-1 is recomputed on a second stream while segment s is reversed).
+// Then the adjoint fields (lambda x3, sigma), the forward halo buffer, the
+// adjoint ring (two for RK2), alpha partial sums and the recomputation's step
+// counter.
 constexpr size_t kOverlapBytes = size_t(4) << 30;
 
 struct AdjSet {
-  size_t levels = 0, slevels = 0, ring0 = 0, sring0 = 0;
+  size_t levels = 0, slevels = 0, ring = 0, sring = 0;
 };
 
 struct AdjLayout {
-  size_t ck = 0, off_lam[3] = {0, 0, 0}, off_sigma = 0;
+  size_t ck = 0, ck_f[2] = {0, 0}, ck_ring = 0, ck_sring = 0;   // checkpoint size and offsets inside one
+  size_t off_lam[3] = {0, 0, 0}, off_sigma = 0;
   size_t off_hbuf = 0, off_aring = 0, off_bring = 0;
-  size_t off_partial = 0, off_out = 0, total = 0, aring_bytes = 0;
+  size_t off_partial = 0, off_out = 0, off_counter = 0, total = 0, aring_bytes = 0;
   AdjSet set[2];
   int nsets = 1;
-  int64_t nck = 0;
+  int64_t nck = 0;         // segments
   int anslots = 0;
+  int rslots = 0;          // slots of a segment's ring (0: the synchronous arm has none)
   bool rk2 = false;
+  bool gather = false;     // 3-D stage kernel: nothing of the adjoint ring is read before it is written
 };
 
 AdjLayout adj_layout(const at_ctx* c, int64_t nsteps, int every) {
   AdjLayout a;
-  size_t ck = 0;
-  at_checkpoint_size(c, &ck);
-  a.ck = align_up(ck);
+  const Layout& l = c->lay;
+  const size_t w = c->g.f64 ? 8 : 4;
   a.nck = (nsteps + every - 1) / every;
   a.rk2 = c->prob.integrator == AT_RK2;
-  size_t off = a.ck * static_cast<size_t>(a.nck + 1);
+  a.gather = adj3d_applies(c->sp, c->g.f64);
+  size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
     off = align_up(off + bytes);
     return o;
   };
-  const Layout& l = c->lay;
-  const size_t w = c->g.f64 ? 8 : 4;
-  const size_t seg_bytes = l.field_bytes * static_cast<size_t>(every + 1) +
-                           (a.rk2 ? l.field_bytes * static_cast<size_t>(every) + l.ring_bytes : 0) + l.ring_bytes;
+  take(l.field_bytes);
+  for (int i = 0; i < l.nfbuf; ++i) a.ck_f[i] = take(l.field_bytes);
+  a.ck_ring = take(l.ring_bytes);
+  if (a.rk2) a.ck_sring = take(l.ring_bytes);
+  a.ck = off;
+  off = a.ck * static_cast<size_t>(a.nck - 1);
+  // a segment of fewer steps than `every` (a short run) needs no more levels
+  const int64_t seg = std::min<int64_t>(every, nsteps);
+  a.rslots = l.nslots ? static_cast<int>(l.nslots + seg) : 0;
+  const size_t slot = static_cast<size_t>(c->g.npe) * l.pe_block * w;
+  const size_t ring = slot * static_cast<size_t>(a.rslots);
+  const size_t seg_bytes = l.field_bytes * static_cast<size_t>(seg + 1) + ring +
+                           (a.rk2 ? l.field_bytes * static_cast<size_t>(seg) + ring : 0);
   a.nsets = a.nck > 1 && seg_bytes <= kOverlapBytes ? 2 : 1;
   for (int k = 0; k < a.nsets; ++k) {
-    a.set[k].levels = take(l.field_bytes * static_cast<size_t>(every + 1));
-    if (a.rk2) a.set[k].slevels = take(l.field_bytes * static_cast<size_t>(every));
-    a.set[k].ring0 = take(l.ring_bytes);
-    if (a.rk2) a.set[k].sring0 = take(l.ring_bytes);
+    a.set[k].levels = take(l.field_bytes * static_cast<size_t>(seg + 1));
+    if (a.rk2) a.set[k].slevels = take(l.field_bytes * static_cast<size_t>(seg));
+    a.set[k].ring = take(ring);
+    if (a.rk2) a.set[k].sring = take(ring);
   }
   for (int i = 0; i < 3; ++i) a.off_lam[i] = take(l.field_bytes);
   if (a.rk2) a.off_sigma = take(l.field_bytes);
-  a.off_hbuf = take(static_cast<size_t>(c->g.npe) * l.pe_block * w);
+  a.off_hbuf = take(slot);
   a.anslots = c->delay.mode == AT_SYNC ? 1 : l.nslots;
-  a.aring_bytes = static_cast<size_t>(a.anslots) * c->g.npe * l.pe_block * w;
+  a.aring_bytes = static_cast<size_t>(a.anslots) * slot;
   a.off_aring = take(a.aring_bytes);
   if (a.rk2) a.off_bring = take(a.aring_bytes);
   a.off_partial = take(static_cast<size_t>(adj_partials(c->sp)) * sizeof(double));
   a.off_out = take(sizeof(double));
+  a.off_counter = take(kCounterWords * sizeof(int64_t));
   a.total = off;
   return a;
 }
@@ -888,6 +905,8 @@ at_status adj_check(at_ctx* c, int64_t nsteps, int32_t every) {
     return fail(c, AT_EINVAL, "the adjoint covers the time-expanded schemes");
   if (c->delay.mode == AT_DELAY_HOST && nsteps > c->delay.host_nsteps)
     return fail(c, AT_EINVAL, "host delay table covers %lld steps", (long long)c->delay.host_nsteps);
+  if (std::min<int64_t>(every, nsteps) > (int64_t(1) << 30))
+    return fail(c, AT_EINVAL, "a segment of more than 2^30 steps");
   if (c->g.npts >= (int64_t(1) << 31) || c->g.npe * c->lay.pe_block >= (int64_t(1) << 31))
     return fail(c, AT_EINVAL, "the adjoint covers fields and strip sets below 2^31 values");
   return AT_OK;
@@ -918,76 +937,114 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
   unsigned char* sc = static_cast<unsigned char*>(scratch_dev);
   const Layout& l = c->lay;
   const int64_t N = nsteps;
-  // forward run, checkpoint at the start of every segment and at the end
-  for (int64_t s = 0; s < a.nck; ++s) {
-    st = at_save(c, sc + a.ck * s);
-    if (st != AT_OK) return st;
-    const int64_t len = std::min<int64_t>(every, N - s * every);
-    st = at_step(c, len);
+  const bool f64 = c->g.f64;
+  // ring levels that a step from level n on can read: L + T - 1 of them
+  const int64_t reach = l.nslots ? l.nslots - 1 : 0;
+  auto first_live = [&](int64_t n) { return std::max<int64_t>(0, n - reach + 1); };
+  // the forward run up to the last segment, with a checkpoint at the start of
+  // every segment
+  for (int64_t s = 0; s + 1 < a.nck; ++s) {
+    unsigned char* ck = sc + a.ck * s;
+    HIP_TRY(c, hipMemcpyAsync(ck, c->sp.ubuf[c->n & 1], l.field_bytes, hipMemcpyDeviceToDevice, c->stream));
+    for (int i = 0; i < l.nfbuf; ++i)
+      HIP_TRY(c, hipMemcpyAsync(ck + a.ck_f[i], c->sp.fbuf[i], l.field_bytes, hipMemcpyDeviceToDevice, c->stream));
+    if (l.nslots) {
+      const int64_t lo = first_live(c->n);
+      HIP_TRY(c, launch_ring_levels(c->sp, f64, c->sp.ring, l.nslots, ck + a.ck_ring, l.nslots, lo, c->n - lo + 1,
+                                    c->stream));
+      // (the predictor of level n does not exist yet)
+      if (a.rk2)
+        HIP_TRY(c, launch_ring_levels(c->sp, f64, c->sp.sring, l.nslots, ck + a.ck_sring, l.nslots, lo, c->n - lo,
+                                      c->stream));
+    }
+    st = at_step(c, every);
     if (st != AT_OK) return st;
   }
-  st = at_save(c, sc + a.ck * a.nck);
-  if (st != AT_OK) return st;
-  // reverse sweep from lambda^N = seed
+  // reverse sweep from lambda^N = seed (adjoint fields in the context's layout)
   unsigned char* lam[3] = {sc + a.off_lam[0], sc + a.off_lam[1], sc + a.off_lam[2]};
   int i1 = 0, i2 = 1, i0 = 2;   // roles: lambda^{n+1}, lambda^{n+2}, lambda^n
-  HIP_TRY(c, hipMemcpyAsync(lam[i1], seed_dev, l.field_bytes, hipMemcpyDeviceToDevice, c->stream));
-  HIP_TRY(c, hipMemsetAsync(lam[i2], 0, l.field_bytes, c->stream));
-  HIP_TRY(c, hipMemsetAsync(sc + a.off_aring, 0, a.aring_bytes, c->stream));
-  if (a.rk2) HIP_TRY(c, hipMemsetAsync(sc + a.off_bring, 0, a.aring_bytes, c->stream));
+  HIP_TRY(c, launch_field_copy(c->sp, f64, seed_dev, lam[i1], true, c->stream));
+  if (!a.gather) {
+    HIP_TRY(c, hipMemsetAsync(sc + a.off_aring, 0, a.aring_bytes, c->stream));
+    if (a.rk2) HIP_TRY(c, hipMemsetAsync(sc + a.off_bring, 0, a.aring_bytes, c->stream));
+  }
   HIP_TRY(c, hipMemsetAsync(sc + a.off_partial, 0, static_cast<size_t>(adj_partials(c->sp)) * sizeof(double),
                             c->stream));
   const double dt = c->prob.dt;
-  // Recompute segment s into level set k on stream st: restore its
-  // checkpoint into the context, keep the forward rings at its start and
-  // step through it with every level kept.
+  // Step through segment s on stream st with every level kept in level set k,
+  // from its checkpoint (whose history the steps then rewrite in place) or,
+  // for the last segment, from the context itself, which is left at step N.
+  // Level seg+j-1 is read from the segment's levels and level seg+j (and the
+  // RK2 predictor) written straight into them; the segment's ring keeps every
+  // level.
   auto recompute = [&](int64_t s, int k, hipStream_t st) -> at_status {
     const AdjSet& z = a.set[k];
+    const bool last = s + 1 == a.nck;
+    unsigned char* ck = sc + a.ck * s;   // (not touched for the last segment)
     unsigned char* levels = sc + z.levels;
     unsigned char* slevels = a.rk2 ? sc + z.slevels : nullptr;
     const int64_t seg = s * every;
     const int64_t len = std::min<int64_t>(every, N - seg);
-    c->n = seg;
-    at_status r = ckpt_copy(c, nullptr, sc + a.ck * s, false, st);
-    if (r != AT_OK) return r;
-    // the adjoint kernels take the levels in the [z][y][x] layout
-    HIP_TRY(c, launch_field_copy(c->sp, c->g.f64, c->sp.ubuf[c->n & 1], levels, false, st));
-    if (l.ring_bytes) {
-      HIP_TRY(c, hipMemcpyAsync(sc + z.ring0, c->sp.ring, l.ring_bytes, hipMemcpyDeviceToDevice, st));
-      if (a.rk2) HIP_TRY(c, hipMemcpyAsync(sc + z.sring0, c->sp.sring, l.ring_bytes, hipMemcpyDeviceToDevice, st));
+    StepParams p = c->sp;
+    p.counter = reinterpret_cast<int64_t*>(sc + a.off_counter);
+    // A small 1-D context takes its own steps in one launch (which round
+    // differently from the sweep): it is stepped by itself below, and the
+    // segment works on a copy of the history, in the adjoint field that the
+    // reversal writes first.
+    const bool line = last && c->line.plan.pt > 0;
+    if (!last) {
+      for (int i = 0; i < l.nfbuf; ++i) p.fbuf[i] = ck + a.ck_f[i];
+    } else if (line && l.nfbuf) {
+      p.fbuf[0] = lam[i0];
+      HIP_TRY(c, hipMemcpyAsync(p.fbuf[0], c->sp.fbuf[0], l.field_bytes, hipMemcpyDeviceToDevice, st));
     }
-    for (int64_t j = 1; j <= len; ++j) {
-      if (c->sp.pe_major) {
-        // the 32 x 32 path keeps its fields PE-major: step, then copy the
-        // levels out in the [z][y][x] layout
-        r = enqueue_step(c, st);
-        if (r != AT_OK) return r;
-        c->n += 1;
-        HIP_TRY(c, launch_field_copy(c->sp, c->g.f64, c->sp.ubuf[c->n & 1], levels + l.field_bytes * j, false, st));
-        if (a.rk2)
-          HIP_TRY(c, launch_field_copy(c->sp, c->g.f64, c->sp.ustar, slevels + l.field_bytes * (j - 1), false, st));
-      } else {
-        // the step reads level seg+j-1 from the segment's levels and writes
-        // level seg+j (and the RK2 predictor) straight into them: no copies
-        // (the generic sweep takes two solution buffers as well as one)
-        StepParams p = c->sp;
-        p.ubuf[c->n & 1] = levels + l.field_bytes * (j - 1);
-        p.ubuf[(c->n + 1) & 1] = levels + l.field_bytes * j;
-        if (a.rk2) p.ustar = slevels + l.field_bytes * (j - 1);
-        r = enqueue_step_p(c, p, st);
-        if (r != AT_OK) return r;
-        c->n += 1;
+    const void* u0 = last ? c->sp.ubuf[seg & 1] : static_cast<const void*>(ck);
+    HIP_TRY(c, launch_set_counter(p.counter, seg, st));
+    HIP_TRY(c, hipMemcpyAsync(levels, u0, l.field_bytes, hipMemcpyDeviceToDevice, st));
+    if (l.nslots) {
+      const int64_t lo = first_live(seg);
+      const void* ring = last ? c->sp.ring : static_cast<const void*>(ck + a.ck_ring);
+      const void* sring = last ? c->sp.sring : static_cast<const void*>(ck + a.ck_sring);
+      p.ring = sc + z.ring;
+      p.nslots = a.rslots;
+      HIP_TRY(c, launch_ring_levels(c->sp, f64, ring, l.nslots, p.ring, a.rslots, lo, seg - lo + 1, st));
+      if (a.rk2) {
+        p.sring = sc + z.sring;
+        HIP_TRY(c, launch_ring_levels(c->sp, f64, sring, l.nslots, p.sring, a.rslots, lo, seg - lo, st));
       }
     }
+    for (int64_t j = 1; j <= len; ++j) {
+      const int64_t n = seg + j - 1;
+      p.ubuf[n & 1] = levels + l.field_bytes * (j - 1);
+      p.ubuf[(n + 1) & 1] = levels + l.field_bytes * j;
+      if (a.rk2) p.ustar = slevels + l.field_bytes * (j - 1);
+      const at_status r = enqueue_step_p(c, p, st);
+      if (r != AT_OK) return r;
+    }
+    if (!last) return AT_OK;
+    if (line) return at_step(c, len);
+    // the context at step N
+    HIP_TRY(c, hipMemcpyAsync(c->sp.ubuf[N & 1], levels + l.field_bytes * len, l.field_bytes,
+                              hipMemcpyDeviceToDevice, st));
+    if (a.rk2)
+      HIP_TRY(c, hipMemcpyAsync(c->sp.ustar, slevels + l.field_bytes * (len - 1), l.field_bytes,
+                                hipMemcpyDeviceToDevice, st));
+    if (l.nslots) {
+      const int64_t lo = first_live(N);
+      HIP_TRY(c, launch_ring_levels(c->sp, f64, p.ring, a.rslots, c->sp.ring, l.nslots, lo, N - lo + 1, st));
+      if (a.rk2)
+        HIP_TRY(c, launch_ring_levels(c->sp, f64, p.sring, a.rslots, c->sp.sring, l.nslots, lo, N - lo, st));
+    }
+    HIP_TRY(c, launch_set_counter(c->sp.counter, N, st));
+    c->n = N;
     return AT_OK;
   };
   // Two level sets: segment s-1 is recomputed on the auxiliary stream while
   // segment s is reversed on the context's stream. Events order the reuse of
   // a set (the recomputation of s-1 waits for the reversal of s+1, which
   // read the same set) and the start of each reversal (it waits for its
-  // recomputation). The reversal reads only the level set, the ring copies
-  // and the adjoint's own buffers, never the context's live fields, which
-  // the recomputation overwrites.
+  // recomputation). The reversal reads only the level set and the adjoint's
+  // own buffers, which the recomputation of another segment does not touch.
   const bool overlap = a.nsets == 2;
   hipEvent_t ev_start = nullptr, ev_rec[2] = {nullptr, nullptr}, ev_rev[2] = {nullptr, nullptr};
   struct EventGuard {
@@ -1002,17 +1059,17 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
     if (!c->aux_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->aux_stream, hipStreamNonBlocking));
     aux = c->aux_stream;
     for (hipEvent_t* e : guard.e) HIP_TRY(c, hipEventCreateWithFlags(e, hipEventDisableTiming));
-    // the recomputations start after the forward run and the initialisation
+    // the last segment continues the forward run; the recomputations start
+    // after it and the initialisation
+    st = recompute(a.nck - 1, (a.nck - 1) & 1, c->stream);
+    if (st != AT_OK) return st;
     HIP_TRY(c, hipEventRecord(ev_start, c->stream));
     HIP_TRY(c, hipStreamWaitEvent(aux, ev_start, 0));
-    st = recompute(a.nck - 1, (a.nck - 1) & 1, aux);
-    if (st != AT_OK) return st;
-    HIP_TRY(c, hipEventRecord(ev_rec[(a.nck - 1) & 1], aux));
   }
   for (int64_t s = a.nck - 1; s >= 0; --s) {
     const int k = overlap ? static_cast<int>(s & 1) : 0;
     if (overlap) {
-      HIP_TRY(c, hipStreamWaitEvent(c->stream, ev_rec[k], 0));
+      if (s + 1 < a.nck) HIP_TRY(c, hipStreamWaitEvent(c->stream, ev_rec[k], 0));
       if (s >= 1) {
         // set (s-1) & 1 was last read by the reversal of segment s+1
         if (s + 1 <= a.nck - 1) HIP_TRY(c, hipStreamWaitEvent(aux, ev_rev[(s + 1) & 1], 0));
@@ -1037,6 +1094,8 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
       q.burgers = c->prob.equation == AT_BURGERS;
       q.hbuf = sc + a.off_hbuf;
       q.anslots = a.anslots;
+      q.fslots = a.rslots > 0 ? a.rslots : 1;
+      q.nsteps = N;
       q.seg_start = seg;
       q.partial = reinterpret_cast<double*>(sc + a.off_partial);
       for (int k = 0; k < kMaxL; ++k) {
@@ -1054,7 +1113,7 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
         q2.b0 = 0.5;
         q2.out = sc + a.off_sigma;
         q2.levels = slevels;
-        q2.ring0 = sc + a.set[k].sring0;
+        q2.fring = sc + a.set[k].sring;
         q2.aring = sc + a.off_bring;
         HIP_TRY(c, launch_adj_step(q2, c->g.f64, c->stream));
         // stage 1: lambda^n from mu = dt sigma
@@ -1075,7 +1134,7 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
       }
       q.out = lam[i0];
       q.levels = levels;
-      q.ring0 = sc + a.set[k].ring0;
+      q.fring = sc + a.set[k].ring;
       q.aring = sc + a.off_aring;
       HIP_TRY(c, launch_adj_step(q, c->g.f64, c->stream));
       const int t = i2;
@@ -1085,13 +1144,10 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
     }
     if (overlap) HIP_TRY(c, hipEventRecord(ev_rev[k], c->stream));
   }
-  HIP_TRY(c, hipMemcpyAsync(grad_u0_dev, lam[i1], l.field_bytes, hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(c, launch_field_copy(c->sp, f64, lam[i1], grad_u0_dev, false, c->stream));
   double* out = reinterpret_cast<double*>(sc + a.off_out);
   HIP_TRY(c, launch_adj_sum(reinterpret_cast<double*>(sc + a.off_partial), adj_partials(c->sp), out, c->stream));
   HIP_TRY(c, hipMemcpyAsync(grad_alpha, out, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  // leave the context at the end of the forward run
-  st = at_load(c, sc + a.ck * a.nck);
-  if (st != AT_OK) return st;
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return AT_OK;
 }
