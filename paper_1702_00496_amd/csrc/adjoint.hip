@@ -17,10 +17,11 @@
 // where A^l gathers, at the edge strips that neighbours read, K_{i,a,o} c_m(k)
 // mu_i of every later step with n - k - m = l: an adjoint ring of the forward
 // ring's shape, filled in gather form (one thread per strip value: the strip
-// kernel, or the PE-tiled stage kernel's own strip phase in 1-D / 2-D) and
-// drained when the sweep reaches level l. 3-D problems take the stage kernel of
-// adjoint3d.hpp, which keeps the sums over mu themselves and combines them when
-// level l is reached; the kernels here serve the shapes it does not take. The alpha-gradient adds
+// kernel) and drained when the sweep reaches level l. Most problems take the
+// stage kernels of adjoint2d.hpp and adjoint3d.hpp instead, which keep the sums
+// over mu themselves and combine them when level l is reached; the kernels here
+// serve the shapes those do not take (3-D cross-sections of more than 2048
+// points, planes too large for LDS). The alpha-gradient adds
 // <mu, dF/dalpha> = <mu, AT Laplacian of c>.
 //
 // Euler/AB2 (Sec. 4.1 eqs. time_disc, time_ab2): one stage per step, mu =
@@ -194,8 +195,7 @@ __device__ inline double tap_k(const AdjParams& q, int a, int o, double ci) {
 // collects the transposed taps of the consumer PE across F, weighted by the
 // consumer's level weights, into the adjoint ring slots of levels n-k-m.
 template <typename Real, int S>
-__device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const double (*wt)[kMaxT],
-                                    Real* drain = nullptr) {
+__device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const double (*wt)[kMaxT]) {
   const StepParams& p = q.sp;
   Real* aring = static_cast<Real*>(q.aring);
   const int pe = sp.pe, F = sp.F, d = sp.d, a = F >> 1;
@@ -238,26 +238,6 @@ __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const
     const int slot = slot_back(static_cast<int>(q.n % q.anslots), k + m, q.anslots);
     dst[m] = aring + ring_at_pt(p, slot, pe, F, lsF, S);
     old[m] = static_cast<double>(*dst[m]);
-  }
-  // the level-n entry, read with the others (before the taps' sum is used)
-  Real* en = nullptr;
-  Real en_old = Real(0);
-  if (drain) {
-    en = aring + ring_at_pt(p, static_cast<int>(q.n % q.anslots), pe, F, lsF, S);
-    en_old = *en;
-  }
-  if (drain) {
-    // the caller drains level n here: its entry (this step's contribution
-    // added when k = 0, as below) goes to *drain and the ring entry is
-    // cleared; only older levels stay in the ring
-    *drain = k == 0 ? static_cast<Real>(old[0] + w[0] * g) : en_old;
-    *en = Real(0);
-#pragma unroll
-    for (int m = 0; m < kMaxT; ++m) {
-      if (m >= T) break;
-      if (k + m > 0 && w[m] != 0.0) *dst[m] = static_cast<Real>(old[m] + w[m] * g);
-    }
-    return;
   }
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m) {
@@ -415,256 +395,6 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
   }
 }
 
-// PE-tiled form of adj_lambda_kernel for 1-D / 2-D (same formula, same
-// per-point order of the sums): one workgroup per PE, every global value
-// loaded once. The PE's plane in LDS: the stage values c with the frame of
-// forward halo values the stencil reads across the PE's faces, and the two mu
-// fields y0, y1 with a zero frame (taps of consumer points outside the PE
-// reach this point through the adjoint ring instead). The workgroup first does
-// its PE's strip work (the halo values straight into the frame, the
-// gather-form scatter into its own adjoint-ring entries, the level-n drains
-// into LDS), so no strip kernel runs before it. 3-D: adjoint3d.hpp.
-constexpr int kAdjPeThreads = 1024;
-
-template <typename Real, int DIM, int S>
-__global__ __launch_bounds__(kAdjPeThreads) void adj_lambda_pe_kernel(AdjParams q) {
-  const StepParams& p = q.sp;
-  extern __shared__ __align__(16) unsigned char adj_smem[];
-  const int pe = blockIdx.x;
-  const int qx = pe % p.px, qy = pe / p.px;
-  const int bx = p.bx, by = DIM >= 2 ? p.by : 1;
-  const int x0 = qx * p.bx, y0 = qy * p.by;
-  const int W = bx + 2 * S, H = DIM >= 2 ? by + 2 * S : 1;   // LDS plane: rows of W, x = 0 at column S
-  const int plane = W * H;
-  Real* Cl = reinterpret_cast<Real*>(adj_smem);            // [plane]
-  Real* Y0l = Cl + plane;
-  Real* Y1l = Y0l + plane;
-  Real* __restrict__ out = static_cast<Real*>(q.out);
-  const Real* __restrict__ X0 = static_cast<const Real*>(q.x0);
-  const Real* __restrict__ X1 = static_cast<const Real*>(q.b1 != 0.0 ? q.x1 : q.x0);
-  const Real* __restrict__ Yg0 = static_cast<const Real*>(q.y0);
-  const Real* __restrict__ Yg1 = static_cast<const Real*>(q.m1 != 0.0 ? q.y1 : q.y0);
-  const Real* __restrict__ C = static_cast<const Real*>(q.levels) + (q.n - q.seg_start) * q.npts;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const double m0 = q.m0, m1 = q.m1;
-  const bool burg = q.burgers != 0;
-  // zero frames of y0, y1
-  for (int i = tid; i < plane; i += nt) {
-    Y0l[i] = Real(0);
-    Y1l[i] = Real(0);
-  }
-  // the level weights c_m(k) of every k < L for the strip work
-  __shared__ double s_wt[kMaxL][kMaxT];
-  if (tid < kMaxL * kMaxT) s_wt[tid / kMaxT][tid % kMaxT] = q.wt[tid / kMaxT][tid % kMaxT];
-  __syncthreads();   // the zeros land before any own value is written over them
-  // the per-point adjoint (x, y, z PE coordinates; global index g); cget(a, o)
-  // / yget(a, o) give c and (y0, y1) at offset o along axis a
-  double da = 0.0;
-  // dr: the adjoint-ring entries of the strips the point lies in, one per
-  // axis (dr[a], where din[a]), loaded and cleared by the caller
-  auto point = [&](int x, int y, int z, int64_t g, double cj, double y0j, double y1j, double x0j, double x1j,
-                   auto cget, auto yget, const Real* dr, const bool* din) {
-    const double mu = m0 * y0j + m1 * y1j;
-    double acc = q.b0 * x0j + q.b1 * x1j;
-    double lap = 0.0, grad = 0.0, sumk = 0.0;
-    const int l[3] = {x, y, z};
-    auto axis = [&](int a) {
-      const int b = a == 0 ? bx : by;
-      auto tk = [&](int o, double ci) -> double {
-        return burg ? p.alpha * p.c2[a][o + S] - ci * p.c1[a][o + S] : p.kad[a][o + S];
-      };
-#pragma unroll
-      for (int o = -S; o <= S; ++o) {
-        if (o == 0) continue;
-        sumk += tk(o, cj);
-        // transposed interior tap from i = j - o (zero mu outside the PE)
-        double yi0, yi1;
-        yget(a, -o, yi0, yi1);
-        const double mi = m0 * yi0 + m1 * yi1;
-        const double ci = burg ? cget(a, -o) : 0.0;
-        const int ia = l[a] - o;
-        acc += (ia >= 0 && ia < b) ? tk(o, ci) * mi : 0.0;
-        // forward stencil of the stage field at j
-        const double v = cget(a, o) - cj;
-        lap += p.c2[a][o + S] * v;
-        grad += p.c1[a][o + S] * v;
-      }
-    };
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) axis(a);
-    // drain the adjoint-ring entries of the strips j lies in
-#pragma unroll
-    for (int a = 0; a < DIM; ++a)
-      if (din[a]) acc += static_cast<double>(dr[a]);
-    acc += (-sumk - (burg ? grad : 0.0)) * mu;
-    out[g] = static_cast<Real>(acc);
-    da += mu * lap;
-  };
-
-  {
-    // A thread's first kPre points: their base terms are loaded with the plane
-    constexpr int kPre = sizeof(Real) == 4 ? 4 : 3;
-    Real pre_x0[kPre], pre_x1[kPre];
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-      const int i = tid + k * nt;
-      pre_x0[k] = pre_x1[k] = Real(0);
-      if (i < bx * by) {
-        const int y = i / bx, x = i - y * bx;
-        const int64_t g = gindex(p, x0 + x, y0 + y, 0);
-        pre_x0[k] = X0[g];
-        pre_x1[k] = X1[g];
-      }
-    }
-    // the plane's own values: a thread's first kPre points are loaded into
-    // registers here and stored to LDS after the strip work, so that those
-    // loads and the strip work's are in flight together
-    Real pc[kPre], p0[kPre], p1[kPre];
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-      const int i = tid + k * nt;
-      pc[k] = p0[k] = p1[k] = Real(0);
-      if (i < bx * by) {
-        const int y = i / bx, x = i - y * bx;
-        const int64_t g = gindex(p, x0 + x, y0 + y, 0);
-        pc[k] = C[g];
-        p0[k] = Yg0[g];
-        p1[k] = Yg1[g];
-      }
-    }
-    for (int i = tid + kPre * nt; i < bx * by; i += nt) {
-      const int y = i / bx, x = i - y * bx;
-      const int64_t g = gindex(p, x0 + x, y0 + y, 0);
-      const int at = (DIM >= 2 ? y + S : 0) * W + x + S;
-      Cl[at] = C[g];
-      Y0l[at] = Yg0[g];
-      Y1l[at] = Yg1[g];
-    }
-    // This PE's strip values (the strip kernel's work, which only this
-    // workgroup touches), behind the plane's loads. Items 0..blk-1: the
-    // forward halo value that this PE reads across its face f (consumer
-    // view), straight into the frame of the LDS plane. Items blk..2 blk-1:
-    // in gather form, the transposed taps of the neighbour that reads this
-    // PE's strip value into its older adjoint-ring levels, and the drained
-    // level-n entry (this step's contribution included) into Dl, clearing
-    // the ring entry. The two halves run in different waves side by side.
-    Real* Dl = Y1l + plane;                        // [pe_block]
-    {
-      const int blk = static_cast<int>(p.pe_block);
-      for (int r = tid; r < 2 * blk; r += nt) {
-        const bool scat = r >= blk;
-        const int rr = scat ? r - blk : r;
-        const StripPt sp = strip_point<S>(q, pe * blk + rr);
-        if (scat) {
-          scatter_elem<Real, S>(q, sp, s_wt, Dl + rr);
-        } else {
-          // frame position of the value: depth d of the producer strip is
-          // column d - S (low face) or b + d (high face) along its axis
-          const int a = sp.F >> 1, b = a == 0 ? bx : by;
-          const int ta = (sp.F & 1) ? b + sp.d : sp.d - S;
-          const int at = a == 0 ? (DIM >= 2 ? sp.l[1] + S : 0) * W + ta + S : (ta + S) * W + sp.l[0] + S;
-          Cl[at] = halo_value<Real, S>(q, sp, s_wt);
-        }
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-      const int i = tid + k * nt;
-      if (i < bx * by) {
-        const int y = i / bx, x = i - y * bx;
-        const int at = (DIM >= 2 ? y + S : 0) * W + x + S;
-        Cl[at] = pc[k];
-        Y0l[at] = p0[k];
-        Y1l[at] = p1[k];
-      }
-    }
-    __syncthreads();
-    // the drained level-n entries of a point's strips (x, y), from Dl
-    auto drains = [&](int x, int y, Real* dr, bool* din) {
-      const int l[3] = {x, y, 0};
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        din[a] = false;
-        dr[a] = Real(0);
-        if (a < DIM) {
-          const int b = a == 0 ? bx : by, la = a == 0 ? x : y;
-          const bool lo = la < S, hi = la >= b - S;
-          if (lo || hi) {
-            const int F = 2 * a + (hi ? 1 : 0);
-            const int64_t pfo = F == 0 ? q.pfo[0] : F == 1 ? q.pfo[1] : F == 2 ? q.pfo[2] : q.pfo[3];
-            din[a] = true;
-            dr[a] = Dl[pfo + strip_elem(p, F, l, S)];
-          }
-        }
-      }
-    };
-    auto plane_point = [&](int i, Real vx0, Real vx1) {
-      const int y = i / bx, x = i - y * bx;
-      const int at = (DIM >= 2 ? y + S : 0) * W + x + S;
-      auto cget = [&](int a, int o) -> double { return static_cast<double>(Cl[at + (a == 0 ? o : o * W)]); };
-      auto yget = [&](int a, int o, double& v0, double& v1) {
-        const int k = at + (a == 0 ? o : o * W);
-        v0 = static_cast<double>(Y0l[k]);
-        v1 = static_cast<double>(Y1l[k]);
-      };
-      const int64_t g = gindex(p, x0 + x, y0 + y, 0);
-      Real dr[2];
-      bool din[2];
-      drains(x, y, dr, din);
-      point(x, y, 0, g, static_cast<double>(Cl[at]), static_cast<double>(Y0l[at]), static_cast<double>(Y1l[at]),
-            static_cast<double>(vx0), static_cast<double>(vx1), cget, yget, dr, din);
-    };
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-      const int i = tid + k * nt;
-      if (i < bx * by) plane_point(i, pre_x0[k], pre_x1[k]);
-    }
-    for (int i = tid + kPre * nt; i < bx * by; i += nt) {
-      const int y = i / bx, x = i - y * bx;
-      const int64_t g = gindex(p, x0 + x, y0 + y, 0);
-      plane_point(i, X0[g], X1[g]);
-    }
-  }
-  // fixed-order block reduction of the alpha-gradient part
-  for (int off = 32; off > 0; off >>= 1) da += __shfl_down(da, off, 64);
-  __shared__ double part[kAdjPeThreads / 64];
-  if ((tid & 63) == 0) part[tid / 64] = da;
-  __syncthreads();
-  if (tid == 0) {
-    double s = 0.0;
-    for (int w = 0; w < nt / 64; ++w) s += part[w];
-    q.partial[pe] += s;
-  }
-}
-
-template <typename Real>
-size_t adj_pe_lds(const StepParams& p) {
-  const int S = p.s;
-  const size_t W = p.bx + 2 * S, H = p.ndim >= 2 ? p.by + 2 * S : 1;
-  // the three fields and the drained adjoint-ring entries of the PE's strips
-  return 3 * W * H * sizeof(Real) + static_cast<size_t>(p.pe_block) * sizeof(Real);
-}
-
-template <typename Real>
-hipError_t launch_lambda_pe(const AdjParams& q, hipStream_t st) {
-  const StepParams& p = q.sp;
-  const size_t lds = adj_pe_lds<Real>(p);
-  const int pts = p.bx * (p.ndim >= 2 ? p.by : 1);
-  const int threads = std::min(kAdjPeThreads, (pts + 63) / 64 * 64);
-  const int key = p.ndim * 10 + p.s;
-  switch (key) {
-#define ATFD_ADJ_PE_CASE(D, S)                                                                          \
-  case D * 10 + S:                                                                                      \
-    hipLaunchKernelGGL((adj_lambda_pe_kernel<Real, D, S>), dim3(p.npe), dim3(threads), lds, st, q);      \
-    break;
-    ATFD_ADJ_PE_CASE(1, 1) ATFD_ADJ_PE_CASE(1, 2) ATFD_ADJ_PE_CASE(1, 3)
-    ATFD_ADJ_PE_CASE(2, 1) ATFD_ADJ_PE_CASE(2, 2) ATFD_ADJ_PE_CASE(2, 3)
-#undef ATFD_ADJ_PE_CASE
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 template <typename Real>
 hipError_t launch_strip(const AdjParams& q, int blocks, hipStream_t st) {
   switch (q.sp.s) {
@@ -710,16 +440,13 @@ int adj_blocks(int64_t npts) {
   return static_cast<int>(b < kAdjBlocks ? b : kAdjBlocks);
 }
 
-bool adj_pe_applies(const StepParams& p, bool f64) {
-  const size_t lds = f64 ? adj_pe_lds<double>(p) : adj_pe_lds<float>(p);
-  return p.ndim <= 2 && lds <= 64 * 1024;
-}
-
 hipError_t launch_adj_step(const AdjParams& q, bool f64, hipStream_t st) {
   if (adj3d_applies(q.sp, f64)) return f64 ? launch_adj3d_f64(q, st) : launch_adj3d_f32(q, st);
+  if (adj2d_applies(q.sp, f64)) {
+    if (q.sp.ndim == 1) return f64 ? launch_adj1d_f64(q, st) : launch_adj1d_f32(q, st);
+    return f64 ? launch_adj2d_f64(q, st) : launch_adj2d_f32(q, st);
+  }
   if (q.sp.pe_major) return hipErrorInvalidValue;   // the kernels below take [z][y][x] fields
-  // the 1-D / 2-D PE-tiled stage kernel does its PE's strip work itself
-  if (adj_pe_applies(q.sp, f64)) return f64 ? launch_lambda_pe<double>(q, st) : launch_lambda_pe<float>(q, st);
   const int64_t strips = static_cast<int64_t>(q.sp.npe) * q.sp.pe_block;
   const int64_t sb = (strips + kAdjThreads - 1) / kAdjThreads;
   const int sblocks = static_cast<int>(sb < kAdjBlocks ? (sb > 0 ? sb : 1) : kAdjBlocks);

@@ -51,6 +51,28 @@ inline bool adj3d_applies(const StepParams& p, bool f64) {
   // (with the wider planes of a second mu term; 8 KB for the static part)
   return p.ndim == 3 && adj3d_threads(p) <= 1024 && adj3d_lds(p, f64 ? 8 : 4, true) <= kLdsLimit - 8 * 1024;
 }
+// The 1-D / 2-D stage kernel (adjoint2d.hpp): the PE's plane in LDS, two points
+// and at most two pairs of them ahead per thread, at least the face set-up's
+// 160 threads.
+inline int adj2d_threads(const StepParams& p) {
+  const int64_t vec = static_cast<int64_t>((p.bx + 1) / 2) * (p.ndim == 2 ? p.by : 1);
+  int64_t t = (vec + 63) / 64 * 64;
+  if (t < 192) t = 192;
+  return static_cast<int>(t < 1024 ? t : 1024);
+}
+inline size_t adj2d_lds(const StepParams& p, int w, bool m1) {
+  const size_t S = p.s, by = p.ndim == 2 ? p.by : 1, W = (p.bx + 4 + S + 2) & ~size_t(1), H = by + (p.ndim == 2 ? 2 * S : 0),
+               nh = 2 * S * by + (p.ndim == 2 ? 2 * S * p.bx : 0);
+  return nh * sizeof(double) + W * H * ((m1 ? sizeof(double) : w) + w);
+}
+inline bool adj2d_applies(const StepParams& p, bool f64) {
+  return p.ndim <= 2 && adj2d_lds(p, f64 ? 8 : 4, true) <= kLdsLimit - 8 * 1024;
+}
+inline bool adj_gather(const StepParams& p, bool f64) { return adj2d_applies(p, f64) || adj3d_applies(p, f64); }
+hipError_t launch_adj1d_f32(const AdjParams& q, hipStream_t st);
+hipError_t launch_adj1d_f64(const AdjParams& q, hipStream_t st);
+hipError_t launch_adj2d_f32(const AdjParams& q, hipStream_t st);
+hipError_t launch_adj2d_f64(const AdjParams& q, hipStream_t st);
 hipError_t launch_adj3d_f32(const AdjParams& q, hipStream_t st);
 hipError_t launch_adj3d_f64(const AdjParams& q, hipStream_t st);
 

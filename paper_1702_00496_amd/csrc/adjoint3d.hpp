@@ -1,18 +1,5 @@
-// Stage of the reversed step for 3-D problems (adjoint.hip states the method
-// and the formula): one workgroup per PE, two x points per thread, sweeping
-// the PE's z-planes. Everything a stage does for a PE is in this one kernel,
-// and every value is gathered:
-//  - the forward halo values (for the Laplacian and the gradient of the stage
-//    field) are the forward step's own combinations, read from the segment's
-//    ring, whose slots keep every level of the segment;
-//  - the transposed taps that leave a PE across a face with a delay go, once,
-//    to the g ring: g_n[entry] = sum K mu over the consumer's points, in the
-//    ring slot of step n at the neighbour's strip entry;
-//  - the adjoint of level n of a strip entry is then the sum over the later
-//    steps n' = n + j whose delay k' reaches level n (0 <= j - k' < T) of
-//    c_{j-k'}(k') g_{n'}, and, where the neighbour's delay at n is 0, of the
-//    neighbour's taps themselves. No ring entry is read and written back, or
-//    cleared; the sums are in double.
+// Stage of the reversed step for 3-D problems: one workgroup per PE, two x points per thread, sweeping
+// the PE's z-planes (adjoint_gather.hpp: how the strips are done).
 //
 // What bounds it: memory (the stage fields read once, about T + 1 ring values
 // per strip entry), then FP64 issue: per tap pair one fused multiply-add each
@@ -27,62 +14,12 @@
 
 #pragma once
 
-#include <type_traits>
-
-#include "adjoint.hpp"
+#include "adjoint_gather.hpp"
 
 namespace atfd {
 namespace adj3d {
 
-constexpr int kDrain = 6;        // g values of an entry read ahead (more: a loop)
-constexpr int kMaxDrain = kMaxL + kMaxT;
-
-template <typename Real>
-struct Two {
-  Real v[2];
-};
-
-// Two consecutive values; EVEN: PE x edges are even, so both exist; else the
-// second repeats the first past the PE's row.
-template <bool EVEN, typename Real>
-__device__ inline Two<Real> ld2(const Real* p, bool has2) {
-  Two<Real> r;
-  if constexpr (EVEN) {
-    __builtin_memcpy(&r, p, sizeof(r));
-  } else {
-    r.v[0] = p[0];
-    r.v[1] = p[has2 ? 1 : 0];
-  }
-  return r;
-}
-template <bool EVEN, typename Real>
-__device__ inline void st2(Real* p, const Two<Real>& q, bool has2) {
-  if constexpr (EVEN) {
-    __builtin_memcpy(p, &q, sizeof(q));
-  } else {
-    p[0] = q.v[0];
-    if (has2) p[1] = q.v[1];
-  }
-}
-
-__device__ inline int neighbour3(const StepParams& p, int pid, int f) {
-  const int qx = pid % p.px, qy = (pid / p.px) % p.py, qz = pid / (p.px * p.py);
-  const int up = f & 1;
-  if (f < 2) return (up ? (qx + 1 == p.px ? 0 : qx + 1) : (qx == 0 ? p.px - 1 : qx - 1)) + p.px * (qy + p.py * qz);
-  if (f < 4) return qx + p.px * ((up ? (qy + 1 == p.py ? 0 : qy + 1) : (qy == 0 ? p.py - 1 : qy - 1)) + p.py * qz);
-  return qx + p.px * (qy + p.py * (up ? (qz + 1 == p.pz ? 0 : qz + 1) : (qz == 0 ? p.pz - 1 : qz - 1)));
-}
-
-__device__ inline int delay3(const StepParams& p, int pid, int f, int64_t n) {
-  int k = 0;
-  if (p.mode == AT_DELAY_RNG)
-    k = raw_delay(p.key, n, static_cast<uint32_t>(pid * 6 + f), p.thr, p.L);
-  else if (p.mode == AT_DELAY_HOST)
-    k = p.host_delays[(n * p.npe + pid) * 6 + f];
-  else
-    return 0;
-  return clamp_startup(k, n, p.T);
-}
+using namespace adjg;
 
 // MAXT: threads; TT: levels read of a combination (S + 1, the schemes' own
 // count, or kMaxT for the others; weights past T are zero); BURG: Burgers (taps depend on the stage field); M1: mu has a
@@ -103,95 +40,16 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
   Y* sY = reinterpret_cast<Y*>(sA + 2 * nh);                 // [2][plane]
   Real* sC = reinterpret_cast<Real*>(sY + 2 * plane);        // [2][plane]
   Real* sZ = sC + 2 * plane;                                 // [S][by][bx] planes bz .. bz + S - 1 of c
-  // forward combination of face f (weights, offsets of the slots in the
-  // neighbour's strip), and the entries of the g ring that reach level n
-  // (weights, offsets of the slots in this PE's strip; zero past the count)
-  __shared__ double s_w[6][TT];
-  __shared__ int64_t s_hoff[6][TT];
-  __shared__ int s_nbr[6], s_k[6], s_own[6], s_cnt[6];
-  __shared__ double s_dw[6][kMaxDrain], s_cw[6][16];
-  __shared__ int64_t s_goff[6][kMaxDrain];
-  // taps by |o| (0 beyond S): [o > 0][|o|], first kind: alpha c2 (Burgers) or
-  // kad; second kind: c1 (Burgers)
-  __shared__ double s_t1[3][2][2 * S + 1], s_t2[3][2][2 * S + 1];
+  __shared__ Faces<S, TT, 6> fc;
   const int tid = threadIdx.x, nt = blockDim.x;
   const int pe = pe_of_workgroup(blockIdx.x, gridDim.x);
   const int64_t n = q.n;
   const bool sync = p.mode == AT_SYNC;
-  const int T = sync ? 1 : p.T;
   const double m0 = q.m0, m1 = q.m1;
 
-  // strips: element r of plane z of face f of PE e in slot s
-  auto chunk_of = [&](int f) __attribute__((always_inline)) { return f < 2 ? p.face_chunk[0] : f < 4 ? p.face_chunk[2] : p.face_chunk[4]; };
-  auto foff_of = [&](int f) __attribute__((always_inline)) {
-    return f == 0 ? p.face_off[0] : f == 1 ? p.face_off[1] : f == 2 ? p.face_off[2]
-         : f == 3 ? p.face_off[3] : f == 4 ? p.face_off[4] : p.face_off[5];
-  };
-  auto strip0 = [&](int f, int e, int slots, int64_t r) __attribute__((always_inline)) -> int64_t {   // slot 0, plane 0
-    return p.pe_major ? slots * foff_of(f) + static_cast<int64_t>(e) * slots * chunk_of(f) + r
-                      : foff_of(f) + e * chunk_of(f) + r;
-  };
-  auto slot_step = [&](int f) __attribute__((always_inline)) -> int64_t {
-    return p.pe_major ? chunk_of(f) : static_cast<int64_t>(p.npe) * p.pe_block;
-  };
-  auto strip_zs = [&](int f, int slots) __attribute__((always_inline)) -> int64_t {
-    return static_cast<int64_t>(p.npe) * chunk_of(f) * (p.pe_major ? slots : 1);
-  };
-
-  // ---- faces: neighbours, this PE's delays, the neighbours' delays at this
-  // and the later steps that can reach level n
-  if (tid < 6) {
-    const int f = tid;
-    s_nbr[f] = neighbour3(p, pe, f);
-    const int k = delay3(p, pe, f, n);
-    s_k[f] = k;
-    const int r0 = static_cast<int>(n % q.fslots);
-    for (int m = 0; m < TT; ++m) {
-      // (a level of weight zero re-reads level n - k)
-      const double w = m < T ? q.wt[k][m] : 0.0;
-      s_w[f][m] = w;
-      s_hoff[f][m] = sync ? 0 : slot_back(r0, k + (w != 0.0 ? m : 0), q.fslots) * slot_step(f ^ 1);
-    }
-  }
-  if (tid < 96) {
-    const int f = tid >> 4, j = tid & 15;   // step n + j
-    const int64_t nn = n + j;
-    double w = 0.0;
-    if (j <= (sync ? 0 : p.L + T - 2) && nn < q.nsteps) {
-      const int k = delay3(p, neighbour3(p, pe, f), f ^ 1, nn), m = j - k;
-      if (m >= 0 && m < T) w = q.wt[k][m];
-    }
-    s_cw[f][j] = w;                         // j = 0: 1 where the neighbour's delay is 0
-  }
-  if (tid >= 96 && tid < 96 + 3 * 2 * (2 * S + 1) && tid < nt) {
-    const int i = tid - 96, a = i / (2 * (2 * S + 1)), r = i % (2 * (2 * S + 1)), up = r / (2 * S + 1), o = r % (2 * S + 1);
-    const int at = up ? S + o : S - o;
-    const bool in = o >= 1 && o <= S;
-    s_t1[a][up][o] = !in ? 0.0 : BURG ? p.alpha * p.c2[a][at] : p.kad[a][at];
-    s_t2[a][up][o] = !in || !BURG ? 0.0 : p.c1[a][at];
-  }
   // zero frames of mu
   for (int i = tid; i < 2 * plane; i += nt) sY[i] = Y(0);
-  __syncthreads();
-  if (tid < 6) {
-    const int f = tid;
-    s_own[f] = s_cw[f][0] != 0.0;
-    int c = 0;
-    for (int j = 1; j < 16; ++j) {
-      const double w = s_cw[f][j];
-      if (w != 0.0) {
-        s_dw[f][c] = w;
-        s_goff[f][c] = static_cast<int64_t>(static_cast<int>((n + j) % q.anslots)) * slot_step(f);
-        ++c;
-      }
-    }
-    s_cnt[f] = c;
-    for (; c < kMaxDrain; ++c) {
-      s_dw[f][c] = 0.0;
-      s_goff[f][c] = 0;
-    }
-  }
-  __syncthreads();
+  face_setup<S, TT, 6, BURG>(q, pe, fc);
 
   // ---- fields: plane z of PE e starts at e's base + z zs, rows pitch apart
   const int64_t pitch = p.pe_major ? bx : p.nx;
@@ -247,12 +105,12 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
     }
   }
   const int side = f & 1, axis = f >> 1;
-  const int nb = s_nbr[f];
+  const int nb = fc.nbr[f];
   // distance beyond the face of the neighbour's entry, and inside it of the own one
   const int e_out = side ? d : S - 1 - d, e_in = side ? S - 1 - d : d;
-  const bool send = item && !sync && s_k[f] > 0;
-  const bool own = item && s_own[f] != 0;
-  const int cnt = item ? s_cnt[f] : 0;
+  const bool send = item && !sync && fc.k[f] > 0;
+  const bool own = item && fc.own[f] != 0;
+  const int cnt = item ? fc.cnt[f] : 0;
   const bool wave_own = __any(own ? 1 : 0);
   int wave_cnt = cnt;
 #pragma unroll
@@ -268,16 +126,16 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
       hsrc = C + pe_base(nb) + static_cast<int64_t>(item ? ly : 0) * pitch + (item ? lx : 0);
       hzs = zs;
     } else {
-      hsrc = F + strip0(f ^ 1, nb, q.fslots, r);
-      hzs = strip_zs(f ^ 1, q.fslots);
+      hsrc = F + strip0(p, f ^ 1, nb, q.fslots, r);
+      hzs = strip_zs(p, f ^ 1, q.fslots);
     }
   }
   // own entry in the g ring, and the neighbour's points next to the face (for
   // a delay of 0 there): ia = 0, 1, .. from the face
-  const Real* gsrc = G + strip0(f, pe, q.anslots, r);
-  const int64_t gzs = strip_zs(f, q.anslots);
-  Real* gdst = G + strip0(f ^ 1, nb, q.anslots, r) + static_cast<int64_t>(n % q.anslots) * slot_step(f ^ 1);
-  const int64_t gdzs = strip_zs(f ^ 1, q.anslots);
+  const Real* gsrc = G + strip0(p, f, pe, q.anslots, r);
+  const int64_t gzs = strip_zs(p, f, q.anslots);
+  Real* gdst = G + strip0(p, f ^ 1, nb, q.anslots, r) + static_cast<int64_t>(n % q.anslots) * slot_step(p, f ^ 1);
+  const int64_t gdzs = strip_zs(p, f ^ 1, q.anslots);
   int64_t n_at, n_step;
   {
     const int lx = axis == 0 ? (side ? 0 : bx - 1) : r - d * bx, ly = axis == 1 ? (side ? 0 : by - 1) : r / S;
@@ -307,14 +165,14 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
     if (b1) a.x1 = ld2<EVEN>(X1 + o + col, has2);
     if (any_item) {
 #pragma unroll
-      for (int m = 0; m < TT; ++m) a.h[m] = hz[s_hoff[f][m]];
+      for (int m = 0; m < TT; ++m) a.h[m] = hz[fc.hoff[f][m]];
       if (wave_cnt > 0) {
 #pragma unroll
-        for (int i = 0; i < kDrain / 2; ++i) a.g[i] = gz[s_goff[f][i]];
+        for (int i = 0; i < kDrain / 2; ++i) a.g[i] = gz[fc.goff[f][i]];
       }
       if (wave_cnt > kDrain / 2) {
 #pragma unroll
-        for (int i = kDrain / 2; i < kDrain; ++i) a.g[i] = gz[s_goff[f][i]];
+        for (int i = kDrain / 2; i < kDrain; ++i) a.g[i] = gz[fc.goff[f][i]];
       }
       if (wave_own) {
 #pragma unroll
@@ -330,16 +188,8 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
     gz += gzs;
     oz += zs;
   };
-  // transposed taps of points ia = 0 .. from a face of axis a into the point at
-  // distance e across it (up: towards larger coordinates)
   auto taps = [&](int a, int up, int e, const double (&mu)[S], const double (&pr)[S]) __attribute__((always_inline)) {
-    double g = 0.0;
-#pragma unroll
-    for (int ia = 0; ia < S; ++ia) {
-      g += s_t1[a][up][1 + e + ia] * mu[ia];
-      if (BURG) g -= s_t2[a][up][1 + e + ia] * pr[ia];
-    }
-    return g;
+    return face_taps<S, TT, 6, BURG>(fc, a, up, e, mu, pr);
   };
   const double mf = M1 ? 1.0 : m0;         // factor of the sums over Y values
   auto y_of = [&](Real a, Real b) __attribute__((always_inline)) -> Y {
@@ -355,7 +205,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
 #pragma unroll
   for (int up = 0; up < 2; ++up) {
     const int fz = 4 + up;
-    if (active && !sync && s_k[fz] > 0) {
+    if (active && !sync && fc.k[fz] > 0) {
       double mu[2][S], pr[2][S];
 #pragma unroll
       for (int ia = 0; ia < S; ++ia) {
@@ -375,23 +225,23 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
 #pragma unroll
         for (int v = 0; v < 2; ++v) g.v[v] = static_cast<Real>(mf * taps(2, up, e, mu[v], pr[v]));
         const int dd = up ? e : S - 1 - e;
-        st2<EVEN>(G + strip0(fz ^ 1, s_nbr[fz], q.anslots, rz) + dd * strip_zs(fz ^ 1, q.anslots) +
-                      static_cast<int64_t>(n % q.anslots) * slot_step(fz ^ 1), g, has2);
+        st2<EVEN>(G + strip0(p, fz ^ 1, fc.nbr[fz], q.anslots, rz) + dd * strip_zs(p, fz ^ 1, q.anslots) +
+                      static_cast<int64_t>(n % q.anslots) * slot_step(p, fz ^ 1), g, has2);
       }
     }
 #pragma unroll
     for (int dd = 0; dd < S; ++dd) {
       R2 h;
       if (sync) {
-        h = ld2<EVEN>(C + pe_base(s_nbr[fz]) + y * pitch + x + (up ? dd : bz - S + dd) * zs, has2);
+        h = ld2<EVEN>(C + pe_base(fc.nbr[fz]) + y * pitch + x + (up ? dd : bz - S + dd) * zs, has2);
       } else {
-        const Real* src = F + strip0(fz ^ 1, s_nbr[fz], q.fslots, rz) + dd * strip_zs(fz ^ 1, q.fslots);
+        const Real* src = F + strip0(p, fz ^ 1, fc.nbr[fz], q.fslots, rz) + dd * strip_zs(p, fz ^ 1, q.fslots);
         double s0 = 0.0, s1 = 0.0;
 #pragma unroll
         for (int m = 0; m < TT; ++m) {
-          const R2 l = ld2<EVEN>(src + s_hoff[fz][m], has2);
-          s0 += s_w[fz][m] * static_cast<double>(l.v[0]);
-          s1 += s_w[fz][m] * static_cast<double>(l.v[1]);
+          const R2 l = ld2<EVEN>(src + fc.hoff[fz][m], has2);
+          s0 += fc.w[fz][m] * static_cast<double>(l.v[0]);
+          s1 += fc.w[fz][m] * static_cast<double>(l.v[1]);
         }
         h.v[0] = static_cast<Real>(s0);
         h.v[1] = static_cast<Real>(s1);
@@ -421,7 +271,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
-    for (int o = 1; o <= S; ++o) ksum += s_t1[a][0][o] + s_t1[a][1][o];
+    for (int o = 1; o <= S; ++o) ksum += fc.t1[a][0][o] + fc.t1[a][1][o];
 
   double da = 0.0;
   for (int z = 0; z < bz; ++z) {
@@ -446,18 +296,18 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
     if (item) {
       double hs = 0.0;                     // (the synchronous scheme: weights 1, 0, ..)
 #pragma unroll
-      for (int m = 0; m < TT; ++m) hs += s_w[f][m] * static_cast<double>(nx.h[m]);
+      for (int m = 0; m < TT; ++m) hs += fc.w[f][m] * static_cast<double>(nx.h[m]);
       Cp[h_at] = static_cast<Real>(hs);
       double g = 0.0;
       if (wave_cnt > 0) {
 #pragma unroll
-        for (int i = 0; i < kDrain / 2; ++i) g += i < cnt ? s_dw[f][i] * static_cast<double>(nx.g[i]) : 0.0;
+        for (int i = 0; i < kDrain / 2; ++i) g += i < cnt ? fc.dw[f][i] * static_cast<double>(nx.g[i]) : 0.0;
       }
       if (wave_cnt > kDrain / 2) {
 #pragma unroll
-        for (int i = kDrain / 2; i < kDrain; ++i) g += i < cnt ? s_dw[f][i] * static_cast<double>(nx.g[i]) : 0.0;
+        for (int i = kDrain / 2; i < kDrain; ++i) g += i < cnt ? fc.dw[f][i] * static_cast<double>(nx.g[i]) : 0.0;
         // (gz is a plane ahead)
-        for (int i = kDrain; i < cnt; ++i) g += s_dw[f][i] * static_cast<double>((gz - gzs)[s_goff[f][i]]);
+        for (int i = kDrain; i < cnt; ++i) g += fc.dw[f][i] * static_cast<double>((gz - gzs)[fc.goff[f][i]]);
       }
       if (own) {
         double mu[S], pr[S];
@@ -540,15 +390,15 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
       for (int up = 0; up < 2; ++up) {
         if (up ? z < bz - S : z >= S) continue;   // uniform
         const int fz = 4 + up, dd = up ? z - (bz - S) : z, e = up ? S - 1 - dd : dd;
-        const Real* src = G + strip0(fz, pe, q.anslots, rz) + dd * strip_zs(fz, q.anslots);
-        for (int i = 0; i < s_cnt[fz]; ++i) {
-          const R2 g = ld2<EVEN>(src + s_goff[fz][i], has2);
-          in[0] += s_dw[fz][i] * static_cast<double>(g.v[0]);
-          in[1] += s_dw[fz][i] * static_cast<double>(g.v[1]);
+        const Real* src = G + strip0(p, fz, pe, q.anslots, rz) + dd * strip_zs(p, fz, q.anslots);
+        for (int i = 0; i < fc.cnt[fz]; ++i) {
+          const R2 g = ld2<EVEN>(src + fc.goff[fz][i], has2);
+          in[0] += fc.dw[fz][i] * static_cast<double>(g.v[0]);
+          in[1] += fc.dw[fz][i] * static_cast<double>(g.v[1]);
         }
-        if (s_own[fz]) {
+        if (fc.own[fz]) {
           double mu[2][S], pr[2][S];
-          const int64_t o0 = pe_base(s_nbr[fz]) + y * pitch + x;
+          const int64_t o0 = pe_base(fc.nbr[fz]) + y * pitch + x;
 #pragma unroll
           for (int ia = 0; ia < S; ++ia) {
             const int64_t g = o0 + (up ? ia : bz - 1 - ia) * zs;

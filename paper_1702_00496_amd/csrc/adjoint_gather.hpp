@@ -1,0 +1,194 @@
+// Shared by the gathering stage kernels of the adjoint (adjoint2d.hpp for 1-D
+// and 2-D, adjoint3d.hpp for 3-D; adjoint.hip states the method and the
+// formula). One workgroup does everything a stage does for a PE, and every
+// value is gathered:
+//  - the forward halo values (for the Laplacian and the gradient of the stage
+//    field) are the forward step's own combinations, read from the segment's
+//    ring, whose slots keep every level of the segment;
+//  - the transposed taps that leave a PE across a face with a delay go, once,
+//    to the g ring: g_n[entry] = sum K mu over the consumer's points, in the
+//    ring slot of step n at the neighbour's strip entry;
+//  - the adjoint of level n of a strip entry is then the sum over the later
+//    steps n' = n + j whose delay k' reaches level n (0 <= j - k' < T) of
+//    c_{j-k'}(k') g_{n'}, and, where the neighbour's delay at n is 0, of the
+//    neighbour's taps themselves. No ring entry is read and written back, or
+//    cleared; the sums are in double.
+#pragma once
+
+#include <type_traits>
+
+#include "adjoint.hpp"
+
+namespace atfd {
+namespace adjg {
+
+constexpr int kDrain = 6;        // g values of an entry read ahead (more: a loop)
+constexpr int kMaxDrain = kMaxL + kMaxT;
+
+template <typename Real>
+struct Two {
+  Real v[2];
+};
+
+// Two consecutive values; EVEN: PE x edges are even, so both exist; else the
+// second repeats the first past the PE's row.
+template <bool EVEN, typename Real>
+__device__ __forceinline__ Two<Real> ld2(const Real* p, bool has2) {
+  Two<Real> r;
+  if constexpr (EVEN) {
+    __builtin_memcpy(&r, p, sizeof(r));
+  } else {
+    r.v[0] = p[0];
+    r.v[1] = p[has2 ? 1 : 0];
+  }
+  return r;
+}
+template <bool EVEN, typename Real>
+__device__ __forceinline__ void st2(Real* p, const Two<Real>& q, bool has2) {
+  if constexpr (EVEN) {
+    __builtin_memcpy(p, &q, sizeof(q));
+  } else {
+    p[0] = q.v[0];
+    if (has2) p[1] = q.v[1];
+  }
+}
+
+// Neighbour PE across face f = 2 axis + side (periodic).
+__device__ __forceinline__ int neighbour_of(const StepParams& p, int pid, int f) {
+  const int qx = pid % p.px, qy = (pid / p.px) % p.py, qz = pid / (p.px * p.py);
+  const int up = f & 1;
+  if (f < 2) return (up ? (qx + 1 == p.px ? 0 : qx + 1) : (qx == 0 ? p.px - 1 : qx - 1)) + p.px * (qy + p.py * qz);
+  if (f < 4) return qx + p.px * ((up ? (qy + 1 == p.py ? 0 : qy + 1) : (qy == 0 ? p.py - 1 : qy - 1)) + p.py * qz);
+  return qx + p.px * (qy + p.py * (up ? (qz + 1 == p.pz ? 0 : qz + 1) : (qz == 0 ? p.pz - 1 : qz - 1)));
+}
+
+// Delay of face f of PE pid at step n (the synchronous scheme: 0).
+__device__ __forceinline__ int delay_of(const StepParams& p, int pid, int f, int64_t n) {
+  int k = 0;
+  if (p.mode == AT_DELAY_RNG)
+    k = raw_delay(p.key, n, static_cast<uint32_t>(pid * 2 * p.ndim + f), p.thr, p.L);
+  else if (p.mode == AT_DELAY_HOST)
+    k = p.host_delays[(n * p.npe + pid) * (2 * p.ndim) + f];
+  else
+    return 0;
+  return clamp_startup(k, n, p.T);
+}
+
+// Strips in a ring (ring_index): element r of plane z of face f of PE e in slot
+// s lies at strip0(f, e, slots, r) + s slot_step(f) + z strip_zs(f, slots).
+__device__ __forceinline__ int64_t chunk_of(const StepParams& p, int f) {
+  // (every value is read and one selected: a read behind the select would be of
+  // a run-time address and put the kernel's arguments in scratch memory)
+  const int64_t a = p.face_chunk[0], b = p.face_chunk[2], c = p.face_chunk[4];
+  return f < 2 ? a : f < 4 ? b : c;
+}
+__device__ __forceinline__ int64_t foff_of(const StepParams& p, int f) {
+  const int64_t o0 = p.face_off[0], o1 = p.face_off[1], o2 = p.face_off[2], o3 = p.face_off[3], o4 = p.face_off[4],
+                o5 = p.face_off[5];
+  return f == 0 ? o0 : f == 1 ? o1 : f == 2 ? o2 : f == 3 ? o3 : f == 4 ? o4 : o5;
+}
+__device__ __forceinline__ int64_t strip0(const StepParams& p, int f, int e, int slots, int64_t r) {
+  return p.pe_major ? slots * foff_of(p, f) + static_cast<int64_t>(e) * slots * chunk_of(p, f) + r
+                    : foff_of(p, f) + e * chunk_of(p, f) + r;
+}
+__device__ __forceinline__ int64_t slot_step(const StepParams& p, int f) {
+  return p.pe_major ? chunk_of(p, f) : static_cast<int64_t>(p.npe) * p.pe_block;
+}
+__device__ __forceinline__ int64_t strip_zs(const StepParams& p, int f, int slots) {
+  return static_cast<int64_t>(p.npe) * chunk_of(p, f) * (p.pe_major ? slots : 1);
+}
+
+// What a stage needs of the PE's faces (LDS): neighbours and this PE's delays;
+// the forward combination of the stage field across face f (weights, offsets
+// of the slots in the neighbour's strip; a level of weight zero re-reads level
+// n - k); the entries of the g ring that reach level n (weights, offsets of the
+// slots in this PE's strip, zero past the count), and whether the neighbour's
+// delay at n is 0; the taps by |o| (0 beyond S), [o > 0][|o|]: t1 = alpha c2
+// (Burgers) or kad, t2 = c1 (Burgers).
+template <int S, int TT, int NF>
+struct Faces {
+  int64_t hoff[NF][TT], goff[NF][kMaxDrain];
+  double w[NF][TT], dw[NF][kMaxDrain], cw[NF][16];
+  double t1[3][2][2 * S + 1], t2[3][2][2 * S + 1];
+  int nbr[NF], k[NF], own[NF], cnt[NF];
+};
+
+// Fills fc; ends with a barrier. The draws of all faces and later steps run side
+// by side; at least 160 threads.
+template <int S, int TT, int NF, bool BURG>
+__device__ __forceinline__ void face_setup(const AdjParams& q, int pe, Faces<S, TT, NF>& fc) {
+  const StepParams& p = q.sp;
+  const int tid = threadIdx.x;
+  const int64_t n = q.n;
+  const bool sync = p.mode == AT_SYNC;
+  const int T = sync ? 1 : p.T;
+  if (tid < 16 * NF) {
+    const int f = tid >> 4, j = tid & 15;   // step n + j of the neighbour's face
+    const int64_t nn = n + j;
+    double w = 0.0;
+    if (j <= (sync ? 0 : p.L + T - 2) && nn < q.nsteps) {
+      const int k = delay_of(p, neighbour_of(p, pe, f), f ^ 1, nn), m = j - k;
+      if (m >= 0 && m < T) w = q.wt[k][m];
+    }
+    fc.cw[f][j] = w;                        // j = 0: 1 where the neighbour's delay is 0
+  } else if (tid < 16 * NF + NF) {
+    const int f = tid - 16 * NF;
+    fc.nbr[f] = neighbour_of(p, pe, f);
+    const int k = delay_of(p, pe, f, n);
+    fc.k[f] = k;
+    const int r0 = static_cast<int>(n % q.fslots);
+    for (int m = 0; m < TT; ++m) {
+      const double w = m < T ? q.wt[k][m] : 0.0;
+      fc.w[f][m] = w;
+      fc.hoff[f][m] = sync ? 0 : slot_back(r0, k + (w != 0.0 ? m : 0), q.fslots) * slot_step(p, f ^ 1);
+    }
+  }
+  if (tid >= 112 && tid < 112 + 3 * 2 * (2 * S + 1)) {
+    const int i = tid - 112, a = i / (2 * (2 * S + 1)), r = i % (2 * (2 * S + 1)), up = r / (2 * S + 1),
+              o = r % (2 * S + 1);
+    const int at = up ? S + o : S - o;
+    const bool in = o >= 1 && o <= S;
+    fc.t1[a][up][o] = !in ? 0.0 : BURG ? p.alpha * p.c2[a][at] : p.kad[a][at];
+    fc.t2[a][up][o] = !in || !BURG ? 0.0 : p.c1[a][at];
+  }
+  __syncthreads();
+  if (tid < NF) {
+    const int f = tid;
+    fc.own[f] = fc.cw[f][0] != 0.0;
+    const int64_t ss = slot_step(p, f);
+    int c = 0, slot = static_cast<int>(n % q.anslots);
+    for (int j = 1; j < 16; ++j) {
+      slot = slot + 1 == q.anslots ? 0 : slot + 1;
+      const double w = fc.cw[f][j];
+      if (w != 0.0) {
+        fc.dw[f][c] = w;
+        fc.goff[f][c] = slot * ss;
+        ++c;
+      }
+    }
+    fc.cnt[f] = c;
+    for (; c < kMaxDrain; ++c) {
+      fc.dw[f][c] = 0.0;
+      fc.goff[f][c] = 0;
+    }
+  }
+  __syncthreads();
+}
+
+// The transposed taps of the points ia = 0 .. S - 1 counted from a face of axis
+// a into the point at distance e across it (up: towards larger coordinates); mu
+// and, for Burgers, pr = c mu at those points.
+template <int S, int TT, int NF, bool BURG>
+__device__ __forceinline__ double face_taps(const Faces<S, TT, NF>& fc, int a, int up, int e, const double (&mu)[S],
+                                   const double (&pr)[S]) {
+  double g = 0.0;
+#pragma unroll
+  for (int ia = 0; ia < S; ++ia) {
+    g += fc.t1[a][up][1 + e + ia] * mu[ia];
+    if (BURG) g -= fc.t2[a][up][1 + e + ia] * pr[ia];
+  }
+  return g;
+}
+
+}  // namespace adjg
+}  // namespace atfd

@@ -847,7 +847,7 @@ struct AdjLayout {
   int anslots = 0;
   int rslots = 0;          // slots of a segment's ring (0: the synchronous arm has none)
   bool rk2 = false;
-  bool gather = false;     // 3-D stage kernel: nothing of the adjoint ring is read before it is written
+  bool gather = false;     // gathering stage kernels: nothing of the adjoint ring is read before it is written
 };
 
 AdjLayout adj_layout(const at_ctx* c, int64_t nsteps, int every) {
@@ -856,7 +856,7 @@ AdjLayout adj_layout(const at_ctx* c, int64_t nsteps, int every) {
   const size_t w = c->g.f64 ? 8 : 4;
   a.nck = (nsteps + every - 1) / every;
   a.rk2 = c->prob.integrator == AT_RK2;
-  a.gather = adj3d_applies(c->sp, c->g.f64);
+  a.gather = adj_gather(c->sp, c->g.f64);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
