@@ -235,7 +235,7 @@ __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const
   for (int m = 0; m < kMaxT; ++m) {
     if (m >= T) break;
     // level n - k - m (before t = 0 only where w[m] = 0: any slot is read)
-    const int slot = slot_back(static_cast<int>(q.n % q.anslots), k + m, q.anslots);
+    const int slot = slot_back(q.gslot, k + m, q.anslots);
     dst[m] = aring + ring_at_pt(p, slot, pe, F, lsF, S);
     old[m] = static_cast<double>(*dst[m]);
   }
@@ -269,11 +269,10 @@ __device__ inline Real halo_value(const AdjParams& q, const StripPt& sp, const d
   // level T - 1 and is dropped below, like a level of weight zero), so the
   // loads overlap
   const Real* R = static_cast<const Real*>(q.fring);
-  const int rn = static_cast<int>(q.n % q.fslots);
   double lv[kMaxT];
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m)
-    lv[m] = static_cast<double>(R[ring_at_pt(p, slot_back(rn, k + min(m, T - 1), q.fslots), src, pf, ls, S)]);
+    lv[m] = static_cast<double>(R[ring_at_pt(p, slot_back(q.fslot, k + min(m, T - 1), q.fslots), src, pf, ls, S)]);
   double v = 0.0;
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m)
@@ -318,7 +317,7 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
   const Real* __restrict__ C = static_cast<const Real*>(q.levels) + (q.n - q.seg_start) * q.npts;
   const Real* __restrict__ hb = static_cast<const Real*>(q.hbuf);
   Real* __restrict__ aring = static_cast<Real*>(q.aring);
-  const int slot_n = static_cast<int>(q.n % q.anslots);
+  const int slot_n = q.gslot;
   const int64_t st[3] = {1, p.nx, static_cast<int64_t>(p.nx) * p.ny};
   double da = 0.0;
   for (int64_t g = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; g < q.npts;

@@ -25,12 +25,12 @@ struct AdjParams {
   const void* levels;              // stored levels of the stage field from seg_start, npts apart
   int64_t seg_start;
   const void* fring;               // that field's ring of the segment: fslots slots, level l in l mod fslots
-  int fslots;
+  int fslots, fslot;               // (fslot = n mod fslots)
   int64_t nsteps;                  // steps of the whole run
   void* hbuf;                      // forward halo values of this stage [pe][face strips]
   int64_t pfo[6];                  // offset of face f's strip inside one PE's pe_block values
   void* aring;                     // adjoint ring of the stage field, anslots slots (3-D kernel: the g ring)
-  int anslots;
+  int anslots, gslot;              // (gslot = n mod anslots)
   double* partial;                 // [adj_partials] alpha-gradient partial sums
   double wt[kMaxL][kMaxT];         // level weights c_m(k) of every delay k < L (host-computed)
 };

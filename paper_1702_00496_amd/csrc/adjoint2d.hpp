@@ -197,7 +197,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
         mu[ia] = static_cast<double>(sY[in_at + ia * step]);
         pr[ia] = BURG ? static_cast<double>(sC[in_at + ia * step]) * mu[ia] : 0.0;
       }
-      G[strip0(p, t.f ^ 1, fc.nbr[t.f], q.anslots, t.r) + static_cast<int64_t>(n % q.anslots) * slot_step(p, t.f ^ 1)] =
+      G[strip0(p, t.f ^ 1, fc.nbr[t.f], q.anslots, t.r) + q.gslot * slot_step(p, t.f ^ 1)] =
           static_cast<Real>(mf * face_taps<S, TT, NF, BURG>(fc, axis, side, side ? t.d : S - 1 - t.d, mu, pr));
     }
 

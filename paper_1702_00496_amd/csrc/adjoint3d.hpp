@@ -134,7 +134,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
   // a delay of 0 there): ia = 0, 1, .. from the face
   const Real* gsrc = G + strip0(p, f, pe, q.anslots, r);
   const int64_t gzs = strip_zs(p, f, q.anslots);
-  Real* gdst = G + strip0(p, f ^ 1, nb, q.anslots, r) + static_cast<int64_t>(n % q.anslots) * slot_step(p, f ^ 1);
+  Real* gdst = G + strip0(p, f ^ 1, nb, q.anslots, r) + q.gslot * slot_step(p, f ^ 1);
   const int64_t gdzs = strip_zs(p, f ^ 1, q.anslots);
   int64_t n_at, n_step;
   {
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
         for (int v = 0; v < 2; ++v) g.v[v] = static_cast<Real>(mf * taps(2, up, e, mu[v], pr[v]));
         const int dd = up ? e : S - 1 - e;
         st2<EVEN>(G + strip0(p, fz ^ 1, fc.nbr[fz], q.anslots, rz) + dd * strip_zs(p, fz ^ 1, q.anslots) +
-                      static_cast<int64_t>(n % q.anslots) * slot_step(p, fz ^ 1), g, has2);
+                      q.gslot * slot_step(p, fz ^ 1), g, has2);
       }
     }
 #pragma unroll

@@ -23,7 +23,7 @@ namespace atfd {
 namespace adjg {
 
 constexpr int kDrain = 6;        // g values of an entry read ahead (more: a loop)
-constexpr int kMaxDrain = kMaxL + kMaxT;
+constexpr int kMaxDrain = 15;    // steps n + 1 .. n + 15 (at most L + T - 2 = 10 reach level n)
 
 template <typename Real>
 struct Two {
@@ -108,7 +108,7 @@ __device__ __forceinline__ int64_t strip_zs(const StepParams& p, int f, int slot
 template <int S, int TT, int NF>
 struct Faces {
   int64_t hoff[NF][TT], goff[NF][kMaxDrain];
-  double w[NF][TT], dw[NF][kMaxDrain], cw[NF][16];
+  double w[NF][TT], dw[NF][kMaxDrain];
   double t1[3][2][2 * S + 1], t2[3][2][2 * S + 1];
   int nbr[NF], k[NF], own[NF], cnt[NF];
 };
@@ -130,17 +130,32 @@ __device__ __forceinline__ void face_setup(const AdjParams& q, int pe, Faces<S, 
       const int k = delay_of(p, neighbour_of(p, pe, f), f ^ 1, nn), m = j - k;
       if (m >= 0 && m < T) w = q.wt[k][m];
     }
-    fc.cw[f][j] = w;                        // j = 0: 1 where the neighbour's delay is 0
+    // the 16 lanes of a face compact their entries; j = 0 is the neighbour's
+    // own step (weight 1 where its delay is 0), the rest follow in order
+    const uint64_t live = __ballot(j > 0 && w != 0.0);
+    const uint32_t group = static_cast<uint32_t>(live >> ((tid & 63) & ~15)) & 0xffffu;
+    const uint32_t below = group & ((1u << j) - 1u);
+    const int cnt = __popc(group);
+    if (j == 0) {
+      fc.own[f] = w != 0.0;
+      fc.cnt[f] = cnt;
+    } else {
+      const bool on = w != 0.0;
+      int slot = q.gslot + j;
+      while (slot >= q.anslots) slot -= q.anslots;   // (anslots = 1: the synchronous arm)
+      const int at = on ? __popc(below) : cnt + (j - 1) - __popc(below);
+      fc.dw[f][at] = w;
+      fc.goff[f][at] = on ? slot * slot_step(p, f) : 0;
+    }
   } else if (tid < 16 * NF + NF) {
     const int f = tid - 16 * NF;
     fc.nbr[f] = neighbour_of(p, pe, f);
     const int k = delay_of(p, pe, f, n);
     fc.k[f] = k;
-    const int r0 = static_cast<int>(n % q.fslots);
     for (int m = 0; m < TT; ++m) {
       const double w = m < T ? q.wt[k][m] : 0.0;
       fc.w[f][m] = w;
-      fc.hoff[f][m] = sync ? 0 : slot_back(r0, k + (w != 0.0 ? m : 0), q.fslots) * slot_step(p, f ^ 1);
+      fc.hoff[f][m] = sync ? 0 : slot_back(q.fslot, k + (w != 0.0 ? m : 0), q.fslots) * slot_step(p, f ^ 1);
     }
   }
   if (tid >= 112 && tid < 112 + 3 * 2 * (2 * S + 1)) {
@@ -150,27 +165,6 @@ __device__ __forceinline__ void face_setup(const AdjParams& q, int pe, Faces<S, 
     const bool in = o >= 1 && o <= S;
     fc.t1[a][up][o] = !in ? 0.0 : BURG ? p.alpha * p.c2[a][at] : p.kad[a][at];
     fc.t2[a][up][o] = !in || !BURG ? 0.0 : p.c1[a][at];
-  }
-  __syncthreads();
-  if (tid < NF) {
-    const int f = tid;
-    fc.own[f] = fc.cw[f][0] != 0.0;
-    const int64_t ss = slot_step(p, f);
-    int c = 0, slot = static_cast<int>(n % q.anslots);
-    for (int j = 1; j < 16; ++j) {
-      slot = slot + 1 == q.anslots ? 0 : slot + 1;
-      const double w = fc.cw[f][j];
-      if (w != 0.0) {
-        fc.dw[f][c] = w;
-        fc.goff[f][c] = slot * ss;
-        ++c;
-      }
-    }
-    fc.cnt[f] = c;
-    for (; c < kMaxDrain; ++c) {
-      fc.dw[f][c] = 0.0;
-      fc.goff[f][c] = 0;
-    }
   }
   __syncthreads();
 }

@@ -1095,6 +1095,8 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
       q.hbuf = sc + a.off_hbuf;
       q.anslots = a.anslots;
       q.fslots = a.rslots > 0 ? a.rslots : 1;
+      q.fslot = mod_small(n, q.fslots);
+      q.gslot = mod_small(n, q.anslots);
       q.nsteps = N;
       q.seg_start = seg;
       q.partial = reinterpret_cast<double*>(sc + a.off_partial);

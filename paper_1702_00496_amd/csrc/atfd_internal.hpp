@@ -34,14 +34,25 @@ __host__ __device__ inline uint64_t mix64(uint64_t z) {
 
 // Raw delay of (step n, face id) before the start-up clamp: the top 53 bits
 // of the hash are binned by the cumulative thresholds thr[0..L-1]
-// (thr[L-1] = 2^53), as in the bin matching of Sec. 5.1.
+// (thr[L-1] = 2^53), as in the bin matching of Sec. 5.1. The thresholds ascend,
+// so the bin is the number of those reached: they are read side by side (a
+// search that stops at the bin reads them one after the other, a memory latency
+// each).
 __host__ __device__ inline int raw_delay(uint64_t key, int64_t n, uint32_t face,
                                          const uint64_t* thr, int L) {
   const uint64_t ctr = ((static_cast<uint64_t>(n) << 32) | face) + 1ull;
   const uint64_t u53 = mix64(key + ctr * kGolden) >> 11;
   int k = 0;
-  while (k < L - 1 && u53 >= thr[k]) ++k;
+#pragma unroll
+  for (int j = 0; j < kMaxL - 1; ++j) k += (j < L - 1 && u53 >= thr[j]) ? 1 : 0;
   return k;
+}
+
+// n mod m for 0 <= n, 0 < m < 2^31, in 32 bits while n fits them (a 64-bit
+// remainder takes several times as many instructions).
+__host__ __device__ inline int mod_small(int64_t n, int m) {
+  if ((n >> 31) == 0) return static_cast<int>(static_cast<uint32_t>(n) % static_cast<uint32_t>(m));
+  return static_cast<int>(n % m);
 }
 
 // Ring slot of level n - back from r0 = n mod nslots, for 0 <= back < nslots
@@ -64,16 +75,39 @@ __host__ __device__ inline int clamp_startup(int k, int64_t n, int T) {
 // Lagrange basis on nodes k, k+1, .., k+T-1 evaluated at 0:
 //   w_m(k) = prod_{i != m} (k + i) / (i - m).
 // For k = 0 this is (1, 0, .., 0): the scheme is the standard CD.
-__host__ __device__ inline void level_weights(int k, int T, double* w) {
-  for (int m = 0; m < T; ++m) {
-    double num = 1.0, den = 1.0;
-    for (int i = 0; i < T; ++i) {
-      if (i == m) continue;
-      num *= static_cast<double>(k + i);
-      den *= static_cast<double>(i - m);
-    }
-    w[m] = num / den;
+// The weights are integers, (-1)^m C(k + m - 1, m) C(k + T - 1, T - 1 - m) in
+// magnitude: exact integer products and a division by m! (T - 1 - m)!, which is
+// 1, 2 or 6. Entries m >= T are zero.
+__host__ __device__ inline void level_weights(int k, int T, double (&w)[kMaxT]) {
+#pragma unroll
+  for (int m = 0; m < kMaxT; ++m) {
+    uint32_t num = 1;
+#pragma unroll
+    for (int i = 0; i < kMaxT; ++i) num *= (i == m || i >= T) ? 1u : static_cast<uint32_t>(k + i);
+    const int rest = T - 1 - m;
+    const int f = m < 2 ? 1 : m == 2 ? 2 : 6, g = rest < 2 ? 1 : rest == 2 ? 2 : 6;
+    const int den = f * g;
+    const uint32_t q = den == 1 ? num : den == 2 ? num / 2u : num / 6u;
+    const double v = static_cast<double>(q);
+    w[m] = m >= T ? 0.0 : (m & 1) ? -v : v;
   }
+}
+
+// A workgroup-uniform value into scalar registers.
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+__device__ inline double uniform(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+__device__ inline int64_t uniform(int64_t v) {
+  return static_cast<int64_t>(
+      (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)))) << 32) |
+      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v))));
+}
+template <typename P>
+__device__ inline P* uniform(P* p) {
+  return reinterpret_cast<P*>(uniform(static_cast<int64_t>(reinterpret_cast<uintptr_t>(p))));
 }
 
 // ---------------------------------------------------------------- kernels

@@ -146,24 +146,6 @@ __device__ inline Real euler_update(Real u0, Real dt, Real f) {
   return fmadd(dt, f, u0);
 }
 
-// A workgroup-uniform value into scalar registers.
-__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ inline float uniform(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
-__device__ inline double uniform(double v) {
-  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
-                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
-}
-
-__device__ inline int64_t uniform(int64_t v) {
-  return static_cast<int64_t>(
-      (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32)))) << 32) |
-      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v))));
-}
-template <typename P>
-__device__ inline P* uniform(P* p) {
-  return reinterpret_cast<P*>(uniform(static_cast<int64_t>(reinterpret_cast<uintptr_t>(p))));
-}
-
 // Device memory of one line's run: the fields at its first and last step, the
 // history (f0; AB3 also f1, by step parity), the predictor (Heun), the rings,
 // a host delay table [step][pe][side].
@@ -477,7 +459,7 @@ __device__ __forceinline__ void line_run(const Line& Mref, const LinePlan& pl, c
 
   const int batch = line_batch(faces);
   int par = 0;
-  int r0 = nslots > 0 ? static_cast<int>(n0 % nslots) : 0;
+  int r0 = nslots > 0 ? mod_small(n0, nslots) : 0;
   // The delays are drawn two steps ahead of their use at least: batch j (steps
   // j batch ..) into half j & 1 during step j batch - 2, whose threads have all
   // read what that half held before the barrier that began it.

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kB * kB / V) void at_step3d_fast_kernel(StepParams 
   const int tid = threadIdx.x;
   const int vi = tid % VPR, y = tid / VPR;
   const int x = V * vi;
-  const int64_t n = p.counter[0];
+  const int64_t n = uniform(p.counter[0]);
   // a downward sweep also takes the PEs in the opposite order, so that when
   // there are more PEs than resident workgroups the launch starts on the PEs
   // the previous one finished last
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kB * kB / V) void at_step3d_fast_kernel(StepParams 
       // a level whose weight is zero re-reads level n-k (same lines, cache
       // hits) and is multiplied by an exact zero, so every read is issued
       // without a branch
-      const int r0 = static_cast<int>(n % p.nslots);
+      const int r0 = mod_small(n, p.nslots);
       const int s0 = slot_back(r0, k, p.nslots);
       for (int m = 0; m < kMaxT; ++m) {
         const bool live = m < TT && w[m] != 0.0;
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kB * kB / V) void at_step3d_fast_kernel(StepParams 
   const Real dt = static_cast<Real>(p.dt);
   Real* unext = static_cast<Real*>(KIND == kRk1 ? p.ustar : p.ubuf[(n + 1) & 1]);
   Real* pub = static_cast<Real*>(KIND == kRk1 ? p.sring : p.ring);
-  const int pslot = static_cast<int>((KIND == kRk1 ? n : n + 1) % (p.nslots > 0 ? p.nslots : 1));
+  const int pslot = p.nslots > 0 ? mod_small(KIND == kRk1 ? n : n + 1, p.nslots) : 0;
   // this PE's strips in the ring slot of the new level (ring_index): plane
   // z of an x or y face at nslots face_off + ((z npe + pid) nslots + slot)
   // chunk, depth d of a z face likewise with plane d

@@ -925,7 +925,7 @@ struct Sweep {
     if (p.mode == AT_SYNC) return;
     const bool rk1 = p.stage == kStageRk1;
     Real* R = static_cast<Real*>(rk1 ? p.sring : p.ring);
-    const int slot = static_cast<int>((rk1 ? n : n + 1) % p.nslots);
+    const int slot = mod_small(rk1 ? n : n + 1, p.nslots);
     slot_base = R + static_cast<int64_t>(slot) * p.npe * p.pe_block;
 #pragma unroll
     for (int f = 0; f < (DIM >= 2 ? 4 : 2); ++f)
@@ -1000,7 +1000,7 @@ __device__ inline void nonuniform_face(const StepParams& p, int pid, int f, int6
   const bool use = k1 != 0 || k2 != 0;
   if (use && 3 * k1 == k2) ++k1;
   kpos[f] = use;
-  const int r0 = static_cast<int>(n % p.nslots);
+  const int r0 = mod_small(n, p.nslots);
   slot[f * kMaxT + 0] = slot_back(r0, k1, p.nslots);
   slot[f * kMaxT + 1] = slot_back(r0, k2, p.nslots);
   const int a = f >> 1;
@@ -1094,7 +1094,7 @@ __global__ __launch_bounds__(PIPE ? kMaxVec3Threads : kMaxSweepThreads) void at_
       s_kpos[f] = k > 0;
       if constexpr (SP != 0)
         if (VEC && k > 0) face_delta_taps<Real, SP>(p, f, nullptr, s_dt + f * kDtaps);
-      const int r0 = static_cast<int>(n % p.nslots);
+      const int r0 = mod_small(n, p.nslots);
       double w[kMaxT];
       level_weights(k, p.T, w);
       for (int m = 0; m < kMaxT; ++m) {
