@@ -372,8 +372,10 @@ void fill_line(at_ctx* c) {
 }
 
 // Queue the kernels of one time step on `st`, with the context's parameters
-// or with `p` (the same problem, other solution buffers).
-at_status enqueue_step_p(at_ctx* c, StepParams p, hipStream_t st) {
+// or with `p` (the same problem, other solution buffers): step `off` after the
+// one the counter holds; the last step queued (`last`) moves the counter.
+at_status enqueue_step_p(at_ctx* c, StepParams p, hipStream_t st, int64_t off, bool last) {
+  p.step_off = off;
   // alternating schedule variants: every launch sweeps z the other way from
   // the one before it (the direction is a schedule choice only)
   const bool alt = (p.depth & 16) != 0;
@@ -383,10 +385,11 @@ at_status enqueue_step_p(at_ctx* c, StepParams p, hipStream_t st) {
     p.sweep_down = 0;
     HIP_TRY(c, launch_step(p, c->g.f64, c->g.s, st));
     p.stage = kStageRk2;
-    p.advance = 1;
+    p.advance = last ? 1 : 0;
     p.sweep_down = alt ? 1 : 0;
     HIP_TRY(c, launch_step(p, c->g.f64, c->g.s, st));
   } else {
+    p.advance = last ? 1 : 0;
     p.sweep_down = alt ? c->sweep_parity : 0;
     c->sweep_parity ^= 1;
     HIP_TRY(c, launch_step(p, c->g.f64, c->g.s, st));
@@ -394,7 +397,9 @@ at_status enqueue_step_p(at_ctx* c, StepParams p, hipStream_t st) {
   return AT_OK;
 }
 
-at_status enqueue_step(at_ctx* c, hipStream_t st) { return enqueue_step_p(c, c->sp, st); }
+at_status enqueue_step(at_ctx* c, hipStream_t st, int64_t off, bool last) {
+  return enqueue_step_p(c, c->sp, st, off, last);
+}
 
 // Teardown calls below: a failure to release leaves nothing to recover, so
 // their status is deliberately discarded.
@@ -513,7 +518,8 @@ at_status at_step(at_ctx* c, int64_t nsteps) {
       if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
       HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
       at_status st = AT_OK;
-      for (int i = 0; i < c->graph_chunk && st == AT_OK; ++i) st = enqueue_step(c, c->cap_stream);
+      for (int i = 0; i < c->graph_chunk && st == AT_OK; ++i)
+        st = enqueue_step(c, c->cap_stream, i, i + 1 == c->graph_chunk);
       hipGraph_t gr = nullptr;
       hipError_t e = hipStreamEndCapture(c->cap_stream, &gr);
       if (st != AT_OK) {
@@ -529,8 +535,8 @@ at_status at_step(at_ctx* c, int64_t nsteps) {
       done += c->graph_chunk;
     }
   }
-  for (; done < nsteps; ++done) {
-    at_status st = enqueue_step(c, c->stream);
+  for (const int64_t first = done; done < nsteps; ++done) {
+    at_status st = enqueue_step(c, c->stream, done - first, done + 1 == nsteps);
     if (st != AT_OK) return st;
   }
   c->n += nsteps;
@@ -589,9 +595,9 @@ at_status at_autotune(at_ctx* c, void* scratch_dev, size_t scratch_bytes, int32_
     if (chunk_variant(cand[i]) ? chunks_apply : fast3d_applies(trial, c->g.f64)) {
       c->sp.depth = cand[i];
       st = at_load(c, scratch_dev);
-      if (st == AT_OK) st = enqueue_step(c, c->stream);          // warm-up
+      if (st == AT_OK) st = enqueue_step(c, c->stream, 0, true);   // warm-up
       if (st == AT_OK && hipEventRecord(e0, c->stream) != hipSuccess) st = AT_EHIP;
-      for (int k = 0; k < nsteps && st == AT_OK; ++k) st = enqueue_step(c, c->stream);
+      for (int k = 0; k < nsteps && st == AT_OK; ++k) st = enqueue_step(c, c->stream, k, k + 1 == nsteps);
       if (st == AT_OK && hipEventRecord(e1, c->stream) != hipSuccess) st = AT_EHIP;
       if (st == AT_OK && hipEventSynchronize(e1) != hipSuccess) st = AT_EHIP;
       float t = 0.f;
@@ -1018,7 +1024,7 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
       p.ubuf[n & 1] = levels + l.field_bytes * (j - 1);
       p.ubuf[(n + 1) & 1] = levels + l.field_bytes * j;
       if (a.rk2) p.ustar = slevels + l.field_bytes * (j - 1);
-      const at_status r = enqueue_step_p(c, p, st);
+      const at_status r = enqueue_step_p(c, p, st, j - 1, false);
       if (r != AT_OK) return r;
     }
     if (!last) return AT_OK;

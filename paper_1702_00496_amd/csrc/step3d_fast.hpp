@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kB * kB / V) void at_step3d_fast_kernel(StepParams 
   const int tid = threadIdx.x;
   const int vi = tid % VPR, y = tid / VPR;
   const int x = V * vi;
-  const int64_t n = uniform(p.counter[0]);
+  const int64_t n = uniform(p.counter[0]) + p.step_off;
   // a downward sweep also takes the PEs in the opposite order, so that when
   // there are more PEs than resident workgroups the launch starts on the PEs
   // the previous one finished last
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(kB * kB / V) void at_step3d_fast_kernel(StepParams 
     }
   }
 
-  if (KIND != kRk1) {
+  if (KIND != kRk1 && p.advance) {
     // every workgroup has read n before its own increment
     __syncthreads();
     if (tid == 0) advance_counter(p.counter, n);

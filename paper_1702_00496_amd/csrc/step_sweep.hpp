@@ -1071,7 +1071,7 @@ __global__ __launch_bounds__(PIPE ? kMaxVec3Threads : kMaxSweepThreads) void at_
   __shared__ Real s_nur[SP == 3 ? 6 * kNuTaps : 1];
   __shared__ Real s_dt[SP != 0 ? 6 * kDtaps : 1];
 
-  const int64_t n = p.counter[0];
+  const int64_t n = p.counter[0] + p.step_off;
   const int pid = sweep_part<DIM>(p).pid;
   const int tid = threadIdx.x;
   // neighbours, delays and level weights of the 2 * DIM faces
