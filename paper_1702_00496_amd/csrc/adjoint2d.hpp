@@ -40,11 +40,12 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
   const int pe = blockIdx.x;
   const int64_t n = q.n;
   const bool sync = p.mode == AT_SYNC;
+  const double part0 = tid == 0 ? q.partial[pe] : 0.0;       // (ahead of its use)
   const double m0 = q.m0, m1 = q.m1;
-  const int qx = pe % p.px, qy = pe / p.px;
+  const int qy = div_index(pe, p.px), qx = pe - qy * p.px;
   const int64_t pitch = p.nx;
   auto pe_base = [&](int e) __attribute__((always_inline)) -> int64_t {
-    const int ey = e / p.px, ex = e - ey * p.px;
+    const int ey = div_index(e, p.px), ex = e - ey * p.px;
     return static_cast<int64_t>(ey) * by * pitch + static_cast<int64_t>(ex) * bx;
   };
   const int64_t base = static_cast<int64_t>(qy) * by * pitch + static_cast<int64_t>(qx) * bx;
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
     R2 c, y0, y1, x0, x1;
   };
   auto load_own = [&](Own& o, int i) __attribute__((always_inline)) {
-    const int y = DIM == 2 ? i / vx : 0, x = 2 * (i - y * vx);
+    const int y = DIM == 2 ? div_small(i, vx) : 0, x = 2 * (i - y * vx);
     const bool has2 = EVEN || x + 1 < bx;
     const int64_t g = base + y * pitch + x;
     o.c = ld2<EVEN>(C + g, has2);
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
     if (b1) o.x1 = ld2<EVEN>(X1 + g, has2);
   };
   auto put_own = [&](const Own& o, int i) __attribute__((always_inline)) {
-    const int y = DIM == 2 ? i / vx : 0, x = 2 * (i - y * vx);
+    const int y = DIM == 2 ? div_small(i, vx) : 0, x = 2 * (i - y * vx);
     const bool has2 = EVEN || x + 1 < bx;
     const int at = (y + SY) * W + kCo + x;
     Two<Y> m;
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
       const int hy = h - nxh, side = hy >= S * bx ? 1 : 0;
       t.f = 2 + side;
       t.r = side ? hy - S * bx : hy;
-      t.d = t.r / bx;
+      t.d = div_small(t.r, bx);
       t.line = t.r - t.d * bx;
     }
     return t;
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
     for (int o = 1; o <= S; ++o) ksum += fc.t1[a][0][o] + fc.t1[a][1][o];
   double da = 0.0;
   auto points = [&](int i, const R2& x0, const R2& x1) __attribute__((always_inline)) {
-    const int y = DIM == 2 ? i / vx : 0, x = 2 * (i - y * vx);
+    const int y = DIM == 2 ? div_small(i, vx) : 0, x = 2 * (i - y * vx);
     const bool has2 = EVEN || x + 1 < bx;
     const int at = (y + SY) * W + kCo + x;
     constexpr int kRow = kCo + 6;          // columns x - 4 .. x + 5
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
   for (int k = 0; k < kPre; ++k)
     if (tid + k * nt < nvec) points(tid + k * nt, pre[k].x0, b1 ? pre[k].x1 : pre[k].x0);
   for (int i = tid + kPre * nt; i < nvec; i += nt) {
-    const int y = DIM == 2 ? i / vx : 0, x = 2 * (i - y * vx);
+    const int y = DIM == 2 ? div_small(i, vx) : 0, x = 2 * (i - y * vx);
     const bool has2 = EVEN || x + 1 < bx;
     const int64_t g = base + y * pitch + x;
     points(i, ld2<EVEN>(X0 + g, has2), ld2<EVEN>(X1 + g, has2));
@@ -295,7 +296,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
   if (tid == 0) {
     double s = 0.0;
     for (int w = 0; w < nt / 64; ++w) s += part[w];
-    q.partial[pe] += s;
+    q.partial[pe] = part0 + s;
   }
 }
 

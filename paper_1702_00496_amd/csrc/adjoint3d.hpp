@@ -56,8 +56,8 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
   const int64_t zs = p.pe_major ? static_cast<int64_t>(bx) * by : static_cast<int64_t>(p.nx) * p.ny;
   auto pe_base = [&](int e) __attribute__((always_inline)) -> int64_t {
     if (p.pe_major) return static_cast<int64_t>(e) * bx * by * bz;
-    const int qx = e % p.px, qy = (e / p.px) % p.py, qz = e / (p.px * p.py);
-    return (static_cast<int64_t>(qz) * bz * p.ny + static_cast<int64_t>(qy) * by) * p.nx + static_cast<int64_t>(qx) * bx;
+    const PePos at = pe_pos(p, e);
+    return (static_cast<int64_t>(at.z) * bz * p.ny + static_cast<int64_t>(at.y) * by) * p.nx + static_cast<int64_t>(at.x) * bx;
   };
   const Real* __restrict__ C = static_cast<const Real*>(q.levels) + (n - q.seg_start) * q.npts;
   const Real* __restrict__ Y0 = static_cast<const Real*>(q.y0);
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
   // ---- this thread's two points of a plane
   const int vx = (bx + 1) / 2;
   const bool active = tid < vx * by;
-  const int y = active ? tid / vx : 0, x = active ? 2 * (tid - y * vx) : 0;
+  const int y = active ? div_small(tid, vx) : 0, x = active ? 2 * (tid - y * vx) : 0;
   const bool has2 = EVEN || x + 1 < bx;
   const int64_t base = pe_base(pe);        // uniform
   const uint32_t col = static_cast<uint32_t>(y * pitch + x);

@@ -53,15 +53,6 @@ __device__ __forceinline__ void st2(Real* p, const Two<Real>& q, bool has2) {
   }
 }
 
-// Neighbour PE across face f = 2 axis + side (periodic).
-__device__ __forceinline__ int neighbour_of(const StepParams& p, int pid, int f) {
-  const int qx = pid % p.px, qy = (pid / p.px) % p.py, qz = pid / (p.px * p.py);
-  const int up = f & 1;
-  if (f < 2) return (up ? (qx + 1 == p.px ? 0 : qx + 1) : (qx == 0 ? p.px - 1 : qx - 1)) + p.px * (qy + p.py * qz);
-  if (f < 4) return qx + p.px * ((up ? (qy + 1 == p.py ? 0 : qy + 1) : (qy == 0 ? p.py - 1 : qy - 1)) + p.py * qz);
-  return qx + p.px * (qy + p.py * (up ? (qz + 1 == p.pz ? 0 : qz + 1) : (qz == 0 ? p.pz - 1 : qz - 1)));
-}
-
 // Delay of face f of PE pid at step n (the synchronous scheme: 0).
 __device__ __forceinline__ int delay_of(const StepParams& p, int pid, int f, int64_t n) {
   int k = 0;
@@ -127,7 +118,7 @@ __device__ __forceinline__ void face_setup(const AdjParams& q, int pe, Faces<S, 
     const int64_t nn = n + j;
     double w = 0.0;
     if (j <= (sync ? 0 : p.L + T - 2) && nn < q.nsteps) {
-      const int k = delay_of(p, neighbour_of(p, pe, f), f ^ 1, nn), m = j - k;
+      const int k = delay_of(p, neighbour(p, pe, f), f ^ 1, nn), m = j - k;
       if (m >= 0 && m < T) w = q.wt[k][m];
     }
     // the 16 lanes of a face compact their entries; j = 0 is the neighbour's
@@ -149,7 +140,7 @@ __device__ __forceinline__ void face_setup(const AdjParams& q, int pe, Faces<S, 
     }
   } else if (tid < 16 * NF + NF) {
     const int f = tid - 16 * NF;
-    fc.nbr[f] = neighbour_of(p, pe, f);
+    fc.nbr[f] = neighbour(p, pe, f);
     const int k = delay_of(p, pe, f, n);
     fc.k[f] = k;
     for (int m = 0; m < TT; ++m) {

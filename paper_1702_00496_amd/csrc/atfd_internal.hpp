@@ -49,10 +49,48 @@ __host__ __device__ inline int raw_delay(uint64_t key, int64_t n, uint32_t face,
 }
 
 // n mod m for 0 <= n, 0 < m < 2^31, in 32 bits while n fits them (a 64-bit
-// remainder takes several times as many instructions).
+// remainder takes several times as many instructions), and by the reciprocal
+// (div_small below) while it is small.
 __host__ __device__ inline int mod_small(int64_t n, int m) {
+#ifdef __HIP_DEVICE_COMPILE__
+  if ((n >> 20) == 0) {
+    const int a = static_cast<int>(n);
+    return a - static_cast<int>((static_cast<float>(a) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(m))) * m;
+  }
+#endif
   if ((n >> 31) == 0) return static_cast<int>(static_cast<uint32_t>(n) % static_cast<uint32_t>(m));
   return static_cast<int>(n % m);
+}
+
+// a / b for 0 <= a < 2^20, b >= 1: (a + 1/2) / b lies at least 1 / (2 b) from an
+// integer, and the product with the hardware reciprocal (1 ulp) is off by less
+// than 2e-7 a / b. Four instructions; the integer division takes about thirty,
+// and the index arithmetic of a sweep that is over in a few microseconds has a
+// dozen of them.
+__device__ inline int div_small(int a, int b) {
+  return static_cast<int>((static_cast<float>(a) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(b)));
+}
+// The same for any 0 <= a (a PE index).
+__device__ inline int div_index(int a, int b) { return a < (1 << 20) ? div_small(a, b) : a / b; }
+
+// Position (qx, qy, qz) of PE pid.
+struct PePos {
+  int x, y, z;
+};
+template <typename P>
+__device__ inline PePos pe_pos(const P& p, int pid) {
+  const int r = div_index(pid, p.px), z = div_index(r, p.py);
+  return {pid - r * p.px, r - z * p.py, z};
+}
+// Neighbour of PE pid across face f = 2 axis + side (periodic).
+template <typename P>
+__device__ inline int neighbour(const P& p, int pid, int f) {
+  const PePos at = pe_pos(p, pid);
+  const int px = p.px, py = p.py, pz = p.pz;
+  const int a = f >> 1, q = a == 0 ? at.x : a == 1 ? at.y : at.z, ext = a == 0 ? px : a == 1 ? py : pz;
+  const int stride = a == 0 ? 1 : a == 1 ? px : px * py;
+  const int to = (f & 1) ? (q + 1 == ext ? 0 : q + 1) : (q == 0 ? ext - 1 : q - 1);
+  return pid + (to - q) * stride;
 }
 
 // Ring slot of level n - back from r0 = n mod nslots, for 0 <= back < nslots

@@ -115,14 +115,6 @@ __device__ inline void st_run(Real* p, const Real* w) {
   }
 }
 
-__device__ inline int neighbour_pe(const StepParams& p, int pid, int f) {
-  int q[3] = {pid % p.px, (pid / p.px) % p.py, pid / (p.px * p.py)};
-  const int ext[3] = {p.px, p.py, p.pz};
-  const int a = f >> 1;
-  q[a] = (q[a] + ((f & 1) ? 1 : ext[a] - 1)) % ext[a];
-  return q[0] + p.px * (q[1] + p.py * q[2]);
-}
-
 __device__ inline int face_delay_fast(const StepParams& p, int pid, int f, int64_t n) {
   int k = 0;
   if (p.mode == AT_DELAY_RNG) {
@@ -202,7 +194,7 @@ __global__ __launch_bounds__(kB * kB / V) void at_step3d_fast_kernel(StepParams 
 
   if (tid < 6) {
     const int f = tid;
-    s_nbr[f] = neighbour_pe(p, pid, f);
+    s_nbr[f] = neighbour(p, pid, f);
     s_kpos[f] = 0;
     if (!kSync) {
       const int k = face_delay_fast(p, pid, f, n);
