@@ -40,7 +40,7 @@ struct AdjParams {
 inline int adj3d_threads(const StepParams& p) {
   const int64_t vec = static_cast<int64_t>((p.bx + 1) / 2) * p.by, items = 2 * static_cast<int64_t>(p.s) * (p.bx + p.by);
   int64_t t = vec > items ? vec : items;
-  if (t < 160) t = 160;   // the face set-up's threads
+  if (t < 192) t = 192;   // the face set-up's threads
   return static_cast<int>((t + 63) / 64 * 64);
 }
 inline size_t adj3d_lds(const StepParams& p, int w, bool m1) {
@@ -53,7 +53,7 @@ inline bool adj3d_applies(const StepParams& p, bool f64) {
 }
 // The 1-D / 2-D stage kernel (adjoint2d.hpp): the PE's plane in LDS, two points
 // and at most two pairs of them ahead per thread, at least the face set-up's
-// 160 threads.
+// 192 threads.
 inline int adj2d_threads(const StepParams& p) {
   const int64_t vec = static_cast<int64_t>((p.bx + 1) / 2) * (p.ndim == 2 ? p.by : 1);
   int64_t t = (vec + 63) / 64 * 64;

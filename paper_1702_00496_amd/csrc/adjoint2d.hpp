@@ -40,7 +40,6 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
   const int pe = blockIdx.x;
   const int64_t n = q.n;
   const bool sync = p.mode == AT_SYNC;
-  const double part0 = tid == 0 ? q.partial[pe] : 0.0;       // (ahead of its use)
   const double m0 = q.m0, m1 = q.m1;
   const int qy = div_index(pe, p.px), qx = pe - qy * p.px;
   const int64_t pitch = p.nx;
@@ -78,7 +77,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
     o.y0 = ld2<EVEN>(Y0 + g, has2);
     if (M1) o.y1 = ld2<EVEN>(Y1 + g, has2);
     o.x0 = ld2<EVEN>(X0 + g, has2);
-    if (b1) o.x1 = ld2<EVEN>(X1 + g, has2);
+    o.x1 = ld2<EVEN>(X1 + g, has2);
   };
   auto put_own = [&](const Own& o, int i) __attribute__((always_inline)) {
     const int y = DIM == 2 ? div_small(i, vx) : 0, x = 2 * (i - y * vx);
@@ -93,6 +92,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
   Own pre[kPre];
 #pragma unroll
   for (int k = 0; k < kPre; ++k) load_own(pre[k], tid + k * nt < nvec ? tid + k * nt : 0);
+  const double part0 = __hip_atomic_load(&q.partial[pe], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // zero frame of mu
   for (int i = tid; i < plane; i += nt) sY[i] = Y(0);
   face_setup<S, TT, NF, BURG>(q, pe, fc);
@@ -129,17 +129,18 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
       const int a = side ? t.d : (axis ? by : bx) - S + t.d;
       hsrc = C + pe_base(nb) + (axis ? a * pitch + t.line : t.line * pitch + a);
     } else {
-      hsrc = F + strip0(p, t.f ^ 1, nb, q.fslots, t.r);
+      hsrc = F + fc.hbase[t.f] + t.r;
     }
     Real hv[TT];
 #pragma unroll
     for (int m = 0; m < TT; ++m) hv[m] = hsrc[fc.hoff[t.f][m]];
     // entries of the g ring that reach level n
-    const Real* gsrc = G + strip0(p, t.f, pe, q.anslots, t.r);
+    // (the synchronous scheme has none: any value, dropped below)
+    const Real* gsrc = sync ? hsrc : G + fc.gbase[t.f] + t.r;
     const int cnt = fc.cnt[t.f];
     Real gv[kDrain];
 #pragma unroll
-    for (int i = 0; i < kDrain; ++i) gv[i] = sync ? Real(0) : gsrc[fc.goff[t.f][i]];
+    for (int i = 0; i < kDrain; ++i) gv[i] = gsrc[fc.goff[t.f][i]];
     // the neighbour's points next to the face, where its delay is 0
     const bool own = fc.own[t.f] != 0;
     Real oc[S], oy[S], oy1[M1 ? S : 1];
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
         mu[ia] = static_cast<double>(sY[in_at + ia * step]);
         pr[ia] = BURG ? static_cast<double>(sC[in_at + ia * step]) * mu[ia] : 0.0;
       }
-      G[strip0(p, t.f ^ 1, fc.nbr[t.f], q.anslots, t.r) + q.gslot * slot_step(p, t.f ^ 1)] =
+      G[fc.pbase[t.f] + t.r] =
           static_cast<Real>(mf * face_taps<S, TT, NF, BURG>(fc, axis, side, side ? t.d : S - 1 - t.d, mu, pr));
     }
 
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
   };
 #pragma unroll
   for (int k = 0; k < kPre; ++k)
-    if (tid + k * nt < nvec) points(tid + k * nt, pre[k].x0, b1 ? pre[k].x1 : pre[k].x0);
+    if (tid + k * nt < nvec) points(tid + k * nt, pre[k].x0, pre[k].x1);
   for (int i = tid + kPre * nt; i < nvec; i += nt) {
     const int y = DIM == 2 ? div_small(i, vx) : 0, x = 2 * (i - y * vx);
     const bool has2 = EVEN || x + 1 < bx;

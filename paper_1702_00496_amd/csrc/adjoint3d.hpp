@@ -126,15 +126,15 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
       hsrc = C + pe_base(nb) + static_cast<int64_t>(item ? ly : 0) * pitch + (item ? lx : 0);
       hzs = zs;
     } else {
-      hsrc = F + strip0(p, f ^ 1, nb, q.fslots, r);
+      hsrc = F + fc.hbase[f] + r;
       hzs = strip_zs(p, f ^ 1, q.fslots);
     }
   }
   // own entry in the g ring, and the neighbour's points next to the face (for
   // a delay of 0 there): ia = 0, 1, .. from the face
-  const Real* gsrc = G + strip0(p, f, pe, q.anslots, r);
+  const Real* gsrc = G + fc.gbase[f] + r;
   const int64_t gzs = strip_zs(p, f, q.anslots);
-  Real* gdst = G + strip0(p, f ^ 1, nb, q.anslots, r) + q.gslot * slot_step(p, f ^ 1);
+  Real* gdst = G + fc.pbase[f] + r;
   const int64_t gdzs = strip_zs(p, f ^ 1, q.anslots);
   int64_t n_at, n_step;
   {
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
   auto load_plane = [&](Ahead& a, int z) __attribute__((always_inline)) {
     const int64_t o = base + z * zs;
     a.x0 = ld2<EVEN>(X0 + o + col, has2);
-    if (b1) a.x1 = ld2<EVEN>(X1 + o + col, has2);
+    a.x1 = ld2<EVEN>(X1 + o + col, has2);
     if (any_item) {
 #pragma unroll
       for (int m = 0; m < TT; ++m) a.h[m] = hz[fc.hoff[f][m]];
@@ -225,8 +225,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
 #pragma unroll
         for (int v = 0; v < 2; ++v) g.v[v] = static_cast<Real>(mf * taps(2, up, e, mu[v], pr[v]));
         const int dd = up ? e : S - 1 - e;
-        st2<EVEN>(G + strip0(p, fz ^ 1, fc.nbr[fz], q.anslots, rz) + dd * strip_zs(p, fz ^ 1, q.anslots) +
-                      q.gslot * slot_step(p, fz ^ 1), g, has2);
+        st2<EVEN>(G + fc.pbase[fz] + rz + dd * strip_zs(p, fz ^ 1, q.anslots), g, has2);
       }
     }
 #pragma unroll
@@ -235,7 +234,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
       if (sync) {
         h = ld2<EVEN>(C + pe_base(fc.nbr[fz]) + y * pitch + x + (up ? dd : bz - S + dd) * zs, has2);
       } else {
-        const Real* src = F + strip0(p, fz ^ 1, fc.nbr[fz], q.fslots, rz) + dd * strip_zs(p, fz ^ 1, q.fslots);
+        const Real* src = F + fc.hbase[fz] + rz + dd * strip_zs(p, fz ^ 1, q.fslots);
         double s0 = 0.0, s1 = 0.0;
 #pragma unroll
         for (int m = 0; m < TT; ++m) {
@@ -288,7 +287,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
       cq[2 * S] = ld2<EVEN>(sZ + ((z + S - bz) * by + y) * bx + x, has2);
       yq[2 * S].v[0] = yq[2 * S].v[1] = Y(0);
     }
-    const R2 xv0 = nx.x0, xv1 = b1 ? nx.x1 : nx.x0;
+    const R2 xv0 = nx.x0, xv1 = nx.x1;
     if (active) {
       st2<EVEN>(Cp + at, cq[S], has2);
       st2<EVEN>(Yp + at, yq[S], has2);
@@ -390,7 +389,7 @@ __global__ __launch_bounds__(MAXT) void adj3d_kernel(AdjParams q) {
       for (int up = 0; up < 2; ++up) {
         if (up ? z < bz - S : z >= S) continue;   // uniform
         const int fz = 4 + up, dd = up ? z - (bz - S) : z, e = up ? S - 1 - dd : dd;
-        const Real* src = G + strip0(p, fz, pe, q.anslots, rz) + dd * strip_zs(p, fz, q.anslots);
+        const Real* src = G + fc.gbase[fz] + rz + dd * strip_zs(p, fz, q.anslots);
         for (int i = 0; i < fc.cnt[fz]; ++i) {
           const R2 g = ld2<EVEN>(src + fc.goff[fz][i], has2);
           in[0] += fc.dw[fz][i] * static_cast<double>(g.v[0]);

@@ -65,25 +65,32 @@ __device__ __forceinline__ int delay_of(const StepParams& p, int pid, int f, int
   return clamp_startup(k, n, p.T);
 }
 
+// A kernel parameter into a register, opaque to the compiler: a choice between
+// parameters is otherwise turned into a read at a chosen address, a memory
+// latency that the address after it waits for.
+__device__ __forceinline__ int64_t held(int64_t v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 // Strips in a ring (ring_index): element r of plane z of face f of PE e in slot
 // s lies at strip0(f, e, slots, r) + s slot_step(f) + z strip_zs(f, slots).
 __device__ __forceinline__ int64_t chunk_of(const StepParams& p, int f) {
-  // (every value is read and one selected: a read behind the select would be of
-  // a run-time address and put the kernel's arguments in scratch memory)
-  const int64_t a = p.face_chunk[0], b = p.face_chunk[2], c = p.face_chunk[4];
+  const int64_t a = held(p.face_chunk[0]), b = held(p.face_chunk[2]), c = held(p.face_chunk[4]);
   return f < 2 ? a : f < 4 ? b : c;
 }
 __device__ __forceinline__ int64_t foff_of(const StepParams& p, int f) {
-  const int64_t o0 = p.face_off[0], o1 = p.face_off[1], o2 = p.face_off[2], o3 = p.face_off[3], o4 = p.face_off[4],
-                o5 = p.face_off[5];
+  const int64_t o0 = held(p.face_off[0]), o1 = held(p.face_off[1]), o2 = held(p.face_off[2]),
+                o3 = held(p.face_off[3]), o4 = held(p.face_off[4]), o5 = held(p.face_off[5]);
   return f == 0 ? o0 : f == 1 ? o1 : f == 2 ? o2 : f == 3 ? o3 : f == 4 ? o4 : o5;
 }
 __device__ __forceinline__ int64_t strip0(const StepParams& p, int f, int e, int slots, int64_t r) {
-  return p.pe_major ? slots * foff_of(p, f) + static_cast<int64_t>(e) * slots * chunk_of(p, f) + r
-                    : foff_of(p, f) + e * chunk_of(p, f) + r;
+  const int64_t k = p.pe_major ? slots : 1;
+  return k * foff_of(p, f) + e * k * chunk_of(p, f) + r;
 }
 __device__ __forceinline__ int64_t slot_step(const StepParams& p, int f) {
-  return p.pe_major ? chunk_of(p, f) : static_cast<int64_t>(p.npe) * p.pe_block;
+  const int64_t all = static_cast<int64_t>(p.npe) * held(p.pe_block), c = chunk_of(p, f);
+  return p.pe_major ? c : all;
 }
 __device__ __forceinline__ int64_t strip_zs(const StepParams& p, int f, int slots) {
   return static_cast<int64_t>(p.npe) * chunk_of(p, f) * (p.pe_major ? slots : 1);
@@ -101,11 +108,16 @@ struct Faces {
   int64_t hoff[NF][TT], goff[NF][kMaxDrain];
   double w[NF][TT], dw[NF][kMaxDrain];
   double t1[3][2][2 * S + 1], t2[3][2][2 * S + 1];
+  // element 0 of plane 0 of: the neighbour's strip in the forward ring (slot 0),
+  // this PE's strip in the g ring (slot 0), the neighbour's in step n's slot
+  int64_t hbase[NF], gbase[NF], pbase[NF];
   int nbr[NF], k[NF], own[NF], cnt[NF];
 };
 
 // Fills fc; ends with a barrier. The draws of all faces and later steps run side
-// by side; at least 160 threads.
+// by side, each on one lane and on registers only (weights are computed, not
+// read from a table: a chain of reads at run-time addresses took longer than
+// the rest of a 2-D stage's set-up); at least 192 threads.
 template <int S, int TT, int NF, bool BURG>
 __device__ __forceinline__ void face_setup(const AdjParams& q, int pe, Faces<S, TT, NF>& fc) {
   const StepParams& p = q.sp;
@@ -113,47 +125,59 @@ __device__ __forceinline__ void face_setup(const AdjParams& q, int pe, Faces<S, 
   const int64_t n = q.n;
   const bool sync = p.mode == AT_SYNC;
   const int T = sync ? 1 : p.T;
-  if (tid < 16 * NF) {
-    const int f = tid >> 4, j = tid & 15;   // step n + j of the neighbour's face
+  if (tid < 16 * NF + NF) {
+    // lanes of the first kind: step n + j of the neighbour's face across f;
+    // of the second: step n of face f itself
+    const bool later = tid < 16 * NF;
+    const int f = later ? tid >> 4 : tid - 16 * NF, j = later ? tid & 15 : 0;
     const int64_t nn = n + j;
-    double w = 0.0;
-    if (j <= (sync ? 0 : p.L + T - 2) && nn < q.nsteps) {
-      const int k = delay_of(p, neighbour(p, pe, f), f ^ 1, nn), m = j - k;
-      if (m >= 0 && m < T) w = q.wt[k][m];
-    }
-    // the 16 lanes of a face compact their entries; j = 0 is the neighbour's
-    // own step (weight 1 where its delay is 0), the rest follow in order
-    const uint64_t live = __ballot(j > 0 && w != 0.0);
-    const uint32_t group = static_cast<uint32_t>(live >> ((tid & 63) & ~15)) & 0xffffu;
-    const uint32_t below = group & ((1u << j) - 1u);
-    const int cnt = __popc(group);
-    if (j == 0) {
-      fc.own[f] = w != 0.0;
-      fc.cnt[f] = cnt;
+    const int nb = neighbour(p, pe, f);
+    const bool use = !later || (j <= (sync ? 0 : p.L + T - 2) && nn < q.nsteps);
+    const int k = use ? delay_of(p, later ? nb : pe, later ? f ^ 1 : f, nn) : 0;
+    double wk[kMaxT];
+    level_weights(k, T, wk);
+    if (later) {
+      const int m = j - k;
+      double w = 0.0;
+#pragma unroll
+      for (int i = 0; i < kMaxT; ++i) w = m == i && i < T && use ? wk[i] : w;
+      // the 16 lanes of a face compact their entries; j = 0 is the neighbour's
+      // own step (weight 1 where its delay is 0), the rest follow in order
+      const uint64_t live = __ballot(j > 0 && w != 0.0);
+      const uint32_t group = static_cast<uint32_t>(live >> ((tid & 63) & ~15)) & 0xffffu;
+      const uint32_t below = group & ((1u << j) - 1u);
+      const int cnt = __popc(group);
+      if (j == 0) {
+        fc.own[f] = w != 0.0;
+        fc.cnt[f] = cnt;
+      } else {
+        const bool on = w != 0.0;
+        int slot = q.gslot + j;
+        while (slot >= q.anslots) slot -= q.anslots;   // (anslots = 1: the synchronous arm)
+        const int at = on ? __popc(below) : cnt + (j - 1) - __popc(below);
+        fc.dw[f][at] = w;
+        fc.goff[f][at] = on ? slot * slot_step(p, f) : 0;
+      }
     } else {
-      const bool on = w != 0.0;
-      int slot = q.gslot + j;
-      while (slot >= q.anslots) slot -= q.anslots;   // (anslots = 1: the synchronous arm)
-      const int at = on ? __popc(below) : cnt + (j - 1) - __popc(below);
-      fc.dw[f][at] = w;
-      fc.goff[f][at] = on ? slot * slot_step(p, f) : 0;
-    }
-  } else if (tid < 16 * NF + NF) {
-    const int f = tid - 16 * NF;
-    fc.nbr[f] = neighbour(p, pe, f);
-    const int k = delay_of(p, pe, f, n);
-    fc.k[f] = k;
-    for (int m = 0; m < TT; ++m) {
-      const double w = m < T ? q.wt[k][m] : 0.0;
-      fc.w[f][m] = w;
-      fc.hoff[f][m] = sync ? 0 : slot_back(q.fslot, k + (w != 0.0 ? m : 0), q.fslots) * slot_step(p, f ^ 1);
+      fc.nbr[f] = nb;
+      fc.k[f] = k;
+      const int64_t step = slot_step(p, f ^ 1);
+      fc.hbase[f] = strip0(p, f ^ 1, nb, q.fslots, 0);
+      fc.gbase[f] = strip0(p, f, pe, q.anslots, 0);
+      fc.pbase[f] = strip0(p, f ^ 1, nb, q.anslots, 0) + q.gslot * step;
+#pragma unroll
+      for (int m = 0; m < TT; ++m) {
+        const double w = m < T ? wk[m] : 0.0;
+        fc.w[f][m] = w;
+        fc.hoff[f][m] = sync ? 0 : slot_back(q.fslot, k + (w != 0.0 ? m : 0), q.fslots) * step;
+      }
     }
   }
-  if (tid >= 112 && tid < 112 + 3 * 2 * (2 * S + 1)) {
-    const int i = tid - 112, a = i / (2 * (2 * S + 1)), r = i % (2 * (2 * S + 1)), up = r / (2 * S + 1),
-              o = r % (2 * S + 1);
-    const int at = up ? S + o : S - o;
-    const bool in = o >= 1 && o <= S;
+  if (tid >= 128 && tid < 128 + 3 * 2 * (2 * S + 1)) {
+    const int e = tid - 128;
+    const int a = e / (2 * (2 * S + 1)), r = e - a * 2 * (2 * S + 1), up = r >= 2 * S + 1, o = up ? r - (2 * S + 1) : r;
+    const bool in = o <= S;
+    const int at = in ? (up ? S + o : S - o) : 0;
     fc.t1[a][up][o] = !in ? 0.0 : BURG ? p.alpha * p.c2[a][at] : p.kad[a][at];
     fc.t2[a][up][o] = !in || !BURG ? 0.0 : p.c1[a][at];
   }
