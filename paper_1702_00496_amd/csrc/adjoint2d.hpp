@@ -7,7 +7,8 @@
 // instructions a point) and the stores; two barriers besides the two of the face
 // set-up. 1024^2 in 16^2 PEs, fourth-order AB2, FP32: 15.9 us a stage; 25 us
 // with a scatter that read and wrote back T ring slots per strip value before
-// the plane could be used.
+// the plane could be used; 11.9 us with every address of the set-up and the strips
+// found in registers or LDS (14.1 with reads of parameters at run-time addresses).
 #pragma once
 
 #include "adjoint_gather.hpp"
@@ -210,6 +211,16 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
   for (int a = 0; a < DIM; ++a)
 #pragma unroll
     for (int o = 1; o <= S; ++o) ksum += fc.t1[a][0][o] + fc.t1[a][1][o];
+  // The Laplacian of FP32 fields: sums of neighbours are exact in double, and
+  // the centre enters once (lap0) instead of in every difference: two of the
+  // six to eleven FP64 operations of a neighbour pair less. FP64 fields keep
+  // the differences, which lose less to cancellation.
+  constexpr bool kSum = sizeof(Real) == 4;
+  double lap0 = 0.0;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a)
+#pragma unroll
+    for (int o = 1; o <= S; ++o) lap0 -= 2.0 * p.c2[a][S + o];
   double da = 0.0;
   auto points = [&](int i, const R2& x0, const R2& x1) __attribute__((always_inline)) {
     const int y = DIM == 2 ? div_small(i, vx) : 0, x = 2 * (i - y * vx);
@@ -235,10 +246,11 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
     // (cm, cp) and mu (ym, yp); a transposed tap from the point at -o has
     // offset +o and the other way round
     auto pair = [&](int a, int o, int v, Real cm_, Real cp_, Y ym_, Y yp_) __attribute__((always_inline)) {
-      const double cj = static_cast<double>(crow[kCo + v]);
+      [[maybe_unused]] const double cj = static_cast<double>(crow[kCo + v]);
       const double cm = static_cast<double>(cm_), cp = static_cast<double>(cp_);
       const double ym = static_cast<double>(ym_), yp = static_cast<double>(yp_);
-      lap[v] += p.c2[a][S + o] * ((cm - cj) + (cp - cj));
+      if constexpr (kSum) lap[v] += p.c2[a][S + o] * (cm + cp);
+      else lap[v] += p.c2[a][S + o] * ((cm - cj) + (cp - cj));
       if constexpr (BURG) {
         grad[v] += p.c1[a][S + o] * (cp - cm);
         acc2[v] += p.c2[a][S + o] * (ym + yp);
@@ -275,6 +287,7 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
       const double sum = (BURG ? p.alpha * acc2[v] + acc[v] : acc[v]) - (ksum + (BURG ? grad[v] : 0.0)) * yv;
       res.v[v] = static_cast<Real>(q.b0 * static_cast<double>(x0.v[v]) + q.b1 * static_cast<double>(x1.v[v]) +
                                    (mf * sum + in));
+      if constexpr (kSum) lap[v] += lap0 * static_cast<double>(crow[kCo + v]);
       if (v == 0 || has2) da += mf * yv * lap[v];
     }
     st2<EVEN>(out + base + y * pitch + x, res, has2);
