@@ -747,7 +747,10 @@ struct Sweep {
   __device__ __forceinline__ void compute_plane_vec(int z, const Pre& pre, const Vec4<Real>* hist = nullptr) {
     static_assert(VEC, "vector layout only");
     using Q = Vec4<Real>;
-    constexpr int QB = 2;   // quads per thread whose loads are issued together
+    // quads per thread whose history loads are issued together; stages without
+    // history take one at a time, which leaves registers for eight waves per SIMD
+    // (non-uniform 4096^2 FP32: 75 -> 62 registers, 38.9 -> 36.2 us per step)
+    constexpr int QB = KIND == kVEuler || KIND == kVRk1 ? 1 : 2;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int bx = p.bx, by = p.by, bz = p.bz;
     const int rows = DIM >= 2 ? rows_sl : 1;   // the workgroup's y-slice
@@ -1154,13 +1157,16 @@ __global__ __launch_bounds__(PIPE ? kMaxVec3Threads : kMaxSweepThreads) void at_
   constexpr int SD = strip_depth<S, SP>();
   extern __shared__ __align__(16) unsigned char smem_raw[];
   Real* lds = reinterpret_cast<Real*>(smem_raw);
-  __shared__ double s_w[6 * kMaxT];
-  __shared__ int s_slot[6 * kMaxT];
-  __shared__ int s_nbr[6];
-  __shared__ int s_kpos[6];
-  __shared__ double s_nu[SP == 3 ? 6 * kNuTaps : 1];
-  __shared__ Real s_nur[SP == 3 ? 6 * kNuTaps : 1];
-  __shared__ Real s_dt[SP != 0 ? 6 * kDtaps : 1];
+  // (no larger than the scheme and the dimension need: eight workgroups of the
+  // non-uniform 2-D sweep in 64 x 64 FP32 PEs fill a CU's LDS to the byte)
+  constexpr int NF = 2 * DIM;
+  __shared__ double s_w[SP == 3 ? 1 : NF * kMaxT];
+  __shared__ int s_slot[NF * kMaxT];
+  __shared__ int s_nbr[NF];
+  __shared__ int s_kpos[NF];
+  __shared__ double s_nu[SP == 3 ? NF * kNuTaps : 1];
+  __shared__ Real s_nur[SP == 3 ? NF * kNuTaps : 1];
+  __shared__ Real s_dt[SP != 0 ? NF * kDtaps : 1];
 
   // (1-D, 2-D: a load past the scalar cache, so that the parameters do not wait
   // for it)
