@@ -1,14 +1,14 @@
 // Stage of the reversed step for 1-D and 2-D problems: one workgroup per PE,
 // the PE's plane in LDS (adjoint_gather.hpp: how the strips are done).
 //
-// What bounds it: latency. The plane is read and computed once, so a stage is
-// the launch, one round of loads (the plane's own values, issued before the
-// delays are drawn), one round of strip loads, the arithmetic (about 60 FP64
-// instructions a point) and the stores; two barriers besides the two of the face
-// set-up. 1024^2 in 16^2 PEs, fourth-order AB2, FP32: 15.9 us a stage; 25 us
-// with a scatter that read and wrote back T ring slots per strip value before
-// the plane could be used; 11.9 us with every address of the set-up and the strips
-// found in registers or LDS (14.1 with reads of parameters at run-time addresses).
+// What bounds it: latency, then FP64 issue. The plane is read and computed once,
+// so a stage is the launch, one round of loads (the plane's own values, issued
+// before the delays are drawn), one round of strip loads, the arithmetic (about
+// 45 FP64 instructions a point, two fifths of the time) and the stores; two
+// barriers besides that of the face set-up. 1024^2 in 16^2 PEs, fourth-order
+// AB2, FP32: 11.2 us a stage; 14.1 us while parameters were read at run-time
+// addresses and every drained value had its own wait; 25 us with a scatter that
+// read and wrote back T ring slots per strip value before the plane could be used.
 #pragma once
 
 #include "adjoint_gather.hpp"

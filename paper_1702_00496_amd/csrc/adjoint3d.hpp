@@ -1,16 +1,16 @@
 // Stage of the reversed step for 3-D problems: one workgroup per PE, two x points per thread, sweeping
 // the PE's z-planes (adjoint_gather.hpp: how the strips are done).
 //
-// What bounds it: memory (the stage fields read once, about T + 1 ring values
-// per strip entry), then FP64 issue: per tap pair one fused multiply-add each
-// for Laplacian, gradient and the two transposed sums (even and odd taps), on
-// products c mu formed once per neighbour. 256^3 in 8^3 PEs, sixth-order
-// Burgers, FP32: 272 us a stage (about 660 MB needed, 130 us at the rate of a
-// large copy; two workgroup rounds of 8 waves a CU, at 211 registers); the
-// separate strip kernel (read-modify-write of T ring slots from gathers strided
-// by the row) and stage kernel (taps and products per tap through LDS) took
-// 453 + 570 us. 192^3 in 6^3 PEs, fourth-order AB2, 16 steps with the forward
-// runs: 6.2 -> 2.4 ms.
+// What bounds it: FP64 issue and latency at two waves per SIMD. A neighbour pair
+// takes up to nine FP64 operations and four conversions (Laplacian, gradient
+// and the transposed sums, even and odd taps together). 256^3 in 8^3 PEs,
+// sixth-order Burgers, FP32: 217 us a stage alone on the chip, the vector
+// units busy 45 % of it (two rounds of 8 waves a CU, at 185 registers); 185 MiB
+// are read and 80 MiB written, 53 us at the rate of a large copy. The separate
+// strip kernel (read-modify-write of T ring slots from gathers strided by the
+// row) and stage kernel (taps and products per tap through LDS) took 453 + 570
+// us. 192^3 in 6^3 PEs, fourth-order AB2, 16 steps with the forward runs: 6.2 ->
+// 2.4 ms. Two workgroups a CU at 128 registers spill: twice as slow.
 
 #pragma once
 
