@@ -82,15 +82,18 @@ __device__ inline PePos pe_pos(const P& p, int pid) {
   const int r = div_index(pid, p.px), z = div_index(r, p.py);
   return {pid - r * p.px, r - z * p.py, z};
 }
-// Neighbour of PE pid across face f = 2 axis + side (periodic).
+// Neighbour of PE pid, at position at, across face f = 2 axis + side (periodic).
 template <typename P>
-__device__ inline int neighbour(const P& p, int pid, int f) {
-  const PePos at = pe_pos(p, pid);
+__device__ inline int neighbour(const P& p, PePos at, int pid, int f) {
   const int px = p.px, py = p.py, pz = p.pz;
   const int a = f >> 1, q = a == 0 ? at.x : a == 1 ? at.y : at.z, ext = a == 0 ? px : a == 1 ? py : pz;
   const int stride = a == 0 ? 1 : a == 1 ? px : px * py;
   const int to = (f & 1) ? (q + 1 == ext ? 0 : q + 1) : (q == 0 ? ext - 1 : q - 1);
   return pid + (to - q) * stride;
+}
+template <typename P>
+__device__ inline int neighbour(const P& p, int pid, int f) {
+  return neighbour(p, pe_pos(p, pid), pid, f);
 }
 
 // Ring slot of level n - back from r0 = n mod nslots, for 0 <= back < nslots

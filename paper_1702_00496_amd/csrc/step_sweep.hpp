@@ -141,6 +141,8 @@ struct Sweep {
     set_step(n_);
   }
 
+  __device__ PePos pos() const { return {qx, qy, qz}; }
+
   __device__ void set_step(int64_t n_) {
     n = n_;
     r0 = p.mode != AT_SYNC ? mod_small(n, p.nslots) : 0;
@@ -268,7 +270,13 @@ struct Sweep {
 #pragma unroll
     for (int m = 0; m < kMaxT; ++m) {
       const int sl = lev_slot[f * kMaxT + m];
-      if (m < p.T && sl >= 0) acc += w[f * kMaxT + m] * static_cast<double>(v[m]);
+      if constexpr (DIM < 3) {
+        // a select: no branch between the loads' waits
+        const double with = acc + w[f * kMaxT + m] * static_cast<double>(v[m]);
+        acc = m < p.T && sl >= 0 ? with : acc;
+      } else if (m < p.T && sl >= 0) {
+        acc += w[f * kMaxT + m] * static_cast<double>(v[m]);
+      }
     }
     return static_cast<Real>(acc);
   }
@@ -346,14 +354,47 @@ struct Sweep {
     }
   };
 
-  // skip: the centre values of the thread that pre_commit has written; first:
-  // its first halo item, if found before.
-  __device__ __forceinline__ void load_plane(int zz, int parts = kPlaneCentre | kPlaneHalos, int skip = 0,
-                                             const HaloItem* first = nullptr) {
+  // Where a halo item of a 1-D or 2-D PE lies, all but the step's ring slots: its
+  // element of slot 0 of the neighbour's strip (synchronous: of the field).
+  __device__ int64_t halo_base(const HaloItem& hi) const {
+    if (p.mode == AT_SYNC) return gidx(hi.gx, hi.gy, 0);
+    return ring_off(0, neighbour(p, pos(), pid, hi.f), hi.f ^ 1, 0, hi.r);
+  }
+  // The halo frame of a 1-D or 2-D PE; first: the thread's first item and its
+  // place, found while the step number arrived (non-uniform 4096^2 FP32 36.2 ->
+  // 35.4 us per step).
+  __device__ __forceinline__ void load_halos(const HaloItem& first, int64_t first_base, int64_t slot_stride) {
+    const int nh = 2 * SD * rows_sl + (DIM >= 2 ? 2 * SD * p.bx : 0);
+    const int tid = threadIdx.x, nt = blockDim.x;
+    auto put = [&](const HaloItem& hi, int64_t base) __attribute__((always_inline)) {
+      Real v[kMaxT];
+      if (p.mode == AT_SYNC) {
+        v[0] = centre[base];
+      } else if constexpr (SP == 3) {
+        v[0] = ring_rd[base + lev_slot[hi.f * kMaxT + hi.m] * slot_stride];
+      } else {
+        const int s0 = lev_slot[hi.f * kMaxT] > 0 ? lev_slot[hi.f * kMaxT] : 0;
+#pragma unroll
+        for (int m = 0; m < kMaxT; ++m) {
+          const int sl = lev_slot[hi.f * kMaxT + m];
+          v[m] = ring_rd[base + (m < p.T && sl >= 0 ? sl : s0) * slot_stride];
+        }
+      }
+      lds[hi.at] = halo_sum(hi.f, v);
+    };
+    if (tid < nh) put(first, first_base);
+    for (int h = tid + nt; h < nh; h += nt) {
+      const HaloItem hi = halo_item(h);
+      put(hi, halo_base(hi));
+    }
+  }
+
+  // skip: the centre values of the thread that pre_commit has written.
+  __device__ __forceinline__ void load_plane(int zz, int parts = kPlaneCentre | kPlaneHalos, int skip = 0) {
     Real* P = lds + slot_of<DIM, SD>(zz) * plane;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int bx = p.bx, by = rows_sl, bz = p.bz;
-    if (zz >= 0 && zz < bz) {
+    if (DIM < 3 || (zz >= 0 && zz < bz)) {
       const int gz = z0 + zz;
       // kBatch loads per thread are issued before any LDS write, from
       // clamped (in-range) addresses
@@ -401,7 +442,7 @@ struct Sweep {
       // x halos and y halos in one pass, so that their loads overlap
       const int nh = (parts & kPlaneHalos) ? 2 * SD * by + (DIM >= 2 ? 2 * SD * bx : 0) : 0;
       for (int h = tid; h < nh; h += nt) {
-        const HaloItem hi = first != nullptr && h == tid ? *first : halo_item(h);
+        const HaloItem hi = halo_item(h);
         P[hi.at] = hi.inner ? centre[gidx(hi.gx, hi.gy, gz)] : halo(hi.f, zz, hi.r, hi.m, hi.gx, hi.gy, gz);
       }
     } else {
@@ -749,7 +790,7 @@ struct Sweep {
     using Q = Vec4<Real>;
     // quads per thread whose history loads are issued together; stages without
     // history take one at a time, which leaves registers for eight waves per SIMD
-    // (non-uniform 4096^2 FP32: 75 -> 62 registers, 38.9 -> 36.2 us per step)
+    // (non-uniform 4096^2 FP32: 75 -> 64 registers, 38.9 -> 36.2 us per step)
     constexpr int QB = KIND == kVEuler || KIND == kVRk1 ? 1 : 2;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int bx = p.bx, by = p.by, bz = p.bz;
@@ -1178,7 +1219,7 @@ __global__ __launch_bounds__(PIPE ? kMaxVec3Threads : kMaxSweepThreads) void at_
   Sweep<Real, DIM, S, SP, VEC> sw(p, lds, n, s_w, s_slot, s_nbr, s_kpos, s_nur, s_dt);
   // neighbours of the 2 * DIM faces, and their delays and level weights at
   // step n
-  if (tid < 2 * DIM) s_nbr[tid] = neighbour(p, pid, tid);
+  if (tid < 2 * DIM) s_nbr[tid] = neighbour(p, sw.pos(), pid, tid);
   auto faces = [&]() {
     if (tid >= 2 * DIM) return;
     const int f = tid, r0 = sw.r0;
@@ -1308,13 +1349,14 @@ __global__ __launch_bounds__(PIPE ? kMaxVec3Threads : kMaxSweepThreads) void at_
     typename SW::Pre pre;
     sw.pre_load(rk2 ? us : un, rk2 ? un : ab ? f0 : nullptr, ab3 ? f1 : nullptr, pre);
     const typename SW::HaloItem h0 = sw.halo_item(tid);
+    const int64_t h0_base = sw.halo_base(h0), slot_stride = static_cast<int64_t>(p.npe) * p.pe_block;
     n = uniform(nv) + p.step_off;
     sw.set_step(n);
     faces();
     sw.pre_commit(pre);
     sw.load_plane(0, kPlaneCentre, SW::kPre);
     __syncthreads();
-    sw.load_plane(0, kPlaneHalos, 0, &h0);
+    sw.load_halos(h0, h0_base, slot_stride);
     __syncthreads();
     if constexpr (VEC)
       sw.template compute_plane_vec<KIND, EQ>(0, pre);
