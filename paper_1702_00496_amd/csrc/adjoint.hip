@@ -17,11 +17,13 @@
 // where A^l gathers, at the edge strips that neighbours read, K_{i,a,o} c_m(k)
 // mu_i of every later step with n - k - m = l: an adjoint ring of the forward
 // ring's shape, filled in gather form (one thread per strip value: the strip
-// kernel) and drained when the sweep reaches level l. Most problems take the
-// stage kernels of adjoint2d.hpp and adjoint3d.hpp instead, which keep the sums
-// over mu themselves and combine them when level l is reached; the kernels here
-// serve the shapes those do not take (3-D cross-sections of more than 2048
-// points, planes too large for LDS). The alpha-gradient adds
+// kernel) and drained when the sweep reaches level l. 1-D, 2-D and most 3-D
+// problems take the stage kernels of adjoint2d.hpp and adjoint3d.hpp instead,
+// which keep the sums over mu themselves and combine them when level l is
+// reached; the kernels here, whose grid is the points and strip values, serve
+// 3-D problems of few, deep or very small PEs (adj3d_pays) and the shapes the
+// others cannot hold (3-D cross-sections of more than 2048 points, planes too
+// large for LDS). They take both field layouts. The alpha-gradient adds
 // <mu, dF/dalpha> = <mu, AT Laplacian of c>.
 //
 // Euler/AB2 (Sec. 4.1 eqs. time_disc, time_ab2): one stage per step, mu =
@@ -41,29 +43,40 @@ namespace {
 constexpr int kAdjThreads = 256;
 
 struct Pt {
-  int x, y, z;      // global coordinates
   int pe;           // PE id
   int l[3];         // coordinates inside the PE
 };
 
-// (fields below 2^31 points: the host checks)
+// Field index of the point at PE coordinates (x, y, z) of PE pe, in either
+// field layout.
+__device__ inline int64_t cell(const StepParams& p, int pe, int x, int y, int z) {
+  if (p.pe_major) return ((static_cast<int64_t>(pe) * p.bz + z) * p.by + y) * p.bx + x;
+  const int r = pe / p.px, qz = r / p.py, qx = pe - r * p.px, qy = r - qz * p.py;
+  return ((static_cast<int64_t>(qz) * p.bz + z) * p.ny + static_cast<int64_t>(qy) * p.by + y) * p.nx +
+         static_cast<int64_t>(qx) * p.bx + x;
+}
+
+// The point at field index g (fields below 2^31 points: the host checks).
 __device__ inline Pt point_of(const StepParams& p, int64_t g64) {
   Pt r;
   const uint32_t g = static_cast<uint32_t>(g64);
-  const uint32_t row = g / static_cast<uint32_t>(p.nx);
-  r.x = static_cast<int>(g - row * static_cast<uint32_t>(p.nx));
-  r.z = static_cast<int>(row / static_cast<uint32_t>(p.ny));
-  r.y = static_cast<int>(row - static_cast<uint32_t>(r.z) * static_cast<uint32_t>(p.ny));
-  const int qx = r.x / p.bx, qy = r.y / p.by, qz = r.z / p.bz;
-  r.l[0] = r.x - qx * p.bx;
-  r.l[1] = r.y - qy * p.by;
-  r.l[2] = r.z - qz * p.bz;
+  const uint32_t nx = static_cast<uint32_t>(p.pe_major ? p.bx : p.nx), ny = static_cast<uint32_t>(p.pe_major ? p.by : p.ny);
+  const uint32_t row = g / nx;
+  const int x = static_cast<int>(g - row * nx), z = static_cast<int>(row / ny);
+  const int y = static_cast<int>(row - static_cast<uint32_t>(z) * ny);
+  const int qz = z / p.bz;
+  r.l[2] = z - qz * p.bz;
+  if (p.pe_major) {   // z counts planes through all PEs
+    r.l[0] = x;
+    r.l[1] = y;
+    r.pe = qz;
+    return r;
+  }
+  const int qx = x / p.bx, qy = y / p.by;
+  r.l[0] = x - qx * p.bx;
+  r.l[1] = y - qy * p.by;
   r.pe = qx + p.px * (qy + p.py * qz);
   return r;
-}
-
-__device__ inline int64_t gindex(const StepParams& p, int x, int y, int z) {
-  return (static_cast<int64_t>(z) * p.ny + y) * p.nx + x;
 }
 
 __device__ inline int edge_of(const StepParams& p, int a) { return a == 0 ? p.bx : a == 1 ? p.by : p.bz; }
@@ -90,16 +103,17 @@ __device__ inline int64_t strip_elem(const StepParams& p, int F, const int* l, i
   return (static_cast<int64_t>(d) * p.by + l[1]) * p.bx + l[0];
 }
 
-// Ring index of the strip value of face F at PE coordinates l (in that strip):
-// x faces plane z, [y][d]; y faces plane z, [d][x]; z faces plane d, [y][x].
-__device__ inline int64_t ring_at_pt(const StepParams& p, int slot, int pe, int F, const int* l, int S) {
+// Index, in a ring of ns slots, of the strip value of face F at PE coordinates l
+// (in that strip): x faces plane z, [y][d]; y faces plane z, [d][x]; z faces
+// plane d, [y][x].
+__device__ inline int64_t ring_at_pt(const StepParams& p, int ns, int slot, int pe, int F, const int* l, int S) {
   const int a = F >> 1;
   const int b = edge_of(p, a);
   const int la = sel3(a, l[0], l[1], l[2]);
   const int d = (F & 1) ? la - (b - S) : la;
-  if (a == 0) return ring_index(p, slot, pe, F, l[2], static_cast<int64_t>(l[1]) * S + d);
-  if (a == 1) return ring_index(p, slot, pe, F, l[2], static_cast<int64_t>(d) * p.bx + l[0]);
-  return ring_index(p, slot, pe, F, d, static_cast<int64_t>(l[1]) * p.bx + l[0]);
+  if (a == 0) return ring_index(p, ns, slot, pe, F, l[2], static_cast<int64_t>(l[1]) * S + d);
+  if (a == 1) return ring_index(p, ns, slot, pe, F, l[2], static_cast<int64_t>(d) * p.bx + l[0]);
+  return ring_index(p, ns, slot, pe, F, d, static_cast<int64_t>(l[1]) * p.bx + l[0]);
 }
 
 // Strip value t of the per-PE numbering used by the strip kernel
@@ -206,8 +220,6 @@ __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const
   const int cf = F ^ 1;
   // coordinate of the strip value in the consumer's frame
   const int jp = (F & 1) ? d - S : b + d;
-  const int cq[3] = {cons % p.px, (cons / p.px) % p.py, cons / (p.px * p.py)};
-  const int org[3] = {cq[0] * p.bx, cq[1] * p.by, cq[2] * p.bz};
   // taps from consumer points outside the consumer PE are dropped by a
   // select after unconditional loads from a clamped (in-PE) point, so that
   // every load of the element is in flight together
@@ -217,9 +229,9 @@ __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const
     if (o == 0) continue;
     const int ia = jp - o;
     const bool valid = ia >= 0 && ia < b;
-    int c[3] = {org[0] + l[0], org[1] + l[1], org[2] + l[2]};
-    set3(c, a, sel3(a, org[0], org[1], org[2]) + min(max(ia, 0), b - 1));
-    const int64_t gi = gindex(p, c[0], c[1], c[2]);
+    int c[3] = {l[0], l[1], l[2]};
+    set3(c, a, min(max(ia, 0), b - 1));
+    const int64_t gi = cell(p, cons, c[0], c[1], c[2]);
     const double ci = q.burgers ? centre_at<Real>(q, gi) : 0.0;   // Burgers taps only
     const double t = tap_k(q, a, o, ci) * mu_at<Real>(q, gi);
     g += valid ? t : 0.0;
@@ -236,7 +248,7 @@ __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const
     if (m >= T) break;
     // level n - k - m (before t = 0 only where w[m] = 0: any slot is read)
     const int slot = slot_back(q.gslot, k + m, q.anslots);
-    dst[m] = aring + ring_at_pt(p, slot, pe, F, lsF, S);
+    dst[m] = aring + ring_at_pt(p, q.anslots, slot, pe, F, lsF, S);
     old[m] = static_cast<double>(*dst[m]);
   }
 #pragma unroll
@@ -259,12 +271,10 @@ __device__ inline Real halo_value(const AdjParams& q, const StripPt& sp, const d
   const int b = edge_of(p, a);
   set3(ls, a, (pf & 1) ? b - S + d : d);
   const int src = nbr_pe(p, pe, f);
-  const int sq[3] = {src % p.px, (src / p.px) % p.py, src / (p.px * p.py)};
-  const int gx = sq[0] * p.bx + ls[0], gy = sq[1] * p.by + ls[1], gz = sq[2] * p.bz + ls[2];
   const int k = adj_delay(p, pe, f, q.n);
   const double* w = wt[k];
   if (p.mode == AT_SYNC)   // level n, always stored
-    return static_cast<const Real*>(q.levels)[(q.n - q.seg_start) * q.npts + gindex(p, gx, gy, gz)];
+    return static_cast<const Real*>(q.levels)[(q.n - q.seg_start) * q.npts + cell(p, src, ls[0], ls[1], ls[2])];
   // all kMaxT levels are loaded unconditionally (a level m >= T repeats
   // level T - 1 and is dropped below, like a level of weight zero), so the
   // loads overlap
@@ -272,7 +282,7 @@ __device__ inline Real halo_value(const AdjParams& q, const StripPt& sp, const d
   double lv[kMaxT];
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m)
-    lv[m] = static_cast<double>(R[ring_at_pt(p, slot_back(q.fslot, k + min(m, T - 1), q.fslots), src, pf, ls, S)]);
+    lv[m] = static_cast<double>(R[ring_at_pt(p, q.fslots, slot_back(q.fslot, k + min(m, T - 1), q.fslots), src, pf, ls, S)]);
   double v = 0.0;
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m)
@@ -318,7 +328,9 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
   const Real* __restrict__ hb = static_cast<const Real*>(q.hbuf);
   Real* __restrict__ aring = static_cast<Real*>(q.aring);
   const int slot_n = q.gslot;
-  const int64_t st[3] = {1, p.nx, static_cast<int64_t>(p.nx) * p.ny};
+  // steps along the axes inside a PE
+  const int64_t st[3] = {1, p.pe_major ? p.bx : p.nx,
+                         p.pe_major ? static_cast<int64_t>(p.bx) * p.by : static_cast<int64_t>(p.nx) * p.ny};
   double da = 0.0;
   for (int64_t g = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; g < q.npts;
        g += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -367,7 +379,7 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
         const bool in = side ? j.l[a] >= b - S : j.l[a] < S;
         int ls[3] = {j.l[0], j.l[1], j.l[2]};
         if (!in) ls[a] = side ? b - S : 0;
-        Real* src = aring + ring_at_pt(p, slot_n, j.pe, 2 * a + side, ls, S);
+        Real* src = aring + ring_at_pt(p, q.anslots, slot_n, j.pe, 2 * a + side, ls, S);
         const double r = static_cast<double>(*src);
         acc += in ? r : 0.0;
         rsrc[2 * a + side] = src;
@@ -445,7 +457,6 @@ hipError_t launch_adj_step(const AdjParams& q, bool f64, hipStream_t st) {
     if (q.sp.ndim == 1) return f64 ? launch_adj1d_f64(q, st) : launch_adj1d_f32(q, st);
     return f64 ? launch_adj2d_f64(q, st) : launch_adj2d_f32(q, st);
   }
-  if (q.sp.pe_major) return hipErrorInvalidValue;   // the kernels below take [z][y][x] fields
   const int64_t strips = static_cast<int64_t>(q.sp.npe) * q.sp.pe_block;
   const int64_t sb = (strips + kAdjThreads - 1) / kAdjThreads;
   const int sblocks = static_cast<int>(sb < kAdjBlocks ? (sb > 0 ? sb : 1) : kAdjBlocks);

@@ -1,5 +1,6 @@
-// Stage of the reversed step for 3-D problems: one workgroup per PE, two x points per thread, sweeping
-// the PE's z-planes (adjoint_gather.hpp: how the strips are done).
+// Stage of the reversed step for 3-D problems whose PEs fill the chip
+// (adj3d_pays): one workgroup per PE, two x points per thread, sweeping the
+// PE's z-planes (adjoint_gather.hpp: how the strips are done).
 //
 // What bounds it: FP64 issue and latency at two waves per SIMD. A neighbour pair
 // takes up to nine FP64 operations and four conversions (Laplacian, gradient
@@ -10,7 +11,9 @@
 // strip kernel (read-modify-write of T ring slots from gathers strided by the
 // row) and stage kernel (taps and products per tap through LDS) took 453 + 570
 // us. 192^3 in 6^3 PEs, fourth-order AB2, 16 steps with the forward runs: 6.2 ->
-// 2.4 ms. Two workgroups a CU at 128 registers spill: twice as slow.
+// 2.4 ms. Two workgroups a CU at 128 registers spill: twice as slow (the forms
+// of 1024 threads, which have no more, run at a third to a half of the rate of
+// the others).
 
 #pragma once
 
@@ -503,7 +506,7 @@ template <typename Real>
 hipError_t launch_adj3d(const AdjParams& q, hipStream_t st) {
   using namespace adj3d;
   const StepParams& p = q.sp;
-  if (!adj3d_applies(p, sizeof(Real) == 8) || p.bz < 2 * p.s || q.anslots < 1) return hipErrorInvalidValue;
+  if (!adj3d_fits(p, sizeof(Real) == 8) || p.bz < 2 * p.s || q.anslots < 1) return hipErrorInvalidValue;
   const int threads = adj3d_threads(p);
   const size_t lds = adj3d_lds(p, sizeof(Real), q.m1 != 0.0);
   switch (p.s) {

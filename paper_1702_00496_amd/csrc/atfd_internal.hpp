@@ -271,23 +271,18 @@ __host__ __device__ inline int64_t pe_major_offset(int x, int y, int z, int bz, 
 //   [face][plane][pe][slot][chunk],
 // so the T delayed levels a halo value combines (consecutive slots) are one
 // contiguous run rather than T runs a slot apart; face f starts at nslots x
-// face_off[f]. A ring of one slot (the adjoint ring of the synchronous arm,
-// whose forward ring has none) takes nslots = 1.
-__host__ __device__ inline int64_t ring_index(const StepParams& p, int slot, int pe, int f, int64_t plane,
+// face_off[f]. The first form is for a ring of the layout with ns slots (the
+// rings of an adjoint's segment, the adjoint ring), the second for the
+// context's own.
+__host__ __device__ inline int64_t ring_index(const StepParams& p, int64_t ns, int slot, int pe, int f, int64_t plane,
                                               int64_t r) {
-  if (p.pe_major) {
-    const int64_t ns = p.nslots > 0 ? p.nslots : 1;
-    return ns * p.face_off[f] + ((plane * p.npe + pe) * ns + slot) * p.face_chunk[f] + r;
-  }
+  if (p.pe_major) return ns * p.face_off[f] + ((plane * p.npe + pe) * ns + slot) * p.face_chunk[f] + r;
   return static_cast<int64_t>(slot) * p.npe * p.pe_block + p.face_off[f] +
          (plane * p.npe + pe) * p.face_chunk[f] + r;
 }
 
-// Same, for element q of the PE's strip counted plane after plane.
-__host__ __device__ inline int64_t ring_index_q(const StepParams& p, int slot, int pe, int f, int64_t q) {
-  const int64_t c = p.face_chunk[f];
-  const int64_t plane = q / c;
-  return ring_index(p, slot, pe, f, plane, q - plane * c);
+__host__ __device__ inline int64_t ring_index(const StepParams& p, int slot, int pe, int f, int64_t plane, int64_t r) {
+  return ring_index(p, p.nslots, slot, pe, f, plane, r);
 }
 
 struct NormParams {
