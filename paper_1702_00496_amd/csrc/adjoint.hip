@@ -211,7 +211,7 @@ __device__ inline double tap_k(const AdjParams& q, int a, int o, double ci) {
 template <typename Real, int S>
 __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const double (*wt)[kMaxT]) {
   const StepParams& p = q.sp;
-  Real* aring = static_cast<Real*>(q.aring);
+  double* aring = static_cast<double*>(q.aring);
   const int pe = sp.pe, F = sp.F, d = sp.d, a = F >> 1;
   const int* l = sp.l;
   const int b = edge_of(p, a);
@@ -241,7 +241,7 @@ __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const
   const int T = adj_levels(p);
   int lsF[3] = {l[0], l[1], l[2]};   // the strip value's PE coordinates
   set3(lsF, a, (F & 1) ? b - S + d : d);
-  Real* dst[kMaxT];
+  double* dst[kMaxT];
   double old[kMaxT];
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m) {
@@ -249,12 +249,12 @@ __device__ inline void scatter_elem(const AdjParams& q, const StripPt& sp, const
     // level n - k - m (before t = 0 only where w[m] = 0: any slot is read)
     const int slot = slot_back(q.gslot, k + m, q.anslots);
     dst[m] = aring + ring_at_pt(p, q.anslots, slot, pe, F, lsF, S);
-    old[m] = static_cast<double>(*dst[m]);
+    old[m] = *dst[m];
   }
 #pragma unroll
   for (int m = 0; m < kMaxT; ++m) {
     if (m >= T) break;
-    if (w[m] != 0.0) *dst[m] = static_cast<Real>(old[m] + w[m] * g);
+    if (w[m] != 0.0) *dst[m] = old[m] + w[m] * g;
   }
 }
 
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
   const Real* __restrict__ x1 = static_cast<const Real*>(q.b1 != 0.0 ? q.x1 : q.x0);
   const Real* __restrict__ C = static_cast<const Real*>(q.levels) + (q.n - q.seg_start) * q.npts;
   const Real* __restrict__ hb = static_cast<const Real*>(q.hbuf);
-  Real* __restrict__ aring = static_cast<Real*>(q.aring);
+  double* __restrict__ aring = static_cast<double*>(q.aring);
   const int slot_n = q.gslot;
   // steps along the axes inside a PE
   const int64_t st[3] = {1, p.pe_major ? p.bx : p.nx,
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
     const Real* hpe = hb + static_cast<int64_t>(j.pe) * p.pe_block;
     // adjoint-ring entries of the strips j belongs to: every load of the
     // point is issued before the entries are cleared at the end
-    Real* rsrc[2 * DIM];
+    double* rsrc[2 * DIM];
     bool rin[2 * DIM];
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
@@ -379,8 +379,8 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
         const bool in = side ? j.l[a] >= b - S : j.l[a] < S;
         int ls[3] = {j.l[0], j.l[1], j.l[2]};
         if (!in) ls[a] = side ? b - S : 0;
-        Real* src = aring + ring_at_pt(p, q.anslots, slot_n, j.pe, 2 * a + side, ls, S);
-        const double r = static_cast<double>(*src);
+        double* src = aring + ring_at_pt(p, q.anslots, slot_n, j.pe, 2 * a + side, ls, S);
+        const double r = *src;
         acc += in ? r : 0.0;
         rsrc[2 * a + side] = src;
         rin[2 * a + side] = in;
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kAdjThreads) void adj_lambda_kernel(AdjParams q) {
     }
 #pragma unroll
     for (int f = 0; f < 2 * DIM; ++f)
-      if (rin[f]) *rsrc[f] = Real(0);
+      if (rin[f]) *rsrc[f] = 0.0;
     // D_j mu_j with D_j = -sum K (- G_j for Burgers)
     acc += (-sumk - (q.burgers ? grad : 0.0)) * mu;
     out[g] = static_cast<Real>(acc);

@@ -29,7 +29,8 @@ struct AdjParams {
   int64_t nsteps;                  // steps of the whole run
   void* hbuf;                      // forward halo values of this stage [pe][face strips]
   int64_t pfo[6];                  // offset of face f's strip inside one PE's pe_block values
-  void* aring;                     // adjoint ring of the stage field, anslots slots (3-D kernel: the g ring)
+  void* aring;                     // anslots slots: the stage field's g ring (gathering kernels), or its adjoint
+                                   // ring, in double (strip and stage kernels)
   int anslots, gslot;              // (gslot = n mod anslots)
   double* partial;                 // [adj_partials] alpha-gradient partial sums
   double wt[kMaxL][kMaxT];         // level weights c_m(k) of every delay k < L (host-computed)

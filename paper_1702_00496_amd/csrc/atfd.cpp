@@ -893,7 +893,7 @@ AdjLayout adj_layout(const at_ctx* c, int64_t nsteps, int every) {
   if (a.rk2) a.off_sigma = take(l.field_bytes);
   a.off_hbuf = take(slot);
   a.anslots = c->delay.mode == AT_SYNC ? 1 : l.nslots;
-  a.aring_bytes = static_cast<size_t>(a.anslots) * slot;
+  a.aring_bytes = static_cast<size_t>(a.anslots) * slot / w * (a.gather ? w : sizeof(double));
   a.off_aring = take(a.aring_bytes);
   if (a.rk2) a.off_bring = take(a.aring_bytes);
   a.off_partial = take(static_cast<size_t>(adj_partials(c->sp)) * sizeof(double));
