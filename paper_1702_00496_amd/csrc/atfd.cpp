@@ -329,7 +329,8 @@ void fill_params(at_ctx* c) {
 // The one-workgroup form of a small 1-D context. Taken for the time-expanded
 // schemes and the synchronous arm where kLineMaxPt points per thread and the
 // LDS of one compute unit hold the problem (up to 8192 points): a step there
-// takes less than the launch of a per-step sweep at every such size.
+// takes less than the launch of a per-step sweep at every such size. The sweep
+// rounds alike (update.hpp), so a call may take either.
 void fill_line(at_ctx* c) {
   LineSteps& q = c->line;
   std::memset(&q, 0, sizeof(q));
@@ -503,7 +504,7 @@ at_status at_step(at_ctx* c, int64_t nsteps) {
   if (!c->state_set) return fail(c, AT_ESTATE, "at_step before at_set_state");
   if (c->delay.mode == AT_DELAY_HOST && c->n + nsteps > c->delay.host_nsteps)
     return fail(c, AT_EINVAL, "host delay table covers %lld steps", (long long)c->delay.host_nsteps);
-  if (c->line.plan.pt > 0) {
+  if (c->line.plan.pt > 0 && line_pays(c->line.line, c->g.f64 ? 8 : 4, nsteps)) {
     if (nsteps > 0) {
       LineSteps q = c->line;
       q.nsteps = nsteps;
@@ -993,17 +994,8 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
     const int64_t len = std::min<int64_t>(every, N - seg);
     StepParams p = c->sp;
     p.counter = reinterpret_cast<int64_t*>(sc + a.off_counter);
-    // A small 1-D context takes its own steps in one launch (which round
-    // differently from the sweep): it is stepped by itself below, and the
-    // segment works on a copy of the history, in the adjoint field that the
-    // reversal writes first.
-    const bool line = last && c->line.plan.pt > 0;
-    if (!last) {
+    if (!last)
       for (int i = 0; i < l.nfbuf; ++i) p.fbuf[i] = ck + a.ck_f[i];
-    } else if (line && l.nfbuf) {
-      p.fbuf[0] = lam[i0];
-      HIP_TRY(c, hipMemcpyAsync(p.fbuf[0], c->sp.fbuf[0], l.field_bytes, hipMemcpyDeviceToDevice, st));
-    }
     const void* u0 = last ? c->sp.ubuf[seg & 1] : static_cast<const void*>(ck);
     HIP_TRY(c, launch_set_counter(p.counter, seg, st));
     HIP_TRY(c, hipMemcpyAsync(levels, u0, l.field_bytes, hipMemcpyDeviceToDevice, st));
@@ -1028,7 +1020,6 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
       if (r != AT_OK) return r;
     }
     if (!last) return AT_OK;
-    if (line) return at_step(c, len);
     // the context at step N
     HIP_TRY(c, hipMemcpyAsync(c->sp.ubuf[N & 1], levels + l.field_bytes * len, l.field_bytes,
                               hipMemcpyDeviceToDevice, st));

@@ -172,10 +172,8 @@ __device__ inline void ens_chunk_finish(const EnsMember& M, const EnsChunk<Real,
     // as a difference to u0, so float rounding stays relative to O(dx) terms
     Real a = Real(0);
 #pragma unroll
-    for (int o = 1; o <= S; ++o) {
-      a = fmadd(ens_tap<Real>(M, S - o), k.w[S + e - o] - u0, a);
-      a = fmadd(ens_tap<Real>(M, S + o), k.w[S + e + o] - u0, a);
-    }
+    for (int o = 1; o <= S; ++o)
+      a = add_pair(a, ens_tap<Real>(M, S - o), k.w[S + e - o] - u0, ens_tap<Real>(M, S + o), k.w[S + e + o] - u0);
     acc[e] = a;
     if constexpr (AB2)
       r[e] = ab2_update(u0, dt, b1, a, b2, k.fo[e]);

@@ -18,6 +18,7 @@
 #pragma once
 
 #include "atfd_internal.hpp"
+#include "update.hpp"
 
 namespace atfd {
 
@@ -122,28 +123,23 @@ struct LineSteps {
 };
 hipError_t launch_line_steps(const LineSteps& q, bool f64, hipStream_t st);
 
-// ------------------------------------------------------------ shared arithmetic
-// The updates below are written with explicit fused multiply-adds: every form
-// of a line's sweep (register-resident, streamed) rounds alike, so schedules
-// and run splits stay bit-identical.
-__device__ inline float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ inline double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
-// One level of the AT combination, in double (a weight of zero drops it).
-template <typename Real>
-__device__ inline double add_level(double acc, double w, Real v) {
-  return w != 0.0 ? fmadd(w, static_cast<double>(v), acc) : acc;
-}
-
-// u + dt (b1 f + b2 f^{n-1}): AB2 (b1 = 3/2, b2 = -1/2), or Euler with b2 = 0
-// (AB2's first step: b1 = 1 and fo must be finite).
-template <typename Real>
-__device__ inline Real ab2_update(Real u0, Real dt, Real b1, Real f, Real b2, Real fo) {
-  return fmadd(dt, fmadd(b1, f, b2 * fo), u0);
-}
-template <typename Real>
-__device__ inline Real euler_update(Real u0, Real dt, Real f) {
-  return fmadd(dt, f, u0);
+// Whether a call of nsteps steps of a context with such a plan takes that
+// launch or a sweep per step (they round alike: update.hpp). The launch reads
+// and writes the whole state through one compute unit whatever the steps, so a
+// call of one or two steps of a large state is faster as sweeps. Microseconds
+// fitted to calls of 1 to 3 steps of 256 to 8192 points, within 10 % of the
+// better: 8192 points, fourth-order AB2, L = 8, FP64: 1 step 13.1 (sweep 6.3), 2
+// steps 15.1 (11.6), 3 steps 17.0 (16.9); 1024 points 5.5 (6.2).
+inline bool line_pays(const Line& M, int w, int64_t nsteps) {
+  const int fields[4] = {2, 4, 6, 3};   // read and written: Euler, AB2, AB3, Heun
+  const int stages = M.integrator == AT_RK2 ? 2 : 1;
+  const double io = static_cast<double>(M.n) * w * fields[M.integrator] +
+                    2.0 * static_cast<double>(line_lds_ring(M.s, M.npe, M.nslots, M.integrator, w));
+  // (the sixth-order FP64 forms spill)
+  const double stage = w == 8 && M.s == 3 ? 1.5 + 5.5e-4 * static_cast<double>(M.n)
+                                          : 0.25 + 7.5e-5 * static_cast<double>(M.n) * M.s;
+  const double steps = static_cast<double>(nsteps) * stages;
+  return 3.7 + io / 45000.0 + steps * stage <= 0.6 + 5.4 * steps;
 }
 
 // Device memory of one line's run: the fields at its first and last step, the
@@ -431,21 +427,16 @@ __device__ __forceinline__ void line_run(const Line& Mref, const LinePlan& pl, c
       if constexpr (EQ == AT_ADVDIFF) {
         Real a = Real(0);
 #pragma unroll
-        for (int o = 1; o <= S; ++o) {
-          a = fmadd(kad[S - o], -dn[o][o], a);
-          a = fmadd(kad[S + o], up[o], a);
-        }
+        for (int o = 1; o <= S; ++o) a = add_pair(a, kad[S - o], -dn[o][o], kad[S + o], up[o]);
         put(e, u0, a);
       } else {
         Real l = Real(0), g = Real(0);
 #pragma unroll
         for (int o = 1; o <= S; ++o) {
-          l = fmadd(lap[S - o], -dn[o][o], l);
-          g = fmadd(grd[S - o], -dn[o][o], g);
-          l = fmadd(lap[S + o], up[o], l);
-          g = fmadd(grd[S + o], up[o], g);
+          l = add_pair(l, lap[S - o], -dn[o][o], lap[S + o], up[o]);
+          g = add_pair(g, grd[S - o], -dn[o][o], grd[S + o], up[o]);
         }
-        put(e, u0, fmadd(-u0, g, l));
+        put(e, u0, burgers_rhs(u0, l, g));
       }
 #pragma unroll
       for (int o = 1; o <= S; ++o) {
@@ -551,12 +542,9 @@ __device__ __forceinline__ void line_run(const Line& Mref, const LinePlan& pl, c
           });
         }
       } else {
-        // AB3 (23, -16, 5)/12; Euler at n = 0, AB2 at n = 1
-        const Real c0 = n == 0 ? Real(1) : n == 1 ? Real(1.5) : Real(23.0 / 12.0);
-        const Real c1 = n == 0 ? Real(0) : n == 1 ? Real(-0.5) : Real(-16.0 / 12.0);
-        const Real c2 = n >= 2 ? Real(5.0 / 12.0) : Real(0);
+        const Ab3<Real> c(n);
         stencil(u, gl, gr, [&](int e, Real u0, Real f) __attribute__((always_inline)) {
-          u[e] = fmadd(dt, fmadd(c2, fb[e], fmadd(c1, fa[e], c0 * f)), u0);
+          u[e] = ab3_update(u0, dt, c, f, fa[e], fb[e]);
           fb[e] = fa[e];
           fa[e] = f;
         });
@@ -589,8 +577,7 @@ __device__ __forceinline__ void line_run(const Line& Mref, const LinePlan& pl, c
       if (active) {
         Real gl[S], gr[S];
         ghosts(s_e + 2 * eset + par * eset, k, hl, hr, gl, gr);
-        const Real half_dt = Real(0.5) * dt;
-        stencil(us, gl, gr, [&](int e, Real u0, Real f) __attribute__((always_inline)) { u[e] = fmadd(half_dt, f, Real(0.5) * (u[e] + u0)); });
+        stencil(us, gl, gr, [&](int e, Real u0, Real f) __attribute__((always_inline)) { u[e] = heun_update(u[e], u0, dt, f); });
         put_edges(u, e_out);
         publish(u, ring, rn);
         halo_sum(k_next & 0xff, nl, hl);

@@ -5,6 +5,7 @@
 
 #include "atfd_internal.hpp"
 #include "delays.hpp"
+#include "update.hpp"
 
 namespace atfd {
 namespace sweep {
@@ -101,6 +102,9 @@ struct Sweep {
   static constexpr int SD = strip_depth<S, SP>();
   static constexpr int NSL = DIM == 3 ? 2 * SD + 2 : 1;
   static constexpr int kBatch = 4;   // points per thread whose loads are issued together
+  // 1-D time-expanded schemes: the arithmetic of update.hpp, so that a step
+  // rounds as it does in a launch that keeps the line on its compute unit
+  static constexpr bool kLine = DIM == 1 && SP == 0;
 
   const StepParams& p;
   Real* lds;
@@ -272,7 +276,7 @@ struct Sweep {
       const int sl = lev_slot[f * kMaxT + m];
       if constexpr (DIM < 3) {
         // a select: no branch between the loads' waits
-        const double with = acc + w[f * kMaxT + m] * static_cast<double>(v[m]);
+        const double with = fmadd(w[f * kMaxT + m], static_cast<double>(v[m]), acc);
         acc = m < p.T && sl >= 0 ? with : acc;
       } else if (m < p.T && sl >= 0) {
         acc += w[f * kMaxT + m] * static_cast<double>(v[m]);
@@ -592,6 +596,12 @@ struct Sweep {
         l1[a][o + SD] = SP != 0 ? static_cast<Real>(p.sl1[a][o + kMaxS]) : Real(0);
         l2[a][o + SD] = SP != 0 ? static_cast<Real>(p.sl2[a][o + kMaxS]) : Real(0);
       }
+    Real ka[2 * S + 1], la[2 * S + 1];
+#pragma unroll
+    for (int o = 0; o <= 2 * S; ++o) {
+      ka[o] = kLine ? static_cast<Real>(p.kad[0][o]) : Real(0);
+      la[o] = kLine ? static_cast<Real>(p.d2a[0][o]) : Real(0);
+    }
     const Real dt = static_cast<Real>(p.dt), alpha = static_cast<Real>(p.alpha);
     const Real vx = static_cast<Real>(p.vel[0]), vy = static_cast<Real>(p.vel[1]),
                vz = static_cast<Real>(p.vel[2]);
@@ -649,8 +659,19 @@ struct Sweep {
         const Real u0 = C[c_at];
         // difference form: the taps of each derivative sum to zero, so each
         // neighbour enters as (v - u0), which keeps float rounding small
-        Real g1 = 0, g2 = 0;
-        if constexpr (SP == 3) {
+        Real g1 = 0, g2 = 0, f1d = 0;
+        if constexpr (kLine) {
+          // (folded taps: the arithmetic of update.hpp)
+          Real kad = 0, lap = 0, grd = 0;
+#pragma unroll
+          for (int o = 1; o <= S; ++o) {
+            const Real xm = C[c_at - o] - u0, xp = C[c_at + o] - u0;
+            kad = add_pair(kad, ka[S - o], xm, ka[S + o], xp);
+            lap = add_pair(lap, la[S - o], xm, la[S + o], xp);
+            grd = add_pair(grd, c1[0][S - o], xm, c1[0][S + o], xp);
+          }
+          f1d = p.equation == AT_ADVDIFF ? kad : burgers_rhs(u0, lap, grd);
+        } else if constexpr (SP == 3) {
           // per axis the CD2; at the point next to a face whose delays are
           // not both zero, the four-point stencil with the face's taps
           const Real vel[3] = {vx, vy, vz};
@@ -740,22 +761,24 @@ struct Sweep {
             g2 += d2;
           }
         }
-        const Real f = p.equation == AT_ADVDIFF ? alpha * g2 - g1 : alpha * g2 - u0 * g1;
+        const Real f = kLine ? f1d : p.equation == AT_ADVDIFF ? alpha * g2 - g1 : alpha * g2 - u0 * g1;
         const int64_t g = gbase + static_cast<int64_t>(y) * p.nx + x;
         Real un;
         if (p.stage == kStageRk1) {
-          un = u0 + dt * f;
+          un = kLine ? euler_update(u0, dt, f) : u0 + dt * f;
           static_cast<Real*>(p.ustar)[g] = un;
         } else if (rk2) {
-          un = Real(0.5) * (pa[k] + u0) + (Real(0.5) * dt) * f;
+          un = kLine ? heun_update(pa[k], u0, dt, f) : Real(0.5) * (pa[k] + u0) + (Real(0.5) * dt) * f;
           static_cast<Real*>(p.ubuf[(n + 1) & 1])[g] = un;
         } else {
           if (!ab) {
-            un = u0 + dt * f;
+            un = kLine ? euler_update(u0, dt, f) : u0 + dt * f;
             if (p.integrator == AT_AB2 || p.integrator == AT_AB3) static_cast<Real*>(p.fbuf[0])[g] = f;
           } else if (!ab3) {
             // AB2, or AB3 at n = 1 (an AB2 step); f^{n-1} is in fbuf[0] either way
-            un = u0 + dt * (Real(1.5) * f - Real(0.5) * pa[k]);
+            un = !kLine ? u0 + dt * (Real(1.5) * f - Real(0.5) * pa[k])
+                 : p.integrator == AT_AB2 ? ab2_update(u0, dt, Real(1.5), f, Real(-0.5), pa[k])
+                                          : ab3_update(u0, dt, Ab3<Real>(n), f, pa[k], Real(0));
             if (p.integrator == AT_AB2) {
               static_cast<Real*>(p.fbuf[0])[g] = f;
             } else {
@@ -763,7 +786,8 @@ struct Sweep {
             }
           } else {
             // AB3, n >= 2: f^{n-1} in fbuf[(n-1)&1], f^{n-2} in fbuf[n&1]
-            un = u0 + dt * ((Real(23) * f - Real(16) * pa[k] + Real(5) * pb[k]) / Real(12));
+            un = kLine ? ab3_update(u0, dt, Ab3<Real>(n), f, pa[k], pb[k])
+                       : u0 + dt * ((Real(23) * f - Real(16) * pa[k] + Real(5) * pb[k]) / Real(12));
             static_cast<Real*>(p.fbuf[n & 1])[g] = f;
           }
           static_cast<Real*>(p.ubuf[(n + 1) & 1])[g] = un;
@@ -909,7 +933,17 @@ struct Sweep {
         for (int e = 0; e < 4; ++e) {
           const Real u0 = row[4 + e];
           Real fval;
-          if constexpr (EQ == AT_ADVDIFF) {
+          if constexpr (kLine) {
+            Real k_ = 0, l_ = 0, g_ = 0;
+#pragma unroll
+            for (int o = 1; o <= S; ++o) {
+              const Real xm = row[4 + e - o] - u0, xp = row[4 + e + o] - u0;
+              k_ = add_pair(k_, kad[0][S - o], xm, kad[0][S + o], xp);
+              l_ = add_pair(l_, lap[0][S - o], xm, lap[0][S + o], xp);
+              g_ = add_pair(g_, grd[0][S - o], xm, grd[0][S + o], xp);
+            }
+            fval = EQ == AT_ADVDIFF ? k_ : burgers_rhs(u0, l_, g_);
+          } else if constexpr (EQ == AT_ADVDIFF) {
             Real ax = 0, ay = 0, az = 0;
 #pragma unroll
             for (int o = 1; o <= S; ++o) {
@@ -1009,7 +1043,12 @@ struct Sweep {
         for (int e = 0; e < 4; ++e) {
           const Real u0 = row[4 + e], f = fq.v[e];
           Real r;
-          if (KIND == kVEuler || KIND == kVRk1) {
+          if constexpr (kLine) {
+            if (KIND == kVEuler || KIND == kVRk1 || (KIND != kVRk2 && !ab)) r = euler_update(u0, dt, f);
+            else if (KIND == kVRk2) r = heun_update(pa[j].v[e], u0, dt, f);
+            else if (KIND == kVAb2) r = ab2_update(u0, dt, Real(1.5), f, Real(-0.5), pa[j].v[e]);
+            else r = ab3_update(u0, dt, Ab3<Real>(n), f, pa[j].v[e], ab3 ? pb[j].v[e] : Real(0));
+          } else if (KIND == kVEuler || KIND == kVRk1) {
             r = u0 + dt * f;
           } else if (KIND == kVRk2) {
             r = Real(0.5) * (pa[j].v[e] + u0) + (Real(0.5) * dt) * f;

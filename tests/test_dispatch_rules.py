@@ -1,4 +1,6 @@
 """The rules that choose kernels, evaluated on the host."""
+import ctypes
+
 import pytest
 
 from tests import _rules
@@ -30,3 +32,19 @@ def test_3d_adjoint_kernel_follows_the_faster_one(rules):
     assert _rules.adjoint_kernel(rules, (384, 384, 64), (8, 8, 16), 4, "ab2", "advdiff", "f32") == 0
     assert _rules.adjoint_kernel(rules, (1024, 1024), (16, 16), 4, "ab2", "advdiff", "f32") == 2
     assert _rules.adjoint_kernel(rules, (4096,), (1,), 6, "ab2", "burgers", "f64") == 2
+
+
+def test_short_calls_of_large_lines_take_the_sweep(rules):
+    """Microseconds a call measured as one launch and as sweeps."""
+    for n, pe, order, integrator, precision, steps, launch, sweeps in [
+            (256, 8, 2, "euler", "f64", 1, 4.8, 6.1), (1024, 16, 4, "ab2", "f64", 1, 5.5, 6.2),
+            (2048, 32, 4, "ab3", "f64", 1, 7.1, 5.8), (4096, 64, 4, "ab2", "f64", 1, 8.4, 6.3),
+            (4096, 64, 4, "ab2", "f64", 2, 9.4, 11.5), (8192, 128, 4, "ab2", "f64", 1, 13.1, 6.3),
+            (8192, 128, 4, "ab2", "f64", 2, 15.1, 11.6), (8192, 128, 4, "ab3", "f64", 3, 20.6, 17.3),
+            (8192, 128, 2, "euler", "f32", 2, 7.2, 11.1), (8192, 128, 4, "rk2", "f32", 1, 9.8, 11.2),
+            (4096, 8, 6, "rk2", "f64", 1, 16.0, 12.2), (1024, 16, 6, "rk2", "f64", 1, 8.6, 11.6),
+            (8192, 8, 6, "rk2", "f32", 2, 14.9, 20.9)]:
+        v = _rules.line(n, pe, order, integrator, 8, "rng")
+        assert rules.context_pt(v, _rules.width(precision)) > 0
+        assert rules.pays(v, _rules.width(precision), ctypes.c_longlong(steps)) == (launch < sweeps), (n, order, integrator, steps)
+        assert rules.pays(v, _rules.width(precision), ctypes.c_longlong(50)) == 1
