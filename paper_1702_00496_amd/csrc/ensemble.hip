@@ -242,18 +242,32 @@ __device__ inline void ens_member_sweep_s(const EnsMember& M, const Real* u, Rea
 // Members whose descriptors a workgroup holds in LDS at a time.
 constexpr int kEnsLdsMembers = AT_ENS_BATCH;
 
-// All steps of the `count` streamed members mem[idx[0..count-1]].
+// Functions that are not inlined into the kernel are each allocated registers
+// by themselves: inlined side by side, the invariants of a kernel's loops were
+// hoisted together and spilled inside them (512-member ensemble: 16.0 us a step
+// inlined, 14.8 this way; 16 streamed members of 65536 points, fourth order, FP64:
+// 57 inlined beside the kept ones, 44 this way or in a kernel of their own). Pointers into LDS are passed
+// as LDS offsets: the callee then addresses LDS directly; the arguments arrive in
+// vector registers.
+using LdsByte = __attribute__((address_space(3))) unsigned char;
+__device__ inline uint32_t lds_offset(const void* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((LdsByte*)p));
+}
+__device__ inline unsigned char* lds_pointer(uint32_t off) {
+  return (unsigned char*)reinterpret_cast<LdsByte*>(uniform(static_cast<int>(off)));
+}
+
+// All steps of the `count` streamed members mem[idx[0..count-1]]
+// (u0 holds the first step's level, u1 the next one's; idx null: all of them).
 template <typename Real, int UX>
-__device__ __forceinline__ void ens_stream(const EnsParams& p, int64_t n0, const EnsMember* mem, const int* idx, int count) {
-  Real* f = static_cast<Real*>(p.f);
-  Real* ring = static_cast<Real*>(p.ring);
-  Real* hb = static_cast<Real*>(p.hbuf);
-  for (int64_t st = 0; st < p.nsteps; ++st) {
+__device__ __forceinline__ void ens_stream(const Real* u0, Real* u1, Real* f, Real* ring, Real* hb, int64_t n0,
+                                           int64_t nsteps, const EnsMember* mem, const int* idx, int count) {
+  for (int64_t st = 0; st < nsteps; ++st) {
     const int64_t n = n0 + st;
-    const Real* u = static_cast<const Real*>(p.u[n & 1]);
-    Real* un = static_cast<Real*>(p.u[(n + 1) & 1]);
+    const Real* u = (st & 1) ? u1 : u0;
+    Real* un = const_cast<Real*>((st & 1) ? u0 : u1);
     for (int i = 0; i < count; ++i) {
-      const EnsMember& M = mem[idx[i]];
+      const EnsMember& M = mem[idx ? uniform(idx[i]) : i];
       switch (M.s) {
         case 1: ens_member_halos<Real, 1>(M, u, ring, hb, n); break;
         case 2: ens_member_halos<Real, 2>(M, u, ring, hb, n); break;
@@ -263,7 +277,7 @@ __device__ __forceinline__ void ens_stream(const EnsParams& p, int64_t n0, const
     // halo values complete before the sweep reads them
     __syncthreads();
     for (int i = 0; i < count; ++i) {
-      const EnsMember& M = mem[idx[i]];
+      const EnsMember& M = mem[idx ? uniform(idx[i]) : i];
       switch (M.s) {
         case 1: ens_member_sweep_s<Real, 1, UX>(M, u, un, f, ring, hb, n); break;
         case 2: ens_member_sweep_s<Real, 2, UX>(M, u, un, f, ring, hb, n); break;
@@ -276,53 +290,46 @@ __device__ __forceinline__ void ens_stream(const EnsParams& p, int64_t n0, const
   }
 }
 
-// All steps of one member kept on the compute unit. A function of its own (not
-// inlined) per form, so that each is allocated registers by itself: inlined
-// side by side the forms' invariants were hoisted together and spilled inside
-// the step loops (512-member ensemble: 16.0 us a step inlined, 14.8 this way).
-// Pointers into LDS are passed as LDS offsets: the callee then addresses LDS
-// directly. SMALL only keeps the 64-register forms apart from the others.
-using LdsByte = __attribute__((address_space(3))) unsigned char;
-__device__ inline uint32_t lds_offset(const void* p) {
-  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((LdsByte*)p));
-}
-__device__ inline unsigned char* lds_pointer(uint32_t off) {
-  return (unsigned char*)reinterpret_cast<LdsByte*>(off);
+template <typename Real, int UX>
+__device__ __attribute__((noinline)) void ens_stream_fn(const Real* u0, Real* u1, Real* f, Real* ring, Real* hb, int64_t n0,
+                                                        int64_t nsteps, uint32_t members, uint32_t indices, int count) {
+  ens_stream<Real, UX>(uniform(u0), uniform(u1), uniform(f), uniform(ring), uniform(hb), uniform(n0), uniform(nsteps),
+                       reinterpret_cast<const EnsMember*>(lds_pointer(members)),
+                       reinterpret_cast<const int*>(lds_pointer(indices)), uniform(count));
 }
 
+// All steps of one member kept on the compute unit. SMALL only keeps the
+// 64-register forms apart from the others.
 template <typename Real, int S, int PT, int KIND, bool GR, bool FG, bool SMALL>
-__device__ __attribute__((noinline)) void ens_line_fn(uint32_t member, LinePlan pl, const Real* u_in, Real* u_out, Real* f,
+__device__ __attribute__((noinline)) void ens_line_fn(uint32_t member, const Real* u_in, Real* u_out, Real* f,
                                                       Real* ring, int64_t n0, int64_t nsteps, uint32_t smem) {
-  // (arguments arrive in vector registers)
   LineBufs<Real> B{uniform(u_in), uniform(u_out), uniform(f), nullptr, nullptr, uniform(ring), nullptr, nullptr, nullptr, nullptr};
-  const EnsMember& M = *reinterpret_cast<const EnsMember*>(lds_pointer(uniform(static_cast<int>(member))));
-  line_run<Real, S, PT, S + 1, KIND, AT_ADVDIFF, GR, FG, false>(M, pl, B, uniform(n0), uniform(nsteps),
-                                                  lds_pointer(uniform(static_cast<int>(smem))));
+  const EnsMember& M = *reinterpret_cast<const EnsMember*>(lds_pointer(member));
+  line_run<Real, S, PT, S + 1, KIND, AT_ADVDIFF, GR, FG, false>(M, M.plan, B, uniform(n0), uniform(nsteps), lds_pointer(smem));
 }
 
 template <typename Real, bool SMALL>
-__device__ __forceinline__ void ens_line(const EnsParams& p, int64_t n0, const EnsMember& M, const LinePlan& pl,
-                                         unsigned char* smem) {
+__device__ __forceinline__ void ens_line(const EnsParams& p, int64_t n0, const EnsMember& M, unsigned char* smem) {
   const Real* u_in = static_cast<const Real*>(p.u[n0 & 1]) + M.off;
   Real* u_out = static_cast<Real*>(p.u[(n0 + p.nsteps) & 1]) + M.off;
   Real* f = static_cast<Real*>(p.f) + M.off;   // read and written by AB2 members only
   Real* ring = static_cast<Real*>(p.ring) + M.ring_off;
   const uint32_t mo = lds_offset(&M), so = lds_offset(smem);
-  const int s = uniform(M.s), pt = uniform(pl.pt);
-  const bool ab2 = uniform(M.integrator) == AT_AB2, glob = uniform(pl.glob) != 0;
+  const int s = uniform(M.s), pt = uniform(M.plan.pt);
+  const bool ab2 = uniform(M.integrator) == AT_AB2, glob = uniform(M.plan.glob) != 0;
   const int64_t ns = p.nsteps;
   auto by_s = [&](auto PTc, auto GRc) __attribute__((always_inline)) {
     constexpr int PT = decltype(PTc)::value;
     constexpr bool GR = decltype(GRc)::value;
     constexpr bool kFg = PT == (sizeof(Real) == 4 ? 64 : 32);   // AB2 keeps f in device memory (line_plan)
     if (ab2) {
-      if (s == 1) ens_line_fn<Real, 1, PT, AT_AB2, GR, kFg, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
-      else if (s == 2) ens_line_fn<Real, 2, PT, AT_AB2, GR, kFg, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
-      else ens_line_fn<Real, 3, PT, AT_AB2, GR, kFg, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
+      if (s == 1) ens_line_fn<Real, 1, PT, AT_AB2, GR, kFg, SMALL>(mo, u_in, u_out, f, ring, n0, ns, so);
+      else if (s == 2) ens_line_fn<Real, 2, PT, AT_AB2, GR, kFg, SMALL>(mo, u_in, u_out, f, ring, n0, ns, so);
+      else ens_line_fn<Real, 3, PT, AT_AB2, GR, kFg, SMALL>(mo, u_in, u_out, f, ring, n0, ns, so);
     } else {
-      if (s == 1) ens_line_fn<Real, 1, PT, AT_EULER, GR, false, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
-      else if (s == 2) ens_line_fn<Real, 2, PT, AT_EULER, GR, false, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
-      else ens_line_fn<Real, 3, PT, AT_EULER, GR, false, SMALL>(mo, pl, u_in, u_out, f, ring, n0, ns, so);
+      if (s == 1) ens_line_fn<Real, 1, PT, AT_EULER, GR, false, SMALL>(mo, u_in, u_out, f, ring, n0, ns, so);
+      else if (s == 2) ens_line_fn<Real, 2, PT, AT_EULER, GR, false, SMALL>(mo, u_in, u_out, f, ring, n0, ns, so);
+      else ens_line_fn<Real, 3, PT, AT_EULER, GR, false, SMALL>(mo, u_in, u_out, f, ring, n0, ns, so);
     }
   };
   auto by_pt = [&](auto PTc) __attribute__((always_inline)) {
@@ -348,14 +355,18 @@ __device__ __forceinline__ void ens_line(const EnsParams& p, int64_t n0, const E
 // loads one CU issues), 7.6 kept (bound by the largest again: 65536 points,
 // fourth order, L = 8, whose history and ring alone stay in memory); 321
 // members of 1024 points, second order, FP64: 4.7 -> 0.77 us.
-template <typename Real, int MAXT, int UX, bool SMALL>
+enum EnsForm { kKept, kKeptSmall, kStreamed };
+template <typename Real, int UX, EnsForm FORM>
 __device__ __forceinline__ void ens_bin(const EnsParams& p, EnsMember* s_mem, unsigned char* smem) {
-  constexpr int kHeld = SMALL ? 1 : kEnsLdsMembers;
-  __shared__ int s_idx[kHeld];
+  constexpr int kHeld = FORM == kKeptSmall ? 1 : kEnsLdsMembers;
+  __shared__ int s_idx[FORM == kKept ? kHeld : 1];
   constexpr int kWords = sizeof(EnsMember) / sizeof(uint32_t);
   static_assert(sizeof(EnsMember) % sizeof(uint32_t) == 0, "descriptors are copied as words");
   const int m0 = p.bin_start[blockIdx.x], m1 = p.bin_start[blockIdx.x + 1];
   const int64_t n0 = p.counter[0];
+  const Real* u0 = static_cast<const Real*>(p.u[n0 & 1]);
+  Real* u1 = static_cast<Real*>(p.u[(n0 + 1) & 1]);
+  Real *f = static_cast<Real*>(p.f), *ring = static_cast<Real*>(p.ring), *hb = static_cast<Real*>(p.hbuf);
   for (int b0 = m0; b0 < m1; b0 += kHeld) {
     const int count = min(kHeld, m1 - b0);
     __syncthreads();   // the previous batch is done with the descriptors
@@ -365,20 +376,23 @@ __device__ __forceinline__ void ens_bin(const EnsParams& p, EnsMember* s_mem, un
       dst[i] = reinterpret_cast<const uint32_t*>(p.mem + p.order[b0 + j])[i - j * kWords];
     }
     __syncthreads();
-    int streamed = 0;   // uniform: every thread sees the same plans
-    for (int j = 0; j < count; ++j) {
-      const LinePlan pl = line_plan(s_mem[j], sizeof(Real), blockDim.x, p.lds, SMALL ? ens_small_pt(sizeof(Real) == 8) : kEnsMaxPt, p.share);
-      if (uniform(pl.pt) != 0) {
-        ens_line<Real, SMALL>(p, n0, s_mem[j], pl, smem);
-      } else {
-        if (threadIdx.x == 0) s_idx[streamed] = j;
-        ++streamed;
+    if constexpr (FORM == kStreamed) {
+      ens_stream<Real, UX>(u0, u1, f, ring, hb, n0, p.nsteps, s_mem, nullptr, count);
+    } else {
+      int streamed = 0;   // uniform: every thread sees the same plans
+      for (int j = 0; j < count; ++j) {
+        if (uniform(s_mem[j].plan.pt) != 0) {
+          ens_line<Real, FORM == kKeptSmall>(p, n0, s_mem[j], smem);
+        } else {
+          if (FORM == kKept && threadIdx.x == 0) s_idx[streamed] = j;
+          ++streamed;
+        }
       }
-    }
-    if constexpr (!SMALL) {
-      if (uniform(streamed) > 0) {
-        __syncthreads();
-        ens_stream<Real, UX>(p, n0, s_mem, s_idx, uniform(streamed));
+      if constexpr (FORM == kKept) {
+        if (uniform(streamed) > 0) {
+          __syncthreads();
+          ens_stream_fn<Real, UX>(u0, u1, f, ring, hb, n0, p.nsteps, lds_offset(s_mem), lds_offset(s_idx), streamed);
+        }
       }
     }
   }
@@ -389,7 +403,7 @@ template <typename Real, int MAXT, int UX>
 __global__ __launch_bounds__(MAXT) void ens_steps_kernel(EnsParams p) {
   extern __shared__ __align__(16) unsigned char ens_smem[];
   __shared__ EnsMember s_mem[kEnsLdsMembers];
-  ens_bin<Real, MAXT, UX, false>(p, s_mem, ens_smem);
+  ens_bin<Real, UX, kKept>(p, s_mem, ens_smem);
 }
 
 // Every member kept on its compute unit with few points per thread: 64
@@ -398,7 +412,14 @@ template <typename Real>
 __global__ __launch_bounds__(kEnsMaxThreads, 8) void ens_small_kernel(EnsParams p) {
   extern __shared__ __align__(16) unsigned char ens_smem[];
   __shared__ EnsMember s_mem[1];
-  ens_bin<Real, kEnsMaxThreads, 1, true>(p, s_mem, ens_smem);
+  ens_bin<Real, 1, kKeptSmall>(p, s_mem, ens_smem);
+}
+
+// Every member streamed.
+template <typename Real, int MAXT, int UX>
+__global__ __launch_bounds__(MAXT) void ens_stream_kernel(EnsParams p) {
+  __shared__ EnsMember s_mem[kEnsLdsMembers];
+  ens_bin<Real, UX, kStreamed>(p, s_mem, nullptr);
 }
 
 // The edge strips of u^0 into the ring slot of level 0 of every member (the
@@ -585,30 +606,25 @@ int64_t ens_static_lds(bool small) {
   return ((small ? 1 : kEnsLdsMembers) * static_cast<int64_t>(sizeof(EnsMember) + sizeof(int)) + 255) / 256 * 256;
 }
 
-hipError_t launch_ens_steps(const EnsParams& p, bool f64, bool small, int nbins, int threads, hipStream_t st) {
-  if (threads < 64 || threads > kEnsMaxThreads || threads % 64) return hipErrorInvalidValue;
-  if (p.lds < 0 || p.lds + ens_static_lds(small) > static_cast<int64_t>(kLdsLimit)) return hipErrorInvalidValue;
-  const size_t lds = static_cast<size_t>(p.lds);
-  if (small) {
-    if (f64)
-      hipLaunchKernelGGL((ens_small_kernel<double>), dim3(nbins), dim3(threads), lds, st, p);
-    else
-      hipLaunchKernelGGL((ens_small_kernel<float>), dim3(nbins), dim3(threads), lds, st, p);
-    return hipGetLastError();
-  }
+template <typename Real>
+void launch_steps(const EnsParams& p, bool small, bool streamed, int nbins, int threads, size_t lds, hipStream_t st) {
   // workgroups of up to 512 threads have twice the registers: twice the
   // chunks in flight of a streamed member
-  if (f64) {
-    if (threads > 512)
-      hipLaunchKernelGGL((ens_steps_kernel<double, 1024, 1>), dim3(nbins), dim3(threads), lds, st, p);
-    else
-      hipLaunchKernelGGL((ens_steps_kernel<double, 512, 2>), dim3(nbins), dim3(threads), lds, st, p);
-  } else {
-    if (threads > 512)
-      hipLaunchKernelGGL((ens_steps_kernel<float, 1024, 1>), dim3(nbins), dim3(threads), lds, st, p);
-    else
-      hipLaunchKernelGGL((ens_steps_kernel<float, 512, 2>), dim3(nbins), dim3(threads), lds, st, p);
-  }
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(nbins), dim3(threads), lds, st, p); };
+  if (streamed && threads > 512) go(ens_stream_kernel<Real, 1024, 1>);
+  else if (streamed) go(ens_stream_kernel<Real, 512, 2>);
+  else if (small) go(ens_small_kernel<Real>);
+  else if (threads > 512) go(ens_steps_kernel<Real, 1024, 1>);
+  else go(ens_steps_kernel<Real, 512, 2>);
+}
+
+hipError_t launch_ens_steps(const EnsParams& p, bool f64, bool small, bool streamed, int nbins, int threads,
+                            hipStream_t st) {
+  if (threads < 64 || threads > kEnsMaxThreads || threads % 64) return hipErrorInvalidValue;
+  if (p.lds < 0 || p.lds + ens_static_lds(small) > static_cast<int64_t>(kLdsLimit)) return hipErrorInvalidValue;
+  const size_t lds = streamed ? 0 : static_cast<size_t>(p.lds);
+  if (f64) launch_steps<double>(p, small, streamed, nbins, threads, lds, st);
+  else launch_steps<float>(p, small, streamed, nbins, threads, lds, st);
   return hipGetLastError();
 }
 

@@ -11,7 +11,8 @@ struct EnsMember : Line {
   int64_t off;                     // first point in the packed fields
   int64_t ring_off;                // first value of its ring in the packed ring
   int64_t hoff;                    // first value of its halo values in the packed halo buffer
-  int64_t vec;                     // 4-point vector sweep (b % 4 == 0 and off % 4 == 0)
+  int vec;                         // 4-point vector sweep (b % 4 == 0 and off % 4 == 0)
+  LinePlan plan;                   // on its compute unit (pt = 0: streamed), for the schedule in force
   double length, c, alpha;         // for the exact solution
 };
 
@@ -26,7 +27,6 @@ struct EnsParams {
   int64_t* counter;                // [0] = step n, [1] = finished workgroups
   int64_t nsteps;                  // steps of this launch
   int64_t lds;                     // dynamic LDS bytes of a workgroup
-  int share;                       // workgroups per compute unit the schedule asks for
 };
 
 struct EnsNormParams {
@@ -52,9 +52,11 @@ struct EnsStatsParams {
 hipError_t launch_ens_stats(const EnsStatsParams& p, hipStream_t st);
 // `small`: every member is kept on its compute unit with at most ens_small_pt
 // points per thread (the lighter kernel, two 1024-thread workgroups per CU).
+// `streamed`: no member is kept.
 inline __host__ __device__ constexpr int ens_small_pt(bool f64) { return f64 ? 4 : 8; }
 constexpr int kEnsMaxPt = 64;
-hipError_t launch_ens_steps(const EnsParams& p, bool f64, bool small, int nbins, int threads, hipStream_t st);
+hipError_t launch_ens_steps(const EnsParams& p, bool f64, bool small, bool streamed, int nbins, int threads,
+                            hipStream_t st);
 // Static LDS of a workgroup of the steps kernel.
 int64_t ens_static_lds(bool small);
 hipError_t launch_ens_publish_level0(const EnsParams& p, bool f64, int count, hipStream_t st);

@@ -24,6 +24,8 @@ struct at_ens {
   std::vector<EnsMember> mem;
   std::vector<int> bin_start, order;
   int groups_per_cu = 1, threads = 1024, nbins = 0, cus = 256;
+  bool small = false;        // the lighter steps kernel (plan_members)
+  int64_t lds = 0;           // its dynamic LDS bytes
   size_t total_points = 0, field_bytes = 0, ring_elems = 0, halo_elems = 0;
   size_t off_mem = 0, off_bins = 0, off_order = 0, off_u[2] = {0, 0}, off_f = 0, off_ring = 0, off_hbuf = 0;
   size_t off_counter = 0, off_out = 0, off_phase = 0, off_stats = 0, total = 0;
@@ -43,9 +45,9 @@ struct at_ens {
 namespace {
 
 constexpr int kPhaseMax = 1 << 16;   // doubles of per-member phases staged for at_ens_norms
-// autotune candidates: workgroups per CU x threads per workgroup
 // points whose arithmetic takes as long as the fixed chain of a step
 constexpr double kEnsChainPoints = 4000.0;
+// autotune candidates: workgroups per CU x threads per workgroup
 constexpr int kEnsTuneGroups[3] = {1, 2, 4};
 constexpr int kEnsTuneThreads[3] = {256, 512, 1024};
 
@@ -160,35 +162,33 @@ at_status plan(at_ens* e, int32_t count, const at_ens_member* m, int32_t precisi
   return AT_OK;
 }
 
-// Dynamic LDS of a workgroup of the steps kernel, and whether the lighter
-// kernel takes the launch: where several workgroups share a CU and every
-// member is kept on it with at most ens_small_pt points per thread. (One
-// workgroup per CU gains nothing from fewer registers, and longer chunks take
-// fewer instructions a step: 8192 points, fourth order, FP32: 1.88 us a step in the
-// lighter kernel, 1.27 in the other.)
-// groups_per_cu workgroups share a CU's LDS.
-void launch_shape(const at_ens* e, bool* small, int64_t* lds) {
+// The members' plans under the schedule in force (groups_per_cu workgroups
+// share a CU's LDS), the dynamic LDS of a workgroup of the steps kernel, and
+// whether the lighter kernel takes the launch: where several workgroups share a
+// CU and every member is kept on it with at most ens_small_pt points per thread.
+// (One workgroup per CU gains nothing from fewer registers, and longer chunks
+// take fewer instructions a step: 8192 points, fourth order, FP32: 1.88 us a step
+// in the lighter kernel, 1.27 in the other.)
+bool plan_members(at_ens* e, bool small) {
   const int w = e->f64 ? 8 : 4;
-  auto need = [&](bool sm, int64_t budget, int64_t* most) -> bool {
-    bool all = true;
-    *most = 0;
-    for (const EnsMember& m : e->mem) {
-      const LinePlan pl = line_plan(m, w, e->threads, budget, sm ? ens_small_pt(e->f64) : kEnsMaxPt, e->groups_per_cu);
-      if (!pl.pt) {
-        all = false;
-        continue;
-      }
-      const int64_t b = line_lds_base(m.s, pl.c * m.npe, m.integrator, w) +
-                        (pl.glob ? 0 : line_lds_ring(m.s, m.npe, m.nslots, m.integrator, w));
-      *most = std::max(*most, b);
+  const int64_t budget = static_cast<int64_t>(kLdsLimit) / e->groups_per_cu - ens_static_lds(small);
+  bool all = true;
+  e->small = small;
+  e->lds = 0;
+  for (EnsMember& m : e->mem) {
+    const LinePlan pl = line_plan(m, w, e->threads, budget, small ? ens_small_pt(e->f64) : kEnsMaxPt, e->groups_per_cu);
+    m.plan = pl;
+    if (!pl.pt) {
+      all = false;
+      continue;
     }
-    return all;
-  };
-  auto budget = [&](bool sm) {
-    return static_cast<int64_t>(kLdsLimit) / e->groups_per_cu - ens_static_lds(sm);
-  };
-  *small = e->groups_per_cu > 1 && need(true, budget(true), lds);
-  if (!*small) need(false, budget(false), lds);
+    e->lds = std::max(e->lds, line_lds_base(m.s, pl.c * m.npe, m.integrator, w) +
+                                  (pl.glob ? 0 : line_lds_ring(m.s, m.npe, m.nslots, m.integrator, w)));
+  }
+  return all;
+}
+void plan_launch(at_ens* e) {
+  if (!(e->groups_per_cu > 1 && plan_members(e, true))) (void)plan_members(e, false);
 }
 
 // The schedule before any tuning: one 1024-thread workgroup per CU, or, where
@@ -202,13 +202,12 @@ void default_schedule(at_ens* e) {
     if (e->count <= e->cus) break;
     e->threads = threads;
     e->groups_per_cu = e->count > 2 * e->cus ? 4 : 2;
-    bool small = false;
-    int64_t lds = 0;
-    launch_shape(e, &small, &lds);
-    if (small) return;
+    plan_launch(e);
+    if (e->small) return;
   }
   e->groups_per_cu = 1;
   e->threads = 1024;
+  plan_launch(e);
 }
 
 // Longest-first balance: members sorted by work, each to the least loaded
@@ -222,9 +221,7 @@ void schedule(at_ens* e) {
     // a step of a member kept on its CU is a fixed chain plus its points'
     // arithmetic; a streamed member's points cost several times as much
     const EnsMember& d = e->mem[i];
-    const LinePlan pl = line_plan(d, e->f64 ? 8 : 4, e->threads, static_cast<int64_t>(kLdsLimit) / e->groups_per_cu -
-                                  ens_static_lds(false), kEnsMaxPt, e->groups_per_cu);
-    return kEnsChainPoints + static_cast<double>(d.n) * (d.integrator == AT_AB2 ? 1.5 : 1.0) * (pl.pt ? 1.0 : 4.0);
+    return kEnsChainPoints + static_cast<double>(d.n) * (d.integrator == AT_AB2 ? 1.5 : 1.0) * (d.plan.pt ? 1.0 : 4.0);
   };
   std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return work(a) > work(b); });
   std::vector<double> load(nb, 0.0);
@@ -248,7 +245,16 @@ void schedule(at_ens* e) {
   e->nbins = nb;
 }
 
+// Whether a run streams every member (the kernel without the kept forms).
+bool streams(const at_ens* e) {
+  for (const EnsMember& m : e->mem)
+    if (m.plan.pt) return false;
+  return true;
+}
+
 at_status upload_schedule(at_ens* e) {
+  ENS_TRY(e, hipMemcpyAsync(e->ws + e->off_mem, e->mem.data(), sizeof(EnsMember) * e->mem.size(), hipMemcpyHostToDevice,
+                            e->stream));
   ENS_TRY(e, hipMemcpyAsync(e->ws + e->off_bins, e->bin_start.data(), sizeof(int) * e->bin_start.size(),
                             hipMemcpyHostToDevice, e->stream));
   ENS_TRY(e, hipMemcpyAsync(e->ws + e->off_order, e->order.data(), sizeof(int) * e->order.size(),
@@ -333,9 +339,7 @@ at_status at_ens_create(int32_t count, const at_ens_member* members, int32_t pre
   p.ring = e->ring_elems ? e->ws + e->off_ring : nullptr;
   p.hbuf = e->ws + e->off_hbuf;
   p.counter = reinterpret_cast<int64_t*>(e->ws + e->off_counter);
-  hipError_t he = hipMemcpyAsync(e->ws + e->off_mem, e->mem.data(), sizeof(EnsMember) * count,
-                                 hipMemcpyHostToDevice, e->stream);
-  if (he == hipSuccess) he = hipMemsetAsync(p.counter, 0, kCounterWords * sizeof(int64_t), e->stream);
+  const hipError_t he = hipMemsetAsync(p.counter, 0, kCounterWords * sizeof(int64_t), e->stream);
   if (he != hipSuccess) {
     delete e;
     return efail(nullptr, AT_EHIP, "ensemble set-up: %s", hipGetErrorString(he));
@@ -371,11 +375,9 @@ at_status at_ens_run(at_ens* e, int64_t nsteps) {
     if (!e->cap_stream) ENS_TRY(e, hipStreamCreateWithFlags(&e->cap_stream, hipStreamNonBlocking));
     EnsParams p = e->ep;
     p.nsteps = nsteps;
-    bool small = false;
-    launch_shape(e, &small, &p.lds);
-    p.share = e->groups_per_cu;
+    p.lds = e->lds;
     ENS_TRY(e, hipStreamBeginCapture(e->cap_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t le = launch_ens_steps(p, e->f64, small, e->nbins, e->threads, e->cap_stream);
+    hipError_t le = launch_ens_steps(p, e->f64, e->small, streams(e), e->nbins, e->threads, e->cap_stream);
     hipGraph_t gr = nullptr;
     hipError_t ce = hipStreamEndCapture(e->cap_stream, &gr);
     if (le != hipSuccess || ce != hipSuccess) {
@@ -404,6 +406,7 @@ at_status at_ens_set_tuning(at_ens* e, int32_t groups_per_cu, int32_t threads) {
   drop_graph(e);
   e->threads = t;
   e->groups_per_cu = g;
+  plan_launch(e);
   schedule(e);
   return upload_schedule(e);
 }
