@@ -16,6 +16,29 @@ struct EnsMember : Line {
   double length, c, alpha;         // for the exact solution
 };
 
+// Microseconds of a run of nsteps steps on the member's compute unit, kept there
+// (beyond kEnsKeptStart) and streamed. A kept member's whole state passes its
+// compute unit twice whatever the steps, so short runs are streamed. Fitted to
+// runs of 1 to 64 steps of 1024 to 65536 points, orders 2 and 4; the choice took
+// at most 20 % longer than the better (one of 280 runs 35 %, at 3 steps). 512 members of 8192 points (two a compute
+// unit), fourth order, FP64, kept / streamed: 1 step 81 / 33, 3 steps 88 / 77, 4
+// steps 91 / 98; 64 of 4096, second order, FP32: 1 step 15 / 17.
+constexpr double kEnsKeptStart = 6.0;
+struct EnsTimes {
+  double kept, streamed;
+};
+inline EnsTimes ens_times(const EnsMember& m, int w, int64_t nsteps) {
+  const double steps = static_cast<double>(nsteps);
+  const double fields = static_cast<double>(m.n) * w * (m.integrator == AT_AB2 ? 4 : 2);   // read and written a step
+  const double ring = static_cast<double>(line_lds_ring(m.s, m.npe, m.nslots, m.integrator, w));
+  EnsTimes t;
+  t.streamed = steps * (2.45 + fields / 25000.0);
+  t.kept = m.plan.pt ? (fields + 2.0 * ring) / (w == 4 ? 17000.0 : 13000.0) +
+                           steps * (0.5 + fields / 210000.0 * (w == 8 && m.plan.fglob ? 4 : 1))
+                     : t.streamed;
+  return t;
+}
+
 struct EnsParams {
   const EnsMember* mem;            // [count]
   const int* bin_start;            // [nbins + 1] ranges of `order`

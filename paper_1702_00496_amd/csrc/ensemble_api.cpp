@@ -245,11 +245,24 @@ void schedule(at_ens* e) {
   e->nbins = nb;
 }
 
-// Whether a run streams every member (the kernel without the kept forms).
-bool streams(const at_ens* e) {
-  for (const EnsMember& m : e->mem)
-    if (m.plan.pt) return false;
-  return true;
+// Whether a run of nsteps steps streams every member: where none is kept, and
+// in short runs (ens_times); the longer of the workgroups decides.
+bool streams(const at_ens* e, int64_t nsteps) {
+  double kept = 0.0, streamed = 0.0;
+  bool any = false;
+  for (int b = 0; b < e->nbins; ++b) {
+    double k = kEnsKeptStart, st = 0.0;
+    for (int i = e->bin_start[b]; i < e->bin_start[b + 1]; ++i) {
+      const EnsMember& m = e->mem[e->order[i]];
+      const EnsTimes t = ens_times(m, e->f64 ? 8 : 4, nsteps);
+      any = any || m.plan.pt;
+      k += t.kept;
+      st += t.streamed;
+    }
+    kept = std::max(kept, k);
+    streamed = std::max(streamed, st);
+  }
+  return !any || streamed < kept;
 }
 
 at_status upload_schedule(at_ens* e) {
@@ -377,7 +390,7 @@ at_status at_ens_run(at_ens* e, int64_t nsteps) {
     p.nsteps = nsteps;
     p.lds = e->lds;
     ENS_TRY(e, hipStreamBeginCapture(e->cap_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t le = launch_ens_steps(p, e->f64, e->small, streams(e), e->nbins, e->threads, e->cap_stream);
+    hipError_t le = launch_ens_steps(p, e->f64, e->small, streams(e, nsteps), e->nbins, e->threads, e->cap_stream);
     hipGraph_t gr = nullptr;
     hipError_t ce = hipStreamEndCapture(e->cap_stream, &gr);
     if (le != hipSuccess || ce != hipSuccess) {

@@ -10,6 +10,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SOURCE = r"""
 #include "adjoint.hpp"
+#include "ensemble.hpp"
 #include "line.hpp"
 using namespace atfd;
 // 0: strip and stage kernels of adjoint.hip, 2: 1-D / 2-D stage kernel, 3: 3-D stage kernel
@@ -41,6 +42,15 @@ extern "C" void plan(const int* v, int w, int threads, long long lds, int max_pt
 // a context: its plan, 0 where it is stepped launch by launch
 extern "C" int context_pt(const int* v, int w) {
   return line_plan(line(v), w, kMaxSweepThreads, static_cast<int64_t>(kLdsLimit), kLineMaxPt, 1).pt;
+}
+// microseconds of `count` such members on one compute unit: {kept, streamed}
+extern "C" void ens(const int* v, int w, int count, long long nsteps, double* out) {
+  EnsMember m{};
+  static_cast<Line&>(m) = line(v);
+  m.plan = line_plan(m, w, 1024, static_cast<int64_t>(kLdsLimit) - 16384, kEnsMaxPt, 1);
+  const EnsTimes t = ens_times(m, w, nsteps);
+  out[0] = kEnsKeptStart + count * t.kept;
+  out[1] = count * t.streamed;
 }
 extern "C" int pays(const int* v, int w, long long nsteps) { return line_pays(line(v), w, nsteps); }
 """

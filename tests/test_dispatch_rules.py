@@ -48,3 +48,18 @@ def test_short_calls_of_large_lines_take_the_sweep(rules):
         assert rules.context_pt(v, _rules.width(precision)) > 0
         assert rules.pays(v, _rules.width(precision), ctypes.c_longlong(steps)) == (launch < sweeps), (n, order, integrator, steps)
         assert rules.pays(v, _rules.width(precision), ctypes.c_longlong(50)) == 1
+
+
+def test_short_ensemble_runs_are_streamed(rules):
+    """Microseconds a run measured with every member kept and streamed."""
+    for per_cu, n, pe, order, precision, steps, kept, streamed in [
+            (1, 1024, 16, 2, "f64", 1, 17.0, 12.0), (1, 1024, 16, 4, "f32", 6, 18.7, 26.0),
+            (1, 4096, 64, 4, "f64", 1, 23.0, 15.0), (1, 4096, 64, 4, "f64", 6, 29.0, 40.0),
+            (1, 16384, 256, 4, "f64", 1, 62.0, 33.0), (1, 16384, 256, 4, "f64", 6, 75.0, 144.0),
+            (2, 8192, 128, 4, "f64", 1, 81.0, 33.0), (2, 8192, 128, 4, "f64", 6, 97.0, 144.0),
+            (2, 65536, 1024, 4, "f32", 1, 273.0, 109.0), (2, 65536, 1024, 4, "f32", 6, 418.0, 567.0),
+            (1, 32768, 512, 4, "f64", 3, 209.0, 145.0), (1, 32768, 512, 4, "f64", 16, 529.0, 725.0)]:
+        v = _rules.line(n, pe, order, "euler" if order == 2 else "ab2", 8, "rng")
+        t = (ctypes.c_double * 2)()
+        rules.ens(v, _rules.width(precision), per_cu, ctypes.c_longlong(steps), t)
+        assert (t[1] < t[0]) == (streamed < kept), (n, order, precision, steps, list(t))
