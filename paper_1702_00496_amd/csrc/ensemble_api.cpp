@@ -9,8 +9,11 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <new>
+#include <queue>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "ensemble.hpp"
@@ -216,21 +219,26 @@ void schedule(at_ens* e) {
   const int count = e->count;
   int nb = std::min(count, std::max(1, e->groups_per_cu * e->cus));
   std::vector<int> idx(count);
-  for (int i = 0; i < count; ++i) idx[i] = i;
-  auto work = [&](int i) {
+  std::vector<double> work(count);
+  for (int i = 0; i < count; ++i) {
     // a step of a member kept on its CU is a fixed chain plus its points'
     // arithmetic; a streamed member's points cost several times as much
     const EnsMember& d = e->mem[i];
-    return kEnsChainPoints + static_cast<double>(d.n) * (d.integrator == AT_AB2 ? 1.5 : 1.0) * (d.plan.pt ? 1.0 : 4.0);
-  };
-  std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return work(a) > work(b); });
+    idx[i] = i;
+    work[i] = kEnsChainPoints + static_cast<double>(d.n) * (d.integrator == AT_AB2 ? 1.5 : 1.0) * (d.plan.pt ? 1.0 : 4.0);
+  }
+  std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return work[a] > work[b]; });
   std::vector<double> load(nb, 0.0);
   std::vector<std::vector<int>> bins(nb);
+  // the least loaded workgroup, the first of equals
+  using Load = std::pair<double, int>;
+  std::priority_queue<Load, std::vector<Load>, std::greater<Load>> least;
+  for (int j = 0; j < nb; ++j) least.push({0.0, j});
   for (int i : idx) {
-    int best = 0;
-    for (int j = 1; j < nb; ++j)
-      if (load[j] < load[best]) best = j;
-    load[best] += work(i);
+    const int best = least.top().second;
+    least.pop();
+    load[best] += work[i];
+    least.push({load[best], best});
     bins[best].push_back(i);
   }
   std::vector<int> bo(nb);
