@@ -44,12 +44,15 @@ struct LinePlan {
 };
 
 // Delays drawn ahead: two halves of kLineDelays bytes, one byte per face and
-// step, used alternately.
+// step, used alternately. A workgroup has a thread per PE at least, so a half
+// always covers two steps.
 constexpr int kLineDelays = 4096;
+constexpr int kLineMaxThreads = 1024;
+static_assert(kLineDelays >= 2 * (2 * kLineMaxThreads), "line_run's batches are of two steps or more");
 
 inline __host__ __device__ int line_batch(int faces) {
   const int r = kLineDelays / faces;
-  return r < 1 ? 1 : r > 64 ? 64 : r;
+  return r > 64 ? 64 : r;
 }
 
 // LDS bytes of a line's run without its ring, and of its ring (one level ring;
@@ -76,8 +79,7 @@ inline __host__ __device__ LinePlan line_plan(const Line& M, int w, int threads,
   LinePlan best{0, 0, 0, 0, 0};
   // (the kernels combine the schemes' own level count)
   if (M.mode != AT_SYNC && M.T != M.s + 1) return best;
-  const int faces = 2 * M.npe;
-  if (faces > kLineDelays || M.b < 2 * M.s) return best;
+  if (threads > kLineMaxThreads || M.b < 2 * M.s) return best;
   const int reg_pt = w == 4 ? 64 : 32;   // u alone
   int64_t best_cost = 0;
   for (int pt = 4; pt <= max_pt && pt <= reg_pt; pt *= 2) {
@@ -455,11 +457,10 @@ __device__ __forceinline__ void line_run(const Line& Mref, const LinePlan& pl, c
   // j batch ..) into half j & 1 during step j batch - 2, whose threads have all
   // read what that half held before the barrier that began it.
   int row = 0, half = 0;     // of the step after the current one
-  for (int64_t nb = 0; nb < nsteps && nb < 2; nb += batch)
-    draw(n0 + nb, static_cast<int>(nsteps - nb < batch ? nsteps - nb : batch), static_cast<int>(nb & 1));
+  draw(n0, static_cast<int>(nsteps < batch ? nsteps : batch), 0);
   // steps until the next batch is drawn (batch j begins at step j batch), and
-  // the half it goes to: j = 1, or 2 where batches are single steps
-  int until = batch == 1 ? 1 : batch - 1, next_half = batch == 1 ? 0 : 1;
+  // the half it goes to
+  int until = batch - 1, next_half = 1;
   if (active) put_edges(u, s_e);
   __syncthreads();
   int k = active ? delays_at(0, 0) : 0;

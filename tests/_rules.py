@@ -39,6 +39,12 @@ extern "C" void plan(const int* v, int w, int threads, long long lds, int max_pt
   const LinePlan p = line_plan(line(v), w, threads, lds, max_pt, share);
   out[0] = p.pt; out[1] = p.c; out[2] = p.nshort; out[3] = p.glob; out[4] = p.fglob;
 }
+// the plan of an ensemble member on one workgroup of `threads` threads a compute unit
+extern "C" void member_plan(const int* v, int w, int threads, int* out) {
+  // (24 descriptors of a batch and their indices, rounded up)
+  const long long fixed = (AT_ENS_BATCH * static_cast<long long>(sizeof(EnsMember) + sizeof(int)) + 255) / 256 * 256;
+  plan(v, w, threads, static_cast<long long>(kLdsLimit) - fixed, kEnsMaxPt, 1, out);
+}
 // a context: its plan, 0 where it is stepped launch by launch
 extern "C" int context_pt(const int* v, int w) {
   return line_plan(line(v), w, kMaxSweepThreads, static_cast<int64_t>(kLdsLimit), kLineMaxPt, 1).pt;

@@ -63,3 +63,24 @@ def test_short_ensemble_runs_are_streamed(rules):
         t = (ctypes.c_double * 2)()
         rules.ens(v, _rules.width(precision), per_cu, ctypes.c_longlong(steps), t)
         assert (t[1] < t[0]) == (streamed < kept), (n, order, precision, steps, list(t))
+
+
+def test_plans_of_members_and_contexts(rules):
+    from tests import test_gpu_line as G
+    from tests.test_gpu_line_forms import MEMBERS
+    out = (ctypes.c_int * 5)()
+    for n, pe, order, integrator, L, mode, want in MEMBERS:
+        for precision, form in want.items():
+            rules.member_plan(_rules.line(n, pe, order, integrator, L, mode), _rules.width(precision), 1024, out)
+            assert tuple(out) == form, (n, pe, order, integrator, precision, tuple(out))
+    # points per thread of the contexts whose runs are compared with the oracle (0: a sweep per step)
+    points = {(8192, 2048): 0, (1100, 220): 0, (10240, 160): 0, (4096, 64): 8, (8192, 128): 8}
+    for n, pe, order, integrator, _, mode, L, _ in G.CONTEXTS:
+        for precision in ("f64", "f32"):
+            v = _rules.line(n, pe, order, integrator, L, mode)
+            assert rules.context_pt(v, _rules.width(precision)) == points.get((n, pe), 4), (n, pe, precision)
+    # overridden level counts, PEs of more threads than a workgroup, chunks shorter than the half-width
+    assert rules.context_pt(_rules.line(64, 4, 4, "ab2", 4, "rng", T=2), 8) == 0
+    assert rules.context_pt(_rules.line(4096, 1024, 2, "euler", 4, "rng"), 8) == 4
+    assert rules.context_pt(_rules.line(4100, 1025, 2, "euler", 4, "rng"), 8) == 0
+    assert rules.context_pt(_rules.line(25, 5, 4, "ab2", 4, "rng"), 8) == 0
