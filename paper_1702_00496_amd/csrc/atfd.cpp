@@ -505,9 +505,9 @@ at_status at_step(at_ctx* c, int64_t nsteps) {
   if (c->delay.mode == AT_DELAY_HOST && c->n + nsteps > c->delay.host_nsteps)
     return fail(c, AT_EINVAL, "host delay table covers %lld steps", (long long)c->delay.host_nsteps);
   if (c->line.plan.pt > 0 && line_pays(c->line.line, c->g.f64 ? 8 : 4, nsteps)) {
-    if (nsteps > 0) {
+    for (int64_t done = 0; done < nsteps; done += kLineMaxSteps) {
       LineSteps q = c->line;
-      q.nsteps = nsteps;
+      q.nsteps = std::min(nsteps - done, kLineMaxSteps);
       HIP_TRY(c, launch_line_steps(q, c->g.f64, c->stream));
     }
     c->n += nsteps;

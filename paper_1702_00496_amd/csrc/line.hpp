@@ -108,6 +108,9 @@ inline __host__ __device__ LinePlan line_plan(const Line& M, int w, int threads,
 
 // A launch that advances a whole 1-D context nsteps steps (line.hip).
 constexpr int kLineMaxPt = 8;      // points per thread of such a launch
+// Steps of one launch: 8 to 80 ms, so that a long call leaves the device gaps to
+// take other work in (a launch costs 4 to 13 us).
+constexpr int64_t kLineMaxSteps = 1 << 14;
 struct LineSteps {
   Line line;
   LinePlan plan;

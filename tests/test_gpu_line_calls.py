@@ -79,3 +79,32 @@ def test_gradient_of_a_line_is_that_of_the_run_it_returns(spec, precision):
         assert torch.equal(s.state(), ref.state()), every
         base = base or (gu, ga)
         assert torch.equal(gu, base[0]) and ga == base[1], every
+
+
+def test_a_long_call_is_several_launches():
+    """40000 steps of a tiny line: three launches of at most 16384 steps (graph
+    nodes of a captured call), the same bits as in short calls, and a replay goes
+    on from the step the device holds."""
+    import ctypes
+    case = _case(16, 2, 2, "euler", "advdiff", "rng", 3, 40000)
+    u0 = torch.from_numpy(initial_field(case))
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        ref = solver_for(case, "f64")
+        ref.set_state(u0)
+        for _ in range(80):
+            ref.step(1000)
+        s = solver_for(case, "f64")
+        s.set_state(u0)
+        s.step(0)
+        side.synchronize()
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g, stream=side):
+            s.step(40000)
+        count = ctypes.c_size_t(0)
+        hip = ctypes.CDLL("libamdhip64.so")
+        assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+        assert count.value == 3
+        g.replay()
+        s.step(40000)
+        assert torch.equal(s.state(), ref.state())
