@@ -2,8 +2,8 @@
 
 A tuned variant depends on the device and on the problem's class, not on
 its data: the key is (architecture, compute units, ndim, PE edges, order, T,
-scheme, precision, integrator, equation, delay mode). Entries live in one
-JSON file; writes replace the file atomically. Nothing here runs any part of
+scheme, precision, integrator, equation, delay mode), and the version of the
+kernels it was timed on. Entries live in one JSON file; writes replace the file atomically. Nothing here runs any part of
 the method: the timing itself is ``at_autotune`` in the library.
 """
 import json
@@ -11,6 +11,18 @@ import os
 import tempfile
 
 __all__ = ["default_path", "make_key", "make_ens_key", "lookup", "store"]
+
+
+# Raised when a kernel change makes the schedules timed before it wrong choices;
+# entries of another version are not found. (Version 1 has no mark in the key:
+# entries stored before there was one.) Ensembles: 2 since a schedule decides
+# which members stay on their compute unit.
+SWEEP_KERNELS = 1
+ENSEMBLE_KERNELS = 2
+
+
+def _mark(version):
+    return "" if version == 1 else f"|v{version}"
 
 
 def default_path():
@@ -21,7 +33,7 @@ def default_path():
 def make_key(arch, cus, ndim, edges, order, T, scheme, precision, integrator, equation, mode):
     b = "x".join(str(int(v)) for v in edges)
     return f"{arch}|cu{int(cus)}|dim{int(ndim)}|b{b}|o{int(order)}|T{int(T)}|{scheme}|{precision}|" \
-           f"{integrator}|{equation}|{mode}"
+           f"{integrator}|{equation}|{mode}{_mark(SWEEP_KERNELS)}"
 
 
 def make_ens_key(arch, cus, members, precision):
@@ -32,7 +44,7 @@ def make_ens_key(arch, cus, members, precision):
     for m in members:
         h.update(f"{int(m['n'])},{int(m['pe'])},{int(m['order'])},{m.get('integrator', 'euler')},"
                  f"{int(m.get('L', 1))},{int(m.get('T', 0))},{m.get('mode', 'rng')};".encode())
-    return f"{arch}|cu{int(cus)}|ensemble|{len(members)}|{precision}|{h.hexdigest()[:16]}"
+    return f"{arch}|cu{int(cus)}|ensemble|{len(members)}|{precision}|{h.hexdigest()[:16]}{_mark(ENSEMBLE_KERNELS)}"
 
 
 def _load(path):

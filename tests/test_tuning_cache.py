@@ -27,3 +27,20 @@ def test_unreadable_or_foreign_cache_is_a_miss(tmp_path):
     assert tuning.lookup(str(path), "k") is None
     tuning.store(str(path), "k", 1, {})
     assert tuning.lookup(str(path), "k") == {"variant": 1, "ms": {}}
+
+
+def test_an_entry_timed_on_other_kernels_is_a_miss(tmp_path, monkeypatch):
+    path = str(tmp_path / "tuning.json")
+    members = [dict(n=1024, pe=16, order=2, L=4)]
+    sweep = ("gfx950", 256, 3, (32, 32, 32), 4, 0, "time", "f32", "ab2", "advdiff", "rng")
+    # what an earlier build stored for an ensemble: the key without a version
+    unversioned = tuning.make_ens_key("gfx950", 256, members, "f32").rsplit("|v", 1)[0]
+    tuning.store(path, unversioned, [1, 512], {})
+    assert tuning.lookup(path, tuning.make_ens_key("gfx950", 256, members, "f32")) is None
+    tuning.store(path, tuning.make_ens_key("gfx950", 256, members, "f32"), [1, 1024], {})
+    tuning.store(path, tuning.make_key(*sweep), 2, {})
+    assert tuning.lookup(path, tuning.make_key(*sweep))["variant"] == 2
+    monkeypatch.setattr(tuning, "ENSEMBLE_KERNELS", tuning.ENSEMBLE_KERNELS + 1)
+    monkeypatch.setattr(tuning, "SWEEP_KERNELS", tuning.SWEEP_KERNELS + 1)
+    assert tuning.lookup(path, tuning.make_ens_key("gfx950", 256, members, "f32")) is None
+    assert tuning.lookup(path, tuning.make_key(*sweep)) is None
