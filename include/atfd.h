@@ -310,11 +310,15 @@ const char* at_last_error(const at_ctx* ctx);
  * the recomputed forward levels of the segment. *grad_alpha receives
  * dJ/dalpha = sum_n <dJ/df^n, d f^n / d alpha>, accumulated in double in a
  * fixed order. The context is left at step N with the forward field.
- * Scratch (device, 256-B aligned) of at_adjoint_scratch_size bytes holds the
- * checkpoints, the levels of one segment and a ring that keeps all of them (two
- * sets when one takes at most 4 GB: segment s-1 is then recomputed on a second
- * stream of the library, at default priority, while segment s is reversed),
- * three adjoint fields and the adjoint ring. Synchronises the stream.
+ * Scratch (device, 256-B aligned) of at_adjoint_scratch_size bytes holds a
+ * checkpoint (the field, the integrator's history and a ring of L + T slots; RK2
+ * two) for every segment but the last, the levels of one segment (RK2: and its
+ * predictors) with its ring (RK2: two) of L + T slots, two such sets where one
+ * takes at most 4 GiB (segment s-1 is then recomputed on a second stream of the
+ * library, at default priority, while segment s is reversed), three adjoint
+ * fields (RK2: four) and the adjoint ring (RK2: two); and at most 24 GiB for ring
+ * slots of all the segment's levels, which spare the reversal putting them back.
+ * Synchronises the stream.
  * AT_ESTATE unless the context is at step 0.
  */
 at_status at_adjoint_scratch_size(at_ctx* ctx, int64_t nsteps, int32_t every, size_t* bytes);

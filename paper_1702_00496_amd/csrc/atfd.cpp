@@ -486,7 +486,7 @@ at_status at_set_state(at_ctx* c, const void* u0_dev) {
   if (!c || !u0_dev) return fail(c, AT_EINVAL, "null argument");
   HIP_TRY(c, launch_field_copy(c->sp, c->g.f64, u0_dev, c->sp.ubuf[0], true, c->stream));
   HIP_TRY(c, launch_set_counter(c->sp.counter, 0, c->stream));
-  if (c->delay.mode != AT_SYNC) HIP_TRY(c, launch_publish_level0(c->sp, c->g.f64, c->g.sd, c->stream));
+  if (c->delay.mode != AT_SYNC) HIP_TRY(c, launch_publish_level(c->sp, c->g.f64, c->g.sd, 0, c->stream));
   c->n = 0;
   c->state_set = true;
   return AT_OK;
@@ -830,14 +830,20 @@ namespace {
 // (the field, the integrator history and the ring levels a later step can
 // read). A level set holds one segment: its levels (contiguous fields:
 // u^seg .. u^{seg+every}, and for RK2 the predictors u*^seg ..
-// u*^{seg+every-1}) and the segment's rings, which have a slot for every level
-// of the segment besides the L + T - 1 before it, so that the reversal reads
-// the delayed levels from them; two sets when they fit kOverlapBytes (then
-// segment s-1 is recomputed on a second stream while segment s is reversed).
-// Then the adjoint fields (lambda x3, sigma), the forward halo buffer, the
-// adjoint ring (two for RK2), alpha partial sums and the recomputation's step
-// counter.
-constexpr size_t kOverlapBytes = size_t(4) << 30;
+// u*^{seg+every-1}) and the segment's rings, which the reversal reads the delayed
+// levels from; two sets when the levels and rings of L + T slots fit kOverlapBytes
+// (then segment s-1 is recomputed on a second stream while segment s is
+// reversed). A segment's ring has L + T slots and as many more as kRingBytes hold,
+// up to one for every level of the segment. Where it has fewer, the last levels
+// are in it after the recomputation, and the reversal puts the older ones back as
+// it goes, from the stored levels or from the ring at the start of the segment
+// (the checkpoint's; the last segment's is kept in `tail`). Then the adjoint
+// fields (lambda x3, sigma), the forward halo buffer (strip and stage kernels),
+// the adjoint ring (two for RK2), alpha partial sums and the recomputation's step
+// counter. kRingBytes, a twelfth of the card's memory, is what all that may take
+// beyond rings of L + T slots: putting a level back costs a launch that reads the
+// field (512^3 FP32 in 32^3 PEs, Heun: 0.7 ms of a reversed step's 6.0).
+constexpr size_t kOverlapBytes = size_t(4) << 30, kRingBytes = size_t(24) << 30;
 
 struct AdjSet {
   size_t levels = 0, slevels = 0, ring = 0, sring = 0;
@@ -846,6 +852,7 @@ struct AdjSet {
 struct AdjLayout {
   size_t ck = 0, ck_f[2] = {0, 0}, ck_ring = 0, ck_sring = 0;   // checkpoint size and offsets inside one
   size_t off_lam[3] = {0, 0, 0}, off_sigma = 0;
+  size_t off_tail = 0, off_stail = 0;
   size_t off_hbuf = 0, off_aring = 0, off_bring = 0;
   size_t off_partial = 0, off_out = 0, off_counter = 0, total = 0, aring_bytes = 0;
   AdjSet set[2];
@@ -853,6 +860,7 @@ struct AdjLayout {
   int64_t nck = 0;         // segments
   int anslots = 0;
   int rslots = 0;          // slots of a segment's ring (0: the synchronous arm has none)
+  bool whole = false;      // ... with one for every level of the segment
   bool rk2 = false;
   bool gather = false;     // gathering stage kernels: nothing of the adjoint ring is read before it is written
 };
@@ -878,21 +886,28 @@ AdjLayout adj_layout(const at_ctx* c, int64_t nsteps, int every) {
   off = a.ck * static_cast<size_t>(a.nck - 1);
   // a segment of fewer steps than `every` (a short run) needs no more levels
   const int64_t seg = std::min<int64_t>(every, nsteps);
-  a.rslots = l.nslots ? static_cast<int>(l.nslots + seg) : 0;
   const size_t slot = static_cast<size_t>(c->g.npe) * l.pe_block * w;
-  const size_t ring = slot * static_cast<size_t>(a.rslots);
-  const size_t seg_bytes = l.field_bytes * static_cast<size_t>(seg + 1) + ring +
-                           (a.rk2 ? l.field_bytes * static_cast<size_t>(seg) + ring : 0);
+  const size_t nrings = a.rk2 ? 2 : 1;
+  const size_t seg_bytes = l.field_bytes * static_cast<size_t>(seg + 1) + (a.rk2 ? l.field_bytes * static_cast<size_t>(seg) : 0) +
+                           nrings * l.ring_bytes;
   a.nsets = a.nck > 1 && seg_bytes <= kOverlapBytes ? 2 : 1;
+  const int64_t more = l.nslots ? std::min<int64_t>(seg, static_cast<int64_t>(kRingBytes / (slot * nrings * a.nsets))) : 0;
+  a.whole = more == seg;
+  a.rslots = l.nslots + static_cast<int>(more);
+  const size_t ring = slot * static_cast<size_t>(a.rslots);
   for (int k = 0; k < a.nsets; ++k) {
     a.set[k].levels = take(l.field_bytes * static_cast<size_t>(seg + 1));
     if (a.rk2) a.set[k].slevels = take(l.field_bytes * static_cast<size_t>(seg));
     a.set[k].ring = take(ring);
     if (a.rk2) a.set[k].sring = take(ring);
   }
+  if (l.nslots && !a.whole) {
+    a.off_tail = take(l.ring_bytes);
+    if (a.rk2) a.off_stail = take(l.ring_bytes);
+  }
   for (int i = 0; i < 3; ++i) a.off_lam[i] = take(l.field_bytes);
   if (a.rk2) a.off_sigma = take(l.field_bytes);
-  a.off_hbuf = take(slot);
+  a.off_hbuf = take(a.gather ? 0 : slot);
   a.anslots = c->delay.mode == AT_SYNC ? 1 : l.nslots;
   a.aring_bytes = static_cast<size_t>(a.anslots) * slot / w * (a.gather ? w : sizeof(double));
   a.off_aring = take(a.aring_bytes);
@@ -1010,6 +1025,11 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
         p.sring = sc + z.sring;
         HIP_TRY(c, launch_ring_levels(c->sp, f64, sring, l.nslots, p.sring, a.rslots, lo, seg - lo, st));
       }
+      if (last && !a.whole) {
+        HIP_TRY(c, launch_ring_levels(c->sp, f64, ring, l.nslots, sc + a.off_tail, l.nslots, lo, seg - lo + 1, st));
+        if (a.rk2)
+          HIP_TRY(c, launch_ring_levels(c->sp, f64, sring, l.nslots, sc + a.off_stail, l.nslots, lo, seg - lo, st));
+      }
     }
     for (int64_t j = 1; j <= len; ++j) {
       const int64_t n = seg + j - 1;
@@ -1082,7 +1102,26 @@ at_status at_adjoint(at_ctx* c, int64_t nsteps, int32_t every, const void* seed_
     unsigned char* slevels = a.rk2 ? sc + a.set[k].slevels : nullptr;
     const int64_t seg = s * every;
     const int64_t len = std::min<int64_t>(every, N - seg);
+    // Level m of the stage field back into the segment's ring, where the
+    // recomputation has written a later level over it.
+    auto put_back = [&](int64_t m, const unsigned char* stored, unsigned char* ring, const unsigned char* start) -> hipError_t {
+      if (m < 0) return hipSuccess;
+      if (m < seg) return launch_ring_levels(c->sp, f64, start, l.nslots, ring, a.rslots, m, 1, c->stream);
+      StepParams p = c->sp;
+      p.ubuf[0] = const_cast<unsigned char*>(stored + l.field_bytes * (m - seg));
+      p.ring = ring;
+      p.nslots = a.rslots;
+      return launch_publish_level(p, f64, c->g.sd, mod_small(m, a.rslots), c->stream);
+    };
     for (int64_t n = seg + len - 1; n >= seg; --n) {
+      if (l.nslots && n - reach + 1 <= seg + len - a.rslots) {
+        // (the reversal of n + 1 had all the older ones but this)
+        const bool last = s + 1 == a.nck;
+        const unsigned char* ck = sc + a.ck * s;
+        HIP_TRY(c, put_back(n - reach + 1, levels, sc + a.set[k].ring, last ? sc + a.off_tail : ck + a.ck_ring));
+        if (a.rk2)
+          HIP_TRY(c, put_back(n - reach + 1, slevels, sc + a.set[k].sring, last ? sc + a.off_stail : ck + a.ck_sring));
+      }
       AdjParams q;
       std::memset(&q, 0, sizeof(q));
       q.sp = c->sp;

@@ -301,7 +301,8 @@ struct NormParams {
 
 // Launchers (step.hip / norms.hip). Return the HIP error of the launch.
 hipError_t launch_step(const StepParams& p, bool f64, int s, hipStream_t st);
-hipError_t launch_publish_level0(const StepParams& p, bool f64, int s, hipStream_t st);
+// The edge strips of field p.ubuf[0] into slot `slot` of p.ring.
+hipError_t launch_publish_level(const StepParams& p, bool f64, int s, int slot, hipStream_t st);
 // Copy a field between the caller's [z][y][x] layout and the context's
 // (PE-major where p.pe_major is set, else a plain copy).
 hipError_t launch_field_copy(const StepParams& p, bool f64, const void* src, void* dst, bool to_internal,

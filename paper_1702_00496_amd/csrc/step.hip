@@ -27,9 +27,10 @@ namespace {
 
 using namespace sweep;
 
-// The edge strips of the current field u^0 into the ring slot of level 0. The
-// other slots, and the predictor's ring, hold levels the run publishes before
-// it reads them: the start-up clamp keeps every level of nonzero weight at or
+// The edge strips of field ubuf[0] into ring slot `slot`: u^0 into the slot of
+// level 0 when a state is set, and a stored level into a segment's ring that
+// keeps only the last of them (the adjoint). At a new state the other slots, and
+// the predictor's ring, hold levels the run publishes before it reads them: the start-up clamp keeps every level of nonzero weight at or
 // above 0, and a level of weight zero is dropped by a select (or re-reads a
 // live one).
 //
@@ -41,7 +42,7 @@ using namespace sweep;
 // filling all slots of both rings took 4.9 to 6.5 ms. 192^3 in 4^3 PEs, FP64:
 // 1121 -> 14 us; 256^3 in 8^3 PEs, FP32: 423 -> 25 us.
 template <typename Real, int DIM, int S>
-__global__ __launch_bounds__(kThreads) void publish_level0_kernel(StepParams p) {
+__global__ __launch_bounds__(kThreads) void publish_level_kernel(StepParams p, int slot) {
   const Real* __restrict__ u = static_cast<const Real*>(p.ubuf[0]);
   Real* __restrict__ R = static_cast<Real*>(p.ring);
   const int bx = p.bx, by = DIM >= 2 ? p.by : 1, bz = DIM == 3 ? p.bz : 1;
@@ -58,7 +59,7 @@ __global__ __launch_bounds__(kThreads) void publish_level0_kernel(StepParams p) 
       if (h < nxh) {   // x faces: [y][d]
         const int side = h >= S * by ? 1 : 0, r = side ? h - S * by : h;
         const int y = r / S, d = r - y * S;
-        R[ring_index(p, 0, pid, side, z, r)] = u[base + y * pitch + (side ? bx - S + d : d)];
+        R[ring_index(p, slot, pid, side, z, r)] = u[base + y * pitch + (side ? bx - S + d : d)];
       } else {         // y faces: [d][x]
         const int hy = h - nxh;
         const int side = hy >= S * bx ? 1 : 0, r = side ? hy - S * bx : hy;
@@ -69,7 +70,7 @@ __global__ __launch_bounds__(kThreads) void publish_level0_kernel(StepParams p) 
             x -= bx;
             ++d;
           }
-        R[ring_index(p, 0, pid, 2 + side, z, r)] = u[base + (side ? by - S + d : d) * pitch + x];
+        R[ring_index(p, slot, pid, 2 + side, z, r)] = u[base + (side ? by - S + d : d) * pitch + x];
       }
     }
     if (DIM == 3 && (z < S || z >= bz - S)) {   // z faces: depth plane [y][x]
@@ -77,8 +78,8 @@ __global__ __launch_bounds__(kThreads) void publish_level0_kernel(StepParams p) 
       for (int i = threadIdx.x; i < area; i += blockDim.x) {
         const int y = i / bx, x = i - y * bx;
         const Real v = u[base + y * pitch + x];
-        if (z < S) R[ring_index(p, 0, pid, 4, z, i)] = v;
-        if (z >= bz - S) R[ring_index(p, 0, pid, 5, z - (bz - S), i)] = v;
+        if (z < S) R[ring_index(p, slot, pid, 4, z, i)] = v;
+        if (z >= bz - S) R[ring_index(p, slot, pid, 5, z - (bz - S), i)] = v;
       }
     }
   }
@@ -294,40 +295,41 @@ hipError_t launch_t(const StepParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Workgroups of the level-0 publish: eight 4-wave workgroups per CU.
+// Workgroups of a level's publish: eight 4-wave workgroups per CU.
 constexpr int kPublishBlocks = 2048;
 
 template <typename Real, int DIM, int S>
-hipError_t launch_pub_t(const StepParams& p, hipStream_t st) {
+hipError_t launch_pub_t(const StepParams& p, int slot, hipStream_t st) {
   const int64_t planes = static_cast<int64_t>(p.npe) * (DIM == 3 ? p.bz : 1);
   const int blocks = static_cast<int>(std::min<int64_t>(planes, kPublishBlocks));
-  hipLaunchKernelGGL((publish_level0_kernel<Real, DIM, S>), dim3(blocks), dim3(kThreads), 0, st, p);
+  hipLaunchKernelGGL((publish_level_kernel<Real, DIM, S>), dim3(blocks), dim3(kThreads), 0, st, p, slot);
   return hipGetLastError();
 }
 
 // Sweep launches by half-width s (and the space-expanded scheme, s = 1);
-// level-0 publishes by strip depth s.
+// publishes of a level (slot >= 0) by strip depth s.
 template <typename Real, int DIM>
-hipError_t dispatch_s(const StepParams& p, int s, hipStream_t st, bool pub) {
+hipError_t dispatch_s(const StepParams& p, int s, hipStream_t st, int slot) {
+  const bool pub = slot >= 0;
   if (!pub && p.scheme != AT_SCHEME_TIME) {
     if (s != 1) return hipErrorInvalidValue;
     if (p.scheme == AT_SCHEME_NONUNIFORM_212) return launch_t<Real, DIM, 1, 3>(p, st);
     return p.scheme == AT_SCHEME_SPACE_212 ? launch_t<Real, DIM, 1, 1>(p, st) : launch_t<Real, DIM, 1, 2>(p, st);
   }
   switch (s) {
-    case 1: return pub ? launch_pub_t<Real, DIM, 1>(p, st) : launch_t<Real, DIM, 1, 0>(p, st);
-    case 2: return pub ? launch_pub_t<Real, DIM, 2>(p, st) : launch_t<Real, DIM, 2, 0>(p, st);
-    case 3: return pub ? launch_pub_t<Real, DIM, 3>(p, st) : launch_t<Real, DIM, 3, 0>(p, st);
+    case 1: return pub ? launch_pub_t<Real, DIM, 1>(p, slot, st) : launch_t<Real, DIM, 1, 0>(p, st);
+    case 2: return pub ? launch_pub_t<Real, DIM, 2>(p, slot, st) : launch_t<Real, DIM, 2, 0>(p, st);
+    case 3: return pub ? launch_pub_t<Real, DIM, 3>(p, slot, st) : launch_t<Real, DIM, 3, 0>(p, st);
   }
   return hipErrorInvalidValue;
 }
 
 template <typename Real>
-hipError_t dispatch_dim(const StepParams& p, int s, hipStream_t st, bool pub) {
+hipError_t dispatch_dim(const StepParams& p, int s, hipStream_t st, int slot) {
   switch (p.ndim) {
-    case 1: return dispatch_s<Real, 1>(p, s, st, pub);
-    case 2: return dispatch_s<Real, 2>(p, s, st, pub);
-    case 3: return dispatch_s<Real, 3>(p, s, st, pub);
+    case 1: return dispatch_s<Real, 1>(p, s, st, slot);
+    case 2: return dispatch_s<Real, 2>(p, s, st, slot);
+    case 3: return dispatch_s<Real, 3>(p, s, st, slot);
   }
   return hipErrorInvalidValue;
 }
@@ -367,7 +369,7 @@ hipError_t launch_step(const StepParams& p, bool f64, int s, hipStream_t st) {
   // PE-major fields are stepped by the 32 x 32 path only (the host accepts
   // only schedule variants that apply)
   if (p.pe_major) return fast3d_applies(p, f64) ? launch_step_fast3d(p, f64, s, st) : hipErrorInvalidValue;
-  return f64 ? dispatch_dim<double>(p, s, st, false) : dispatch_dim<float>(p, s, st, false);
+  return f64 ? dispatch_dim<double>(p, s, st, -1) : dispatch_dim<float>(p, s, st, -1);
 }
 
 hipError_t launch_field_copy(const StepParams& p, bool f64, const void* src, void* dst, bool to_internal,
@@ -397,8 +399,9 @@ hipError_t launch_field_copy(const StepParams& p, bool f64, const void* src, voi
   return hipGetLastError();
 }
 
-hipError_t launch_publish_level0(const StepParams& p, bool f64, int s, hipStream_t st) {
-  return f64 ? dispatch_dim<double>(p, s, st, true) : dispatch_dim<float>(p, s, st, true);
+hipError_t launch_publish_level(const StepParams& p, bool f64, int s, int slot, hipStream_t st) {
+  if (slot < 0 || slot >= p.nslots) return hipErrorInvalidValue;
+  return f64 ? dispatch_dim<double>(p, s, st, slot) : dispatch_dim<float>(p, s, st, slot);
 }
 
 size_t step_lds_bytes(const StepParams& p, bool f64, int s) {
