@@ -417,6 +417,7 @@ hipError_t launch_strip(const AdjParams& q, int blocks, hipStream_t st) {
   return hipGetLastError();
 }
 
+// (2-D and 3-D: a 1-D PE's line always fits the 1-D kernel's LDS)
 template <typename Real>
 hipError_t launch_lambda(const AdjParams& q, int blocks, hipStream_t st) {
   const int key = q.sp.ndim * 10 + q.sp.s;
@@ -425,7 +426,6 @@ hipError_t launch_lambda(const AdjParams& q, int blocks, hipStream_t st) {
   case D * 10 + S:                                                                                   \
     hipLaunchKernelGGL((adj_lambda_kernel<Real, D, S>), dim3(blocks), dim3(kAdjThreads), 0, st, q); \
     break;
-    ATFD_ADJ_CASE(1, 1) ATFD_ADJ_CASE(1, 2) ATFD_ADJ_CASE(1, 3)
     ATFD_ADJ_CASE(2, 1) ATFD_ADJ_CASE(2, 2) ATFD_ADJ_CASE(2, 3)
     ATFD_ADJ_CASE(3, 1) ATFD_ADJ_CASE(3, 2) ATFD_ADJ_CASE(3, 3)
 #undef ATFD_ADJ_CASE

@@ -211,10 +211,11 @@ __global__ __launch_bounds__(1024) void adj2d_kernel(AdjParams q) {
   for (int a = 0; a < DIM; ++a)
 #pragma unroll
     for (int o = 1; o <= S; ++o) ksum += fc.t1[a][0][o] + fc.t1[a][1][o];
-  // The Laplacian of FP32 fields: sums of neighbours are exact in double, and
-  // the centre enters once (lap0) instead of in every difference: two of the
-  // six to eleven FP64 operations of a neighbour pair less. FP64 fields keep
-  // the differences, which lose less to cancellation.
+  // The Laplacian of FP32 fields: a sum of two neighbours rounds at 2^-53 at most
+  // (exact while their exponents lie within 29 of each other), far below the
+  // fields' own rounding, and the centre enters once (lap0) instead of in every
+  // difference: two of the six to eleven FP64 operations of a neighbour pair less.
+  // FP64 fields keep the differences, which lose less to cancellation.
   constexpr bool kSum = sizeof(Real) == 4;
   double lap0 = 0.0;
 #pragma unroll

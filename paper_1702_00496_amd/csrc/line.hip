@@ -4,8 +4,9 @@
 //
 // A step of the per-step sweep costs a launch and its memory round trips,
 // about 6 us whatever the size; here it is a chain of LDS reads and one
-// barrier. 256 points in 8 PEs, second order, Euler, FP64: 5.9 -> 0.5 us a
-// step; 252 points in 6 PEs, fourth-order Burgers, AB2, FP64: 6.8 -> 0.8 us.
+// barrier (Heun: two). 256 points in 8 PEs, second order, Euler, FP64: 5.9 -> 0.5
+// us a step; 252 points in 6 PEs, fourth-order Burgers, AB2, FP64: 6.8 -> 0.8 us.
+// (Compiled for 1024 threads at any size: the sixth-order FP64 forms spill.)
 
 #include "line.hpp"
 

@@ -14,7 +14,7 @@
 // batch of steps at a time by all threads. Microseconds a step, FP32, order 2
 // / fourth-order AB2 with L = 2: 1024 points 0.51 / 0.76, 8192 0.85 / 1.26,
 // 32768 1.53 / 3.17, 65536 2.84 / 6.58 (streamed through the caches: 65536
-// points, fourth order, about 30); the per-step launch of a 1-D context 5.9.
+// points, fourth order, about 30); a sweep per step of a 1-D context 5 to 6.
 #pragma once
 
 #include "atfd_internal.hpp"
@@ -70,11 +70,11 @@ inline __host__ __device__ int64_t line_lds_ring(int s, int npe, int nslots, int
 // unit; pt = 0 if there is none. A step costs a wave about 180 instructions
 // and 12 a point, and the waves of a SIMD take turns: the PT with the smallest
 // product of waves per SIMD and instructions per wave is taken (4096 points,
-// fourth-order AB2, FP32: 1.63 us a step with 4 points per thread, 1.00 with 16). Registers hold u and, for
-// AB2, f: 32 FP32 (16 FP64) points of both or twice as many of u alone, out of
-// the 128 registers a thread of a 1024-thread workgroup has; one size above
-// that AB2 keeps f in device memory (whole chunks only: it is stored
-// chunk-transposed), which costs about twice as much.
+// fourth-order AB2, FP32: 1.63 us a step with 4 points per thread, 1.00 with 16).
+// Registers hold u and, for AB2, f: 32 FP32 (16 FP64) points of both or twice as
+// many of u alone, out of the 128 registers a thread of a 1024-thread workgroup
+// has; one size above that AB2 keeps f in device memory (whole chunks only: it is
+// stored chunk-transposed), which costs about twice as much.
 inline __host__ __device__ LinePlan line_plan(const Line& M, int w, int threads, int64_t lds, int max_pt, int share) {
   LinePlan best{0, 0, 0, 0, 0};
   // (the kernels combine the schemes' own level count)
